@@ -231,3 +231,41 @@ def test_connect_protocol_with_separate_tables(block):
         assert np.array_equal(out[o:o + p.size], p)
     # bytes that crossed the network: the packed MISS blocks, not the held ones
     assert int(tot[3]) < int(lens.sum())
+
+
+@pytest.mark.parametrize("block,reps", [(4096, 40), (32768, 20), (65536, 20), (65536, 1)])
+def test_copy_piece_edges(block, reps):
+    """Payload sizes around the copies' 16-byte words, their 4 KiB and 16 KiB pieces and the
+    block; many short payloads (fewer than four blocks per payload) and a few long ones."""
+    g0 = np.random.default_rng([17, block, reps])
+    sizes = [0, 1, 15, 16, 17, 1023, 1025, 4095, 4096, 4097, 8192 + 7, 16383, 16384, 16385, block - 1, block, block + 1]
+    sizes = sizes * reps if reps > 1 else [4 * block, 9 * block + 4097, 3 * block + 16385]
+    payloads = [g0.integers(0, 256, n, dtype=np.uint8) for n in sizes]
+    held = [p[:block].tobytes() for p in payloads[::3] if p.size >= block]
+    say("copy piece edges", block, len(sizes))
+    check_round_trip(payloads, block, held, skew=reps % 3)
+
+
+@pytest.mark.parametrize("n_seg,hi", [(3, 5), (70_000, 3), (300_000, 5), (2000, 6000)])
+def test_plan_tiles(n_seg, hi):
+    """The plan's tile sizes (256 to 2,048 blocks) and its three-launch path, on statuses
+    of every kind, against running sums on the host."""
+    g0 = np.random.default_rng([19, n_seg])
+    lens = g0.integers(0, hi * 4096 + 1, n_seg).astype(np.uint64)
+    batch = g.Batch(np.zeros(n_seg, np.uint64), lens, 4096)  # the plan reads no payload
+    n = batch.n_blocks
+    say("plan tiles", n_seg, n)
+    status = g0.integers(0, 3, n).astype(np.uint8)
+    digest, ref = (g0.integers(0, 1 << 63, n).astype(np.uint64) for _ in range(2))
+    records, totals = g.send_plan(batch, keys_to_device(digest), to_device(status), keys_to_device(ref))
+    rec = g.records_to_numpy(records)
+    seg = np.repeat(np.arange(n_seg), np.diff(batch.host_first.astype(np.int64)))
+    off = (np.arange(n) - batch.host_first[seg].astype(np.int64)) * 4096
+    length = np.minimum(lens[seg].astype(np.int64) - off, 4096)
+    size = np.where(status == g.MISS, (length + 15) // 16 * 16, 0)
+    ident = np.where(status == g.MISS, (np.cumsum(size) - size).astype(np.uint64),
+                     np.where(status == g.HIT_CACHE, digest, ref))
+    for name, want in (("block", np.arange(n)), ("payload", seg), ("offset", off), ("length", length),
+                       ("kind", status), ("ident", ident)):
+        assert np.array_equal(rec[name].astype(np.uint64), np.asarray(want).astype(np.uint64)), name
+    assert u64(totals).tolist() == [int((status == k).sum()) for k in (g.MISS, g.HIT_CACHE, g.HIT_BATCH)] + [int(size.sum())]
