@@ -4,16 +4,22 @@
 // library sort, no memsets): a caller may capture them in a HIP graph.
 //
 // Keys are 64 or 128 bits (hi:lo), indices u32. Each pass sorts by one 8-bit digit,
-// stably, in three launches over 4096-element tiles:
-//   1. histogram: each tile counts its digits (LDS atomics) into a digit-major array
-//      count[d][tile];
-//   2. scan: one workgroup per digit turns its row into exclusive tile offsets, and the
-//      digit's total goes to totals[d];
-//   3. scatter: each wave of a tile owns 1024 consecutive elements and ranks them
-//      stably (the lanes holding one digit find each other with eight ballots, a running
-//      per-digit count in LDS carries the rank across the wave's rounds); the tile is
-//      then reordered in LDS by digit and written out word by word, so consecutive
-//      lanes store consecutive addresses of one digit's run.
+// stably, over 4096-element tiles. Launches: one clear, one histogram of every digit of
+// every pass (a digit's counts do not depend on the order), then one kernel per pass:
+//   - a workgroup takes the next tile by a ticket; each wave of the tile owns 1024
+//     consecutive elements and ranks them stably (the lanes holding one digit find each
+//     other with eight ballots, a running per-digit count in LDS carries the rank across
+//     the wave's rounds);
+//   - it publishes the tile's count of each digit, and thread d sums digit d's counts of
+//     the tiles before it, back to the nearest tile that has already published its running
+//     sum. A tile publishes its counts before it waits for any other, and the tiles before
+//     it have smaller tickets, so they are running or done: every wait ends, however few
+//     workgroups the GPU holds at once;
+//   - the tile is reordered in LDS by digit and written out word by word, so consecutive
+//     lanes store consecutive addresses of one digit's run.
+// What it is bound by: launches below about a million elements (three launches per pass,
+// with separate histograms and scans, took 24 and 48 launches of at least 4 us), and the
+// scattered writes of the passes above.
 // A pass whose digit is the same for every key moves nothing and is skipped on the
 // device: the caller supplies the AND and the OR of all key words, the pass kernels
 // return at once for such a pass, and the buffers' roles (which holds the input) follow
@@ -62,64 +68,51 @@ __device__ __forceinline__ SortBuf sort_result(const SortBuf& a, const SortBuf& 
   return reads_b(bits, 8u * (uint32_t)words) ? b : a;
 }
 
-__global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortBuf a, SortBuf b, const uint64_t* n_dev,
-                                                                 const uint64_t* bits, uint32_t pass,
-                                                                 uint32_t* count, uint64_t tiles) {
-  if (pass_trivial(bits, pass)) return;
-  __shared__ uint32_t h[kDigits];
-  const SortBuf in = reads_b(bits, pass) ? b : a;
-  const uint64_t* word = pass >= 8 ? in.hi : in.lo;
-  const uint32_t sh = (8 * pass) & 63;
-  const uint64_t n = *n_dev;
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-  const uint64_t last = n ? n - 1 : 0;  // element 0 exists: the buffers hold n_max >= 1
-  uint64_t w[kSortItems];
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {  // unconditional (clamped) loads, issued together
-    const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
-    w[r] = word[i < last ? i : last];
-  }
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
-    if (i < n) atomicAdd(&h[(uint32_t)(w[r] >> sh) & 0xFFu], 1u);
-  }
-  __syncthreads();
-  count[(uint64_t)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+// Zeroes the digit totals, the passes' tickets and the tiles' states.
+__global__ __launch_bounds__(kSortThreads) void sort_clear_kernel(uint64_t* words, uint64_t n) {
+  const uint64_t stride = (uint64_t)gridDim.x * kSortThreads;
+  for (uint64_t i = (uint64_t)blockIdx.x * kSortThreads + threadIdx.x; i < n; i += stride) words[i] = 0;
 }
 
-// One workgroup per digit: exclusive prefix of count[d][0..tiles) in place, total to totals[d].
-__global__ __launch_bounds__(kSortThreads) void sort_scan_kernel(const uint64_t* bits, uint32_t pass,
-                                                                 uint32_t* count, uint64_t tiles, uint32_t* totals) {
-  if (pass_trivial(bits, pass)) return;
-  __shared__ uint32_t wave_sums[kSortWaves];
-  uint32_t* row = count + (uint64_t)blockIdx.x * tiles;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t carry = 0;
-  for (uint64_t base = 0; base < tiles; base += kSortThreads) {
-    const uint64_t t = base + threadIdx.x;
-    const uint32_t x = t < tiles ? row[t] : 0u;
-    uint32_t incl = x;
+// totals[pass][digit] of every pass that moves anything. A grid of at most
+// kSortHistGrid workgroups walks the tiles, so that their final atomics stay few.
+constexpr uint32_t kSortHistGrid = 256;
+template <int kWords>
+__global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortBuf a, const uint64_t* n_dev, const uint64_t* bits,
+                                                                 uint32_t* totals) {
+  constexpr uint32_t kPasses = 8u * kWords;
+  __shared__ uint32_t h[kPasses][kDigits];
+  const uint64_t n = *n_dev;
+  if ((uint64_t)blockIdx.x * kSortTile >= n) return;
+  for (uint32_t p = 0; p < kPasses; ++p) h[p][threadIdx.x] = 0;
+  __syncthreads();
+  uint32_t moves = 0;  // bit p: pass p moves something
+  for (uint32_t p = 0; p < kPasses; ++p) moves |= pass_trivial(bits, p) ? 0u : 1u << p;
+  for (uint64_t base = (uint64_t)blockIdx.x * kSortTile; base < n; base += (uint64_t)gridDim.x * kSortTile) {
+    uint64_t lo[kSortItems], hi[kSortItems];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += y;
+    for (int r = 0; r < kSortItems; ++r) {  // unconditional (clamped) loads, issued together
+      const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
+      const uint64_t at = i < n ? i : n - 1;
+      lo[r] = a.lo[at];
+      hi[r] = kWords == 2 ? a.hi[at] : 0;
     }
-    if (lane == 63) wave_sums[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0, sum = 0;
+    for (uint32_t p = 0; p < kPasses; ++p) {
+      if (!((moves >> p) & 1u)) continue;
+      const uint32_t sh = (8 * p) & 63;
 #pragma unroll
-    for (int w = 0; w < kSortWaves; ++w) {
-      before += w < wave ? wave_sums[w] : 0u;
-      sum += wave_sums[w];
+      for (int r = 0; r < kSortItems; ++r) {
+        const uint64_t i = base + (uint64_t)r * kSortThreads + threadIdx.x;
+        const uint64_t w = kWords == 2 && p >= 8 ? hi[r] : lo[r];
+        if (i < n) atomicAdd(&h[p][(uint32_t)(w >> sh) & 0xFFu], 1u);
+      }
     }
-    __syncthreads();
-    if (t < tiles) row[t] = carry + before + incl - x;
-    carry += sum;
   }
-  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+  __syncthreads();
+  for (uint32_t p = 0; p < kPasses; ++p) {
+    const uint32_t c = h[p][threadIdx.x];
+    if (c) atomicAdd(&totals[p * kDigits + threadIdx.x], c);
+  }
 }
 
 // Exclusive prefix over the workgroup's 256 threads of two values at once.
@@ -151,119 +144,169 @@ __device__ __forceinline__ void block_excl_scan2(uint32_t& x, uint32_t& y, uint3
   y = by + iy - y;
 }
 
+// A tile's published words, one per digit: {tag, count}. The tags of pass p are 2p + 1
+// (the tile's own count) and 2p + 2 (the count of this tile and all before it), so the
+// words of an earlier pass read as not yet published.
+__device__ __forceinline__ uint64_t sort_state(uint32_t tag, uint32_t count) { return ((uint64_t)tag << 32) | count; }
+
+// The elements with digit threadIdx.x in the tiles before `tile`. Reads kAhead tiles'
+// words at once, from the nearest back.
+constexpr uint32_t kSortAhead = 8;
+__device__ __forceinline__ uint32_t sort_before(uint64_t* state, uint64_t tile, uint32_t pass) {
+  const uint32_t own = 2 * pass + 1, sum = 2 * pass + 2;
+  uint32_t before = 0;
+  uint64_t t = tile;
+  while (t > 0) {
+    uint64_t w[kSortAhead];
+#pragma unroll
+    for (uint32_t k = 0; k < kSortAhead; ++k) {
+      const uint64_t at = t > k + 1 ? t - 1 - k : 0;
+      w[k] = __hip_atomic_load(&state[at * kDigits + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    bool stop = false;
+#pragma unroll
+    for (uint32_t k = 0; k < kSortAhead; ++k) {
+      if (stop || t == 0) continue;
+      const uint32_t tag = (uint32_t)(w[k] >> 32);
+      if (tag != own && tag != sum) {  // not published yet: read again from here
+        stop = true;
+        continue;
+      }
+      before += (uint32_t)w[k];
+      t = tag == sum ? 0 : t - 1;
+    }
+    if (stop) __builtin_amdgcn_s_sleep(1);
+  }
+  return before;
+}
+
 template <int kWords>
-__global__ __launch_bounds__(kSortThreads) void sort_scatter_kernel(SortBuf a, SortBuf b, const uint64_t* n_dev,
-                                                                    const uint64_t* bits, uint32_t pass,
-                                                                    const uint32_t* offset, const uint32_t* totals,
-                                                                    uint64_t tiles) {
+__global__ __launch_bounds__(kSortThreads) void sort_pass_kernel(SortBuf a, SortBuf b, const uint64_t* n_dev,
+                                                                 const uint64_t* bits, uint32_t pass,
+                                                                 const uint32_t* totals, uint64_t* state,
+                                                                 uint32_t* ticket) {
   __shared__ uint32_t run[kSortWaves][kDigits];  // per wave: running digit counts, then first local positions
   __shared__ uint32_t gdelta[kDigits];           // global position = gdelta[d] + local sorted position
   __shared__ uint32_t scan_tmp[kSortWaves][2];
   __shared__ uint64_t xch[kSortTile];            // the tile in local sorted order, one word at a time
   __shared__ uint8_t xdig[kSortTile];            // digit of each local sorted position
+  __shared__ uint32_t my_tile;
   const uint64_t n = *n_dev;
-  const uint64_t tile0 = (uint64_t)blockIdx.x * kSortTile;
-  if (tile0 >= n || pass_trivial(bits, pass)) return;  // uniform over the workgroup
+  // uniform over the workgroup; the workgroups below the tile count take every ticket
+  if ((uint64_t)blockIdx.x * kSortTile >= n || pass_trivial(bits, pass)) return;
   const bool from_b = reads_b(bits, pass);
   const SortBuf in = from_b ? b : a, out = from_b ? a : b;
-  const uint32_t in_tile = (uint32_t)(n - tile0 < kSortTile ? n - tile0 : kSortTile);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t lt_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
   const uint32_t sh = (8 * pass) & 63;
   const bool digit_in_hi = kWords == 2 && pass >= 8;
+  const uint32_t digit_total = totals[threadIdx.x];
 
-  for (int k = threadIdx.x; k < kSortWaves * kDigits; k += kSortThreads) (&run[0][0])[k] = 0;
+  for (;;) {
+    if (threadIdx.x == 0) my_tile = atomicAdd(ticket, 1u);
+    for (int k = threadIdx.x; k < kSortWaves * kDigits; k += kSortThreads) (&run[0][0])[k] = 0;
+    __syncthreads();  // my_tile known, run[] cleared
+    const uint64_t tile = my_tile, tile0 = tile * kSortTile;
+    if (tile0 >= n) return;
+    const uint32_t in_tile = (uint32_t)(n - tile0 < kSortTile ? n - tile0 : kSortTile);
 
-  uint64_t lo[kSortItems], hi[kSortItems];
-  uint32_t ix[kSortItems], dg[kSortItems], pos[kSortItems];
+    uint64_t lo[kSortItems], hi[kSortItems];
+    uint32_t ix[kSortItems], dg[kSortItems], pos[kSortItems];
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {  // unconditional (clamped) loads, issued together
-    const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
-    const uint64_t at = tile0 + (li < in_tile ? li : in_tile - 1);
-    lo[r] = in.lo[at];
-    hi[r] = kWords == 2 ? in.hi[at] : 0;
-    ix[r] = in.idx[at];
-  }
-  __syncthreads();  // run[] cleared
-
-  // rank inside the wave, in element order: earlier rounds through run[wave][d], this
-  // round through the peers below this lane
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
-    const bool valid = li < in_tile;
-    const uint32_t d = (uint32_t)((digit_in_hi ? hi[r] : lo[r]) >> sh) & 0xFFu;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < 8; ++bit) {
-      const uint64_t ones = __ballot(valid && ((d >> bit) & 1u));
-      peers &= ((d >> bit) & 1u) ? ones : ~ones;
+    for (int r = 0; r < kSortItems; ++r) {  // unconditional (clamped) loads, issued together
+      const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
+      const uint64_t at = tile0 + (li < in_tile ? li : in_tile - 1);
+      lo[r] = in.lo[at];
+      hi[r] = kWords == 2 ? in.hi[at] : 0;
+      ix[r] = in.idx[at];
     }
-    const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
-    const uint32_t prior = run[wave][d];
-    dg[r] = d;
-    pos[r] = prior + below;
-    if (valid && below == 0) run[wave][d] = prior + (uint32_t)__popcll(peers);
-    wave_lds_sync();  // this round's counts before the next round's reads
-  }
-  __syncthreads();  // every wave's digit counts complete
 
-  {
-    const int d = threadIdx.x;
-    const uint32_t c0 = run[0][d], c1 = run[1][d], c2 = run[2][d], c3 = run[3][d];
-    uint32_t local = c0 + c1 + c2 + c3;  // becomes the digit's first local position
-    uint32_t global = totals[d];         // becomes the digit's first global position
-    block_excl_scan2(local, global, scan_tmp);
-    __syncthreads();  // run[] read by every thread before it is overwritten
-    run[0][d] = local;
-    run[1][d] = local + c0;
-    run[2][d] = local + c0 + c1;
-    run[3][d] = local + c0 + c1 + c2;
-    gdelta[d] = global + offset[(uint64_t)d * tiles + blockIdx.x] - local;
-  }
-  __syncthreads();
-
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
-    if (li < in_tile) {
-      pos[r] += run[wave][dg[r]];
-      xdig[pos[r]] = (uint8_t)dg[r];
-      xch[pos[r]] = lo[r];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < kSortItems; ++k) {
-    const uint32_t j = k * kSortThreads + threadIdx.x;
-    if (j < in_tile) out.lo[gdelta[xdig[j]] + j] = xch[j];
-  }
-  if (kWords == 2) {
-    __syncthreads();  // xch read out before it is refilled
+    // rank inside the wave, in element order: earlier rounds through run[wave][d], this
+    // round through the peers below this lane
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
       const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
-      if (li < in_tile) xch[pos[r]] = hi[r];
+      const bool valid = li < in_tile;
+      const uint32_t d = (uint32_t)((digit_in_hi ? hi[r] : lo[r]) >> sh) & 0xFFu;
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const uint64_t ones = __ballot(valid && ((d >> bit) & 1u));
+        peers &= ((d >> bit) & 1u) ? ones : ~ones;
+      }
+      const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
+      const uint32_t prior = run[wave][d];
+      dg[r] = d;
+      pos[r] = prior + below;
+      if (valid && below == 0) run[wave][d] = prior + (uint32_t)__popcll(peers);
+      wave_lds_sync();  // this round's counts before the next round's reads
+    }
+    __syncthreads();  // every wave's digit counts complete
+
+    {
+      const int d = threadIdx.x;
+      const uint32_t c0 = run[0][d], c1 = run[1][d], c2 = run[2][d], c3 = run[3][d];
+      const uint32_t count = c0 + c1 + c2 + c3;
+      uint64_t* mine = &state[tile * kDigits + d];
+      __hip_atomic_store(mine, sort_state(2 * pass + (tile ? 1 : 2), count), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t local = count;         // becomes the digit's first local position
+      uint32_t global = digit_total;  // becomes the digit's first global position
+      block_excl_scan2(local, global, scan_tmp);
+      const uint32_t before = sort_before(state, tile, pass);
+      if (tile)
+        __hip_atomic_store(mine, sort_state(2 * pass + 2, before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      run[0][d] = local;  // (only this thread touches column d)
+      run[1][d] = local + c0;
+      run[2][d] = local + c0 + c1;
+      run[3][d] = local + c0 + c1 + c2;
+      gdelta[d] = global + before - local;
+    }
+    __syncthreads();
+
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+      const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
+      if (li < in_tile) {
+        pos[r] += run[wave][dg[r]];
+        xdig[pos[r]] = (uint8_t)dg[r];
+        xch[pos[r]] = lo[r];
+      }
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
       const uint32_t j = k * kSortThreads + threadIdx.x;
-      if (j < in_tile) out.hi[gdelta[xdig[j]] + j] = xch[j];
+      if (j < in_tile) out.lo[gdelta[xdig[j]] + j] = xch[j];
     }
-  }
-  __syncthreads();
-  uint32_t* xidx = reinterpret_cast<uint32_t*>(xch);
+    if (kWords == 2) {
+      __syncthreads();  // xch read out before it is refilled
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
-    if (li < in_tile) xidx[pos[r]] = ix[r];
-  }
-  __syncthreads();
+      for (int r = 0; r < kSortItems; ++r) {
+        const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
+        if (li < in_tile) xch[pos[r]] = hi[r];
+      }
+      __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kSortItems; ++k) {
-    const uint32_t j = k * kSortThreads + threadIdx.x;
-    if (j < in_tile) out.idx[gdelta[xdig[j]] + j] = xidx[j];
+      for (int k = 0; k < kSortItems; ++k) {
+        const uint32_t j = k * kSortThreads + threadIdx.x;
+        if (j < in_tile) out.hi[gdelta[xdig[j]] + j] = xch[j];
+      }
+    }
+    __syncthreads();
+    uint32_t* xidx = reinterpret_cast<uint32_t*>(xch);
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+      const uint32_t li = wave * kSortWaveSpan + r * 64 + lane;
+      if (li < in_tile) xidx[pos[r]] = ix[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSortItems; ++k) {
+      const uint32_t j = k * kSortThreads + threadIdx.x;
+      if (j < in_tile) out.idx[gdelta[xdig[j]] + j] = xidx[j];
+    }
+    __syncthreads();  // run, xch and xdig read out before the next tile
   }
 }
 
@@ -405,11 +448,12 @@ __global__ __launch_bounds__(kSortSmallThreads) void sort_small_kernel(SortBuf a
 }
 
 // Workspace of a sort of n elements with `words` 64-bit key words: the second key/index
-// buffer (b), the digit-major tile counts and the digit totals.
+// buffer (b), the digit totals and tickets of the passes, and the tiles' states.
 struct SortLayout {
   uint64_t tiles;
-  size_t hi, lo, idx, count, totals, total;
+  size_t hi, lo, idx, totals, state, total;
 };
+constexpr uint64_t kSortTotalWords = 16 * kDigits / 2 + 8;  // u64 words: u32 totals[16][256], u32 tickets[16]
 
 // Elements to allocate in each key/index buffer of a sort of at most n elements (the
 // caller's buffer a too): a one-workgroup sort reads whole wave spans.
@@ -430,8 +474,9 @@ inline SortLayout sort_layout(uint64_t n_max, int words) {
   L.hi = take(words == 2 ? 8 * n : 0);
   L.lo = take(8 * n);
   L.idx = take(4 * n);
-  L.count = take(4 * (size_t)kDigits * L.tiles);
-  L.totals = take(4 * kDigits);
+  L.totals = off;  // the states follow the totals: one clear
+  L.state = off + 8 * kSortTotalWords;
+  if (n_max > kSortSmallMax) take(8 * (kSortTotalWords + (size_t)kDigits * L.tiles));
   L.total = off;
   return L;
 }
@@ -448,40 +493,44 @@ inline SortBuf sort_other(void* ws, uint64_t n_max, int words) {
 // of a's arrays holds sort_capacity(n_max) elements.
 // `bits` (device u64[4], see pass_trivial) must describe those keys. The result is in `a`
 // or in the workspace's buffer (sort_other), as sort_result() tells on the device. Grids
-// are sized for n_max; tiles past *n_dev do nothing.
+// are sized for n_max, up to kSortMaxGrid workgroups; those past *n_dev do nothing.
+constexpr uint64_t kSortMaxGrid = 1024;
+template <int kWords>
+gleam_status radix_sort_passes(SortBuf a, const uint64_t* n_dev, const uint64_t* bits, uint64_t n_max, void* ws,
+                               hipStream_t s) {
+  const SortBuf b = sort_other(ws, n_max, kWords);
+  if (n_max <= kSortSmallMax) {
+    hipLaunchKernelGGL(sort_small_kernel<kWords>, dim3(1), dim3(kSortSmallThreads), 0, s, a, b, n_dev, bits, n_max);
+    return launch_status("sort_small_kernel");
+  }
+  const SortLayout L = sort_layout(n_max, kWords);
+  uint8_t* p = static_cast<uint8_t*>(ws);
+  uint32_t* totals = reinterpret_cast<uint32_t*>(p + L.totals);
+  uint64_t* state = reinterpret_cast<uint64_t*>(p + L.state);
+  uint32_t* tickets = totals + 16 * kDigits;
+  const uint64_t clear = kSortTotalWords + kDigits * L.tiles;  // the state follows within the padding
+  const uint64_t clear_grid = (clear + 4 * kSortThreads - 1) / (4 * kSortThreads);
+  hipLaunchKernelGGL(sort_clear_kernel, dim3((uint32_t)(clear_grid < kSortMaxGrid ? clear_grid : kSortMaxGrid)),
+                     dim3(kSortThreads), 0, s, reinterpret_cast<uint64_t*>(totals), clear);
+  gleam_status st = launch_status("sort_clear_kernel");
+  if (st != GLEAM_OK) return st;
+  const uint32_t hist_grid = (uint32_t)(L.tiles < kSortHistGrid ? L.tiles : kSortHistGrid);
+  hipLaunchKernelGGL(sort_hist_kernel<kWords>, dim3(hist_grid), dim3(kSortThreads), 0, s, a, n_dev, bits, totals);
+  if ((st = launch_status("sort_hist_kernel")) != GLEAM_OK) return st;
+  const uint32_t grid = (uint32_t)(L.tiles < kSortMaxGrid ? L.tiles : kSortMaxGrid);
+  for (uint32_t q = 0; q < 8u * kWords; ++q) {
+    hipLaunchKernelGGL(sort_pass_kernel<kWords>, dim3(grid), dim3(kSortThreads), 0, s, a, b, n_dev, bits, q,
+                       totals + q * kDigits, state, tickets + q);
+    if ((st = launch_status("sort_pass_kernel")) != GLEAM_OK) return st;
+  }
+  return GLEAM_OK;
+}
+
 inline gleam_status radix_sort_pairs(SortBuf a, const uint64_t* n_dev, const uint64_t* bits, uint64_t n_max,
                                      int words, void* ws, hipStream_t s) {
   if (n_max == 0) return GLEAM_OK;
-  if (n_max <= kSortSmallMax) {
-    const SortBuf b = sort_other(ws, n_max, words);
-    if (words == 2)
-      hipLaunchKernelGGL(sort_small_kernel<2>, dim3(1), dim3(kSortSmallThreads), 0, s, a, b, n_dev, bits, n_max);
-    else
-      hipLaunchKernelGGL(sort_small_kernel<1>, dim3(1), dim3(kSortSmallThreads), 0, s, a, b, n_dev, bits, n_max);
-    return launch_status("sort_small_kernel");
-  }
-  const SortLayout L = sort_layout(n_max, words);
-  uint8_t* p = static_cast<uint8_t*>(ws);
-  const SortBuf b = sort_other(ws, n_max, words);
-  uint32_t* count = reinterpret_cast<uint32_t*>(p + L.count);
-  uint32_t* totals = reinterpret_cast<uint32_t*>(p + L.totals);
-  const uint32_t passes = 8u * (uint32_t)words;
-  for (uint32_t q = 0; q < passes; ++q) {
-    hipLaunchKernelGGL(sort_hist_kernel, dim3((uint32_t)L.tiles), dim3(kSortThreads), 0, s, a, b, n_dev, bits, q,
-                       count, L.tiles);
-    gleam_status st = launch_status("sort_hist_kernel");
-    if (st != GLEAM_OK) return st;
-    hipLaunchKernelGGL(sort_scan_kernel, dim3(kDigits), dim3(kSortThreads), 0, s, bits, q, count, L.tiles, totals);
-    if ((st = launch_status("sort_scan_kernel")) != GLEAM_OK) return st;
-    if (words == 2)
-      hipLaunchKernelGGL(sort_scatter_kernel<2>, dim3((uint32_t)L.tiles), dim3(kSortThreads), 0, s, a, b, n_dev, bits,
-                         q, count, totals, L.tiles);
-    else
-      hipLaunchKernelGGL(sort_scatter_kernel<1>, dim3((uint32_t)L.tiles), dim3(kSortThreads), 0, s, a, b, n_dev, bits,
-                         q, count, totals, L.tiles);
-    if ((st = launch_status("sort_scatter_kernel")) != GLEAM_OK) return st;
-  }
-  return GLEAM_OK;
+  return words == 2 ? radix_sort_passes<2>(a, n_dev, bits, n_max, ws, s)
+                    : radix_sort_passes<1>(a, n_dev, bits, n_max, ws, s);
 }
 
 }  // namespace
