@@ -300,3 +300,78 @@ def test_touch_of_heavily_repeated_keys():
 
     t_hot, t_distinct = timed(d_hot), timed(d_dk)
     assert t_hot < 4 * t_distinct + 0.05, (t_hot, t_distinct)
+
+
+@pytest.mark.parametrize("length,each", [(1, 1), (63, 9), (64, 64), (65, 2), (128, 128), (200, 3), (4095, 5), (4097, 7),
+                                         (4300, 4300)])
+def test_repair_across_windows(length, each):
+    """One cluster of `length` slots that wraps past the table's end, `each` keys per home
+    slot: erase and evict close its gaps over one window of 64 slots, several, and beyond
+    the windows a wave repairs (4,096 slots)."""
+    rng = np.random.default_rng([1010, length])
+    log2_cap = 14
+    homes = (np.arange(length) // each * each + (1 << log2_cap) - min(length, 40)) % (1 << log2_cap)
+    keys = np.unique(keys_at_homes(rng, homes, log2_cap))
+    rng.shuffle(keys)
+    vals = rng.integers(0, 2**64, keys.size, dtype=np.uint64, endpoint=False)
+    table, ot = g.Cache(1 << log2_cap, max_load=0.5), oracle.Table()
+    table.insert(keys_to_device(keys), keys_to_device(vals))
+    ot.insert(keys, vals)
+    ep = rng.integers(1, 50, keys.size, dtype=np.uint64)
+    table.touch(keys_to_device(keys), epochs=keys_to_device(ep))
+    ot.touch(keys, ep)
+    for what in ("erase", "evict", "erase few", "evict few"):
+        say("repair windows", length, what)
+        if what.startswith("erase"):
+            gone = keys[rng.random(keys.size) < (0.02 if "few" in what else 0.3)]
+            counts = table.erase(keys_to_device(gone))
+            assert u64(counts).tolist() == [ot.erase(gone), len(ot)]
+        else:
+            keep = len(ot) - (min(len(ot), 3) if "few" in what else len(ot) // 4)
+            ev, counts = table.evict(keep)
+            want = ot.evict(keep)
+            assert u64(counts).tolist() == [want.size, len(ot)]
+            assert np.array_equal(u64(ev)[:want.size], want)
+        assert_table(table, ot, what)
+        st, ref = table.lookup(keys_to_device(keys))
+        est, eref = oracle.lookup(keys, ot)
+        assert np.array_equal(st.cpu().numpy(), est) and np.array_equal(u64(ref), eref)
+
+
+@pytest.mark.parametrize("log2_cap,shape", [(12, "crowded"), (13, "crowded"), (14, "crowded"), (15, "two ranges"),
+                                            (15, "sequential"), (15, "digests"), (17, "crowded"), (17, "digests"),
+                                            (17, "runs")])
+def test_skewed_keys_and_stamps(log2_cap, shape):
+    """Export and eviction orders of key sets that its bins cut evenly (digests, sequential
+    numbers), that crowd into one bin or one cut of it, and stamps of which half are equal
+    and one is far from the others."""
+    rng = np.random.default_rng([1011, log2_cap, len(shape)])
+    n = (1 << log2_cap) * 5 // 8
+    keys = rng.integers(0, 2**64, n, dtype=np.uint64, endpoint=False)
+    if shape == "crowded":  # a tight range and two outliers
+        keys = np.append(rng.integers(1 << 40, (1 << 40) + 4 * n, n, dtype=np.uint64), np.array([3, 2**64 - 1], np.uint64))
+    elif shape == "two ranges":
+        keys[: n // 2] = np.arange(n // 2, dtype=np.uint64)
+    elif shape == "sequential":
+        keys = np.arange(n, dtype=np.uint64) + np.uint64(12345)
+    elif shape == "runs":  # short runs of neighbours far apart
+        keys = (keys[:n] & ~np.uint64(0xFFFFFFFFFFFF)) | (np.arange(n, dtype=np.uint64) & np.uint64(0xFFF))
+    keys = np.unique(keys)
+    rng.shuffle(keys)
+    vals = rng.integers(0, 2**64, keys.size, dtype=np.uint64, endpoint=False)
+    table, ot = g.Cache(1 << log2_cap, max_load=0.7), oracle.Table()
+    table.insert(keys_to_device(keys), keys_to_device(vals))
+    ot.insert(keys, vals)
+    ep = rng.integers(0, 100_000, keys.size, dtype=np.uint64)
+    ep[rng.random(keys.size) < 0.5] = 7
+    ep[0] = np.uint64(1) << np.uint64(60)
+    table.touch(keys_to_device(keys), epochs=keys_to_device(ep))
+    ot.touch(keys, ep)
+    say("skewed", log2_cap, shape)
+    assert_table(table, ot, "before")
+    for keep in (len(ot), len(ot) - 1, len(ot) * 9 // 10, len(ot) // 3, 2, 0):
+        ev, counts = table.evict(keep)
+        want = ot.evict(keep)
+        assert u64(counts).tolist() == [want.size, len(ot)], keep
+        assert np.array_equal(u64(ev)[:want.size], want), keep
+        assert_table(table, ot, f"keep {keep}")
