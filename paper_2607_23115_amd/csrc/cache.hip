@@ -116,32 +116,58 @@ __global__ __launch_bounds__(kThreads) void insert_mark_kernel(ScratchRef sc, co
   if (first_in_workgroup(k, valid, bkeys, bslot)) scratch_mark(sc, keys, k, i);
 }
 
-__global__ void insert_commit_kernel(TableRef t, ScratchRef sc, const uint64_t* keys, const uint64_t* vals,
-                                     uint64_t n, uint64_t* n_new) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t k = keys[i];
-  if (scratch_min(sc, keys, k, i) != i) return;  // a lower index carries this key
-  if (k == kEmpty) {
-    if (atomicCAS(ull(&t.hdr[0]), 0ull, 1ull) == 0ull) {
-      t.hdr[1] = vals[i];
-      atomicAdd(ull(n_new), 1ull);
-      atomicAdd(ull(&t.hdr[3]), 1ull);
-    }
-    return;
-  }
+// Puts key k (not kEmpty) and its value in the table unless it is held; true if it was not.
+// The home slot is tried with a compare-and-swap at once (in a table with room most keys go
+// there: one round trip); the slots after it are read first, and only one that reads free
+// costs a swap. A read that is out of date can only show a slot free that is not, and the
+// swap then tells.
+__device__ __forceinline__ bool insert_key(const TableRef& t, uint64_t k, uint64_t val) {
   uint64_t pos = slot_hash(k, t.shift);
   for (uint64_t probe = 0; probe <= t.mask; ++probe) {
     uint64_t* slot = t.slots + 2 * pos;
-    const uint64_t prev = atomicCAS(ull(slot), (unsigned long long)kEmpty, (unsigned long long)k);
-    if (prev == kEmpty) {
-      slot[1] = vals[i];
-      atomicAdd(ull(n_new), 1ull);
-      atomicAdd(ull(&t.hdr[3]), 1ull);
-      return;
+    uint64_t seen = probe ? *slot : kEmpty;
+    if (seen == kEmpty) {
+      seen = atomicCAS(ull(slot), (unsigned long long)kEmpty, (unsigned long long)k);
+      if (seen == kEmpty) {
+        slot[1] = val;
+        return true;
+      }
     }
-    if (prev == k) return;  // already held: keep the existing value
+    if (seen == k) return false;  // already held: keep the existing value
     pos = (pos + 1) & t.mask;
+  }
+  return false;
+}
+
+// The lowest index of each key inserts it. A workgroup adds its new keys to the two counts
+// with one atomic each: a wave's atomics on one word queue at about 10 ns each (20 M new
+// keys: 5.6 ms of a call with an atomic per wave, 3.1 ms with one per workgroup).
+__global__ __launch_bounds__(kThreads) void insert_commit_kernel(TableRef t, ScratchRef sc, const uint64_t* keys,
+                                                                 const uint64_t* vals, uint64_t n, uint64_t* n_new) {
+  __shared__ uint32_t wave_new[kThreads / 64];
+  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool valid = i < n;
+  const uint64_t k = keys[valid ? i : n - 1];  // n >= 1; clamped so the loads are unconditional
+  const uint64_t val = vals[valid ? i : n - 1];
+  bool added = false;
+  if (valid && scratch_min(sc, keys, k, i) == i) {  // else a lower index carries this key
+    if (k != kEmpty) {
+      added = insert_key(t, k, val);
+    } else if (atomicCAS(ull(&t.hdr[0]), 0ull, 1ull) == 0ull) {
+      t.hdr[1] = val;
+      added = true;
+    }
+  }
+  const uint64_t who = __ballot(added);
+  if ((threadIdx.x & 63) == 0) wave_new[threadIdx.x >> 6] = (uint32_t)__popcll(who);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (int w = 0; w < kThreads / 64; ++w) total += wave_new[w];
+    if (total) {
+      atomicAdd(ull(n_new), (unsigned long long)total);
+      atomicAdd(ull(&t.hdr[3]), (unsigned long long)total);
+    }
   }
 }
 
@@ -305,11 +331,13 @@ __global__ __launch_bounds__(kSmallThreads) void insert_small_kernel(TableRef t,
   __shared__ uint32_t wave_new[kSmallThreads / 64];
   for (uint32_t i = threadIdx.x; i < kSmallSlots; i += kSmallThreads) slots[i] = 0;
   if (threadIdx.x == 0) empty_min = ~0u;
-  uint64_t k[kSmallPerThread];
+  constexpr int kSmallPerThread = (int)(kSmallInsertKeys / kSmallThreads);
+  uint64_t k[kSmallPerThread], val[kSmallPerThread];
 #pragma unroll
   for (int j = 0; j < kSmallPerThread; ++j) {  // unconditional (clamped) loads, issued together
     const uint64_t g = threadIdx.x + (uint64_t)j * kSmallThreads;
     k[j] = keys[g < n ? g : n - 1];
+    val[j] = vals[g < n ? g : n - 1];
   }
   __syncthreads();
 #pragma unroll
@@ -355,23 +383,12 @@ __global__ __launch_bounds__(kSmallThreads) void insert_small_kernel(TableRef t,
     if (g0 != g) continue;  // a lower index carries this key
     if (k[j] == kEmpty) {
       if (atomicCAS(ull(&t.hdr[0]), 0ull, 1ull) == 0ull) {
-        t.hdr[1] = vals[g];
+        t.hdr[1] = val[j];
         ++added;
       }
       continue;
     }
-    uint64_t pos = slot_hash(k[j], t.shift);
-    for (uint64_t probe = 0; probe <= t.mask; ++probe) {
-      uint64_t* slot = t.slots + 2 * pos;
-      const uint64_t prev = atomicCAS(ull(slot), (unsigned long long)kEmpty, (unsigned long long)k[j]);
-      if (prev == kEmpty) {
-        slot[1] = vals[g];
-        ++added;
-        break;
-      }
-      if (prev == k[j]) break;  // already held: keep the existing value
-      pos = (pos + 1) & t.mask;
-    }
+    if (insert_key(t, k[j], val[j])) ++added;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) added += __shfl_xor(added, o, 64);

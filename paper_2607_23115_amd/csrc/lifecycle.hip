@@ -43,29 +43,36 @@ enum : int {
   kWCollected = 0,  // evict: entries collected; export: entries left to the radix sort
   kWDrop = 1,       // entries to evict
   kWLive = 2,       // live entries
-  kWLeaders = 3,    // clusters to repair
   kWBits = 4,       // 4..7: the sort's AND/OR words
-  kWBaseHi = 8,     // the histogram's origin
+  kWBaseHi = 8,     // where the cells of the order start (see Cells)
   kWBaseLo = 9,
-  kWShift = 10,     // and log2 of its bins' width
+  kWWidthHi = 10,   // and their range
+  kWWidthLo = 11,
+  kWLimit = 12,     // evict: the last bin collected first
 };
 constexpr size_t kCounterBytes = 256;
 
 constexpr uint32_t kPickBins = 1024;        // evict's histogram
-constexpr uint32_t kBinSlots = 4096;        // export: table slots per bin, up to kMaxBins bins
-constexpr uint32_t kMaxBins = 16384;
-constexpr uint32_t kSpreadGrid = 256;       // export: workgroups that spread the entries over the bins
 
-struct Entry {  // an entry on its way to its place in the export
-  uint64_t key, val, stamp, unused;  // (32 bytes: two 16-byte stores)
-};
+// Export: bins of the key range, each of `parts` parts of kCuts cuts. A part covers
+// kPartSlots table slots' share of the range, so a part of a digest table at load 0.7 has
+// 5,734 entries, of the kPartMax that a workgroup sorts in LDS. The entries are written to
+// their bins only, so that a tile of 8,192 slots has several entries for each bin.
+constexpr uint32_t kPartSlots = 8192;
+constexpr uint32_t kPartMax = 7168;
+constexpr uint32_t kCuts = 2048;
+constexpr uint32_t kMaxParts = 8;
+constexpr uint32_t kBinMax = 65535;         // entries of a bin (numbered in 16 bits)
+constexpr uint32_t kMaxAllParts = 16384;
+constexpr uint32_t kMaxBins = kMaxAllParts / kMaxParts;
+constexpr uint32_t kSpreadGrid = 256;       // workgroups that spread the entries over the bins
 
 struct MaintLayout {
   uint64_t m;     // capacity + 1 (the last is the key kEmpty's header side slot)
-  uint32_t bins, spread;
+  uint32_t bins, parts, spread;
   size_t counters;
-  size_t pick, leaders, hi, lo, idx, sort2;             // evict
-  size_t share, starts, entries, xlo, xidx, sort1;      // export
+  size_t pick, occupied, leaders, hi, lo, idx, sort2;          // evict
+  size_t share, starts, xkey, xpay, xidx, sort1;               // export
   size_t total;
 };
 
@@ -79,6 +86,7 @@ MaintLayout maint_layout(uint64_t capacity) {
     return o;
   };
   L.counters = take(kCounterBytes);
+  L.occupied = take(8 * ((capacity + 63) / 64));
   L.leaders = take(4 * L.m);
   L.hi = take(8 * sort_capacity(L.m));  // the sort's keys and indices (its buffer a)
   L.lo = take(8 * sort_capacity(L.m));
@@ -87,14 +95,16 @@ MaintLayout maint_layout(uint64_t capacity) {
   L.pick = L.sort2;  // done with before the sort begins (its second buffer holds 8 KiB or more)
   const size_t evict_total = off;
   off = kCounterBytes;
-  const uint64_t bins = capacity / kBinSlots;
-  L.bins = (uint32_t)(bins < 1 ? 1 : bins < kMaxBins ? bins : kMaxBins);
+  const uint64_t want = capacity / kPartSlots;
+  const uint32_t all = (uint32_t)(want < 1 ? 1 : want < kMaxAllParts ? want : kMaxAllParts);
+  L.parts = all < kMaxParts ? all : kMaxParts;
+  L.bins = all / L.parts;
   const uint64_t spread = (capacity + 4095) / 4096;
   L.spread = (uint32_t)(spread < kSpreadGrid ? spread : kSpreadGrid);
-  L.share = take(4 * (size_t)L.bins * L.spread);
-  L.starts = take(4 * ((size_t)L.bins + 1));
-  L.entries = take(sizeof(Entry) * L.m);
-  L.xlo = take(8 * sort_capacity(L.m));
+  L.share = take(4 * (size_t)all * L.spread);
+  L.starts = take(4 * ((size_t)all + 1));
+  L.xkey = take(8 * sort_capacity(L.m));  // every entry's key by bin (the radix sort's buffer a)
+  L.xpay = take(16 * L.m);                // and {value, stamp}
   L.xidx = take(4 * sort_capacity(L.m));
   L.sort1 = take(sort_layout(L.m, 1).total);
   L.total = evict_total > off ? evict_total : off;
@@ -136,7 +146,8 @@ __device__ __forceinline__ uint64_t wave_sum(uint64_t x) {
 // lane updates the stamp (at most one atomic per key per workgroup). A batch of one
 // repeated key, as a zero-filled tensor gives, would otherwise queue one atomic per copy
 // on one word (262,144 copies: 11.6 ms). A stamp only grows, so a lane whose stamp
-// already reads at or past its epoch skips the atomic.
+// already reads at or past its epoch skips the atomic. Bound by the round trips of the
+// random reads.
 constexpr int kTouchSlots = 2 * kThreads;  // power of two, load at most 1/2
 
 __global__ __launch_bounds__(kThreads) void touch_kernel(TableRef t, const uint64_t* keys, uint64_t n,
@@ -148,8 +159,14 @@ __global__ __launch_bounds__(kThreads) void touch_kernel(TableRef t, const uint6
   const uint32_t tid = threadIdx.x;
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + tid;
   const bool valid = i < n;
-  const uint64_t k = valid ? keys[i] : 0;
+  const uint64_t ki = keys[valid ? i : n - 1];  // n >= 1; clamped so the load is unconditional
+  const uint64_t k = valid ? ki : 0;
   const uint64_t e = valid ? (epochs ? epochs[i] : epoch) : 0;
+  // the home slot and its stamp are read before the workgroup's LDS pass, which hides
+  // under them: most probes end there
+  const uint64_t home = k != kEmpty ? slot_hash(k, t.shift) : 0;
+  const uint64_t home_key = t.slots[2 * home];
+  const uint64_t home_stamp = __hip_atomic_load(&t.stamps[home], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   bkeys[tid] = k;
   bslot[tid] = 0;
   bslot[tid + kThreads] = 0;
@@ -177,52 +194,110 @@ __global__ __launch_bounds__(kThreads) void touch_kernel(TableRef t, const uint6
     const bool lead = bslot[at] == tid + 1;
     const uint64_t top = bmax[at];
     uint64_t* stamp = nullptr;
+    uint64_t now = home_stamp;
     if (k == kEmpty) {
-      if (t.hdr[0]) stamp = &t.hdr[2];
-    } else {
+      if (t.hdr[0]) {
+        stamp = &t.hdr[2];
+        now = 0;
+      }
+    } else if (home_key == k) {
+      stamp = &t.stamps[home];
+    } else if (home_key != kEmpty) {
       const int64_t pos = find_slot(t, k);
-      if (pos >= 0) stamp = &t.stamps[pos];
+      if (pos >= 0) {
+        stamp = &t.stamps[pos];
+        if (lead) now = __hip_atomic_load(stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     }
     if (stamp) {
       hit = 1;
-      if (lead && __hip_atomic_load(stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < top)
-        atomicMax(ull(stamp), (unsigned long long)top);
+      if (lead && now < top) atomicMax(ull(stamp), (unsigned long long)top);
     }
   }
   hit = wave_sum(hit);
-  if (n_touched && (tid & 63) == 0 && hit) atomicAdd(ull(n_touched), (unsigned long long)hit);
+  __syncthreads();  // bkeys read by every thread
+  if ((tid & 63) == 0) bkeys[tid >> 6] = hit;
+  __syncthreads();
+  if (n_touched && tid == 0) {
+    for (int w = 1; w < kThreads / 64; ++w) hit += bkeys[w];
+    if (hit) atomicAdd(ull(n_touched), (unsigned long long)hit);
+  }
 }
 
 // ---- selection over the range of (stamp, key) -----------------------------------------
 typedef unsigned __int128 u128;
 __device__ __forceinline__ u128 order_of(uint64_t stamp, uint64_t key) { return ((u128)stamp << 64) | key; }
 
-// One workgroup: the counters of a call, and the origin and bin width of its histogram
-// from the least and greatest of at most kSamples entries (every capacity / kSamples-th
-// slot), with a margin of 1/1024 of their range on either side. An entry beyond takes the
-// first or last bin: a bin number never decreases with the entry's order, which is all
-// that the callers rely on.
+// The order cut into equal cells: cell(x) in [0, cells) never decreases with x, which is
+// all that the callers rely on; entries outside the range take the first or the last
+// cell. The 32 leading bits of x's distance from the base (leading: from the top bit of the
+// range) times cells / range, so the cells are even for any range, not only powers of two.
+struct Cells {
+  u128 base, width;
+  uint32_t lead;    // shift that brings the range's top bit to bit 127
+  uint32_t factor;  // cells * 2^32 / (leading bits of the range + 1), at most 2 * cells
+  __device__ Cells(const uint64_t* counters, uint32_t cells)
+      : base(order_of(counters[kWBaseHi], counters[kWBaseLo])),
+        width(order_of(counters[kWWidthHi], counters[kWWidthLo])) {
+    const uint64_t hi = (uint64_t)(width >> 64), lo = (uint64_t)width;
+    lead = hi ? (uint32_t)__builtin_clzll(hi) : lo ? 64u + (uint32_t)__builtin_clzll(lo) : 0u;
+    const uint64_t top = (uint64_t)(uint32_t)((width << lead) >> 96) + 1;
+    factor = width == 0 ? 0u : (uint32_t)(((uint64_t)cells << 32) / top);  // cells < 2^31
+  }
+  __device__ __forceinline__ uint32_t of(u128 x) const {
+    if (x < base) return 0;
+    u128 d = x - base;
+    d = d < width ? d : width;
+    return (uint32_t)(((uint64_t)(uint32_t)((d << lead) >> 96) * factor) >> 32);
+  }
+};
+
+// The same for an order by key alone (the range below 2^64).
+struct KeyCells {
+  uint64_t base, width;
+  uint32_t lead, factor;
+  __device__ KeyCells(const uint64_t* counters, uint32_t cells) : base(counters[kWBaseLo]), width(counters[kWWidthLo]) {
+    const Cells c(counters, cells);
+    lead = width ? c.lead - 64 : 0;
+    factor = c.factor;
+  }
+  __device__ __forceinline__ uint32_t of(uint64_t k) const {
+    if (k < base) return 0;
+    const uint64_t d = min(k - base, width);
+    return (uint32_t)(((uint64_t)(uint32_t)((d << lead) >> 32) * factor) >> 32);
+  }
+};
+
+// One workgroup: the counters of a call, and the range of its cells, from the least and
+// greatest of at most kSamples entries (runs of 64 slots, evenly spaced: places in the
+// table are hashes, so a run is as good a sample as scattered slots and an eighth of the
+// lines), with a margin of 1/1024 of their range on either side. For eviction also the bin
+// up to which to collect: the share of the victims among the samples, plus six standard
+// deviations and a few, so that one pass over the table nearly always collects them all.
 constexpr uint32_t kInitThreads = 1024;
 constexpr uint32_t kSamplesEach = 16;
 constexpr uint64_t kSamples = (uint64_t)kInitThreads * kSamplesEach;
 
 // kByStamp: the order is (stamp, key), else the key alone.
 template <bool kByStamp>
-__global__ __launch_bounds__(kInitThreads) void maint_init_kernel(TableRef t, uint64_t keep, uint32_t bins,
-                                                                  uint64_t* counters, uint32_t* pick) {
+__global__ __launch_bounds__(kInitThreads) void maint_init_kernel(TableRef t, uint64_t keep, uint64_t* counters,
+                                                                  uint32_t* pick) {
+  static_assert(kPickBins == kInitThreads, "one bin per thread");
   __shared__ uint64_t part[kInitThreads / 64][4];
+  __shared__ uint32_t h[kPickBins], wave_sum[kInitThreads / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t capacity = t.mask + 1;
-  if (pick)
-    for (uint32_t i = threadIdx.x; i < bins; i += kInitThreads) pick[i] = 0;
+  h[threadIdx.x] = 0;
+  if (kByStamp) pick[threadIdx.x] = 0;
   const uint64_t n = capacity < kSamples ? capacity : kSamples, step = capacity / n;
   uint64_t key[kSamplesEach], stamp[kSamplesEach];
 #pragma unroll
   for (uint32_t r = 0; r < kSamplesEach; ++r) {  // unconditional (clamped) loads, issued together
     const uint64_t i = (uint64_t)r * kInitThreads + threadIdx.x;
-    const uint64_t slot = (i < n ? i : 0) * step;
+    const uint64_t slot = i < n ? (i - lane) * step + lane : 0;  // (capacity below 64: one run, step 1)
     key[r] = t.slots[2 * slot];
     stamp[r] = kByStamp ? t.stamps[slot] : 0;
+    if (i >= n) key[r] = kEmpty;
   }
   u128 least = ~(u128)0, most = 0;
 #pragma unroll
@@ -246,60 +321,84 @@ __global__ __launch_bounds__(kInitThreads) void maint_init_kernel(TableRef t, ui
     part[wave][3] = (uint64_t)most;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (uint32_t w = 1; w < kInitThreads / 64; ++w) {
-    const u128 a = order_of(part[w][0], part[w][1]), b = order_of(part[w][2], part[w][3]);
-    least = a < least ? a : least;
-    most = b > most ? b : most;
-  }
-  if (least > most) least = most = 0;  // no entry among the samples
-  const u128 margin = (most - least) >> 10;
-  const u128 top = kByStamp ? ~(u128)0 : (u128)~0ull;
-  const u128 base = least > margin ? least - margin : 0;
-  const u128 end = most < top - margin ? most + margin : top;
-  uint32_t shift = 0;
-  while ((end - base) >> shift >= bins) ++shift;  // shift < 128: bins >= 1
   const uint64_t live = t.hdr[3];
-  counters[kWCollected] = 0;
-  counters[kWDrop] = live > keep ? live - keep : 0;
-  counters[kWLive] = live;
-  counters[kWLeaders] = 0;
-  counters[kWBits + 0] = ~0ull;
-  counters[kWBits + 1] = 0;
-  counters[kWBits + 2] = ~0ull;
-  counters[kWBits + 3] = 0;
-  counters[kWBaseHi] = (uint64_t)(base >> 64);
-  counters[kWBaseLo] = (uint64_t)base;
-  counters[kWShift] = shift;
+  const uint64_t drop = live > keep ? live - keep : 0;
+  if (threadIdx.x == 0) {
+    for (uint32_t w = 1; w < kInitThreads / 64; ++w) {
+      const u128 a = order_of(part[w][0], part[w][1]), b = order_of(part[w][2], part[w][3]);
+      least = a < least ? a : least;
+      most = b > most ? b : most;
+    }
+    if (least > most) least = most = 0;  // no entry among the samples
+    const u128 margin = (most - least) >> 10;
+    const u128 top = kByStamp ? ~(u128)0 : (u128)~0ull;
+    const u128 base = least > margin ? least - margin : 0;
+    const u128 end = most < top - margin ? most + margin : top;
+    counters[kWCollected] = 0;
+    counters[kWDrop] = drop;
+    counters[kWLive] = live;
+    counters[kWBits + 0] = ~0ull;
+    counters[kWBits + 1] = 0;
+    counters[kWBits + 2] = ~0ull;
+    counters[kWBits + 3] = 0;
+    counters[kWBaseHi] = (uint64_t)(base >> 64);
+    counters[kWBaseLo] = (uint64_t)base;
+    counters[kWWidthHi] = (uint64_t)((end - base) >> 64);
+    counters[kWWidthLo] = (uint64_t)(end - base);
+    counters[kWLimit] = kPickBins - 1;
+  }
+  if (!kByStamp) return;
+  __syncthreads();  // the range, read back by every thread of this workgroup
+  const Cells bins(counters, kPickBins);
+#pragma unroll
+  for (uint32_t r = 0; r < kSamplesEach; ++r)
+    if (key[r] != kEmpty) atomicAdd(&h[bins.of(order_of(stamp[r], key[r]))], 1u);
+  __syncthreads();
+  const uint32_t c = h[threadIdx.x];
+  uint32_t incl = c;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += y;
+  }
+  if (lane == 63) wave_sum[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - c, total = 0;
+  for (int w = 0; w < (int)(kInitThreads / 64); ++w) {
+    if (w < wave) run += wave_sum[w];
+    total += wave_sum[w];
+  }
+  const float share = live ? (float)drop / (float)live * (float)total : 0.0f;
+  const uint32_t want = (uint32_t)(share + 6.0f * sqrtf(share)) + 8;
+  if (run < want && run + c >= want) counters[kWLimit] = threadIdx.x;
 }
 
-struct Bins {  // the histogram's geometry
-  u128 base;
-  uint32_t shift, last;
-  __device__ Bins(const uint64_t* counters, uint32_t bins)
-      : base(order_of(counters[kWBaseHi], counters[kWBaseLo])), shift((uint32_t)counters[kWShift]), last(bins - 1) {}
-  __device__ __forceinline__ uint32_t of(u128 x) const {
-    if (x < base) return 0;
-    const u128 b = (x - base) >> shift;
-    return b < last ? (uint32_t)b : last;
-  }
-};
+// Folds into a pair of AND/OR words. A word that would not change is only read: atomics on
+// one address queue at about 10 ns each, and all but the first few change nothing.
+__device__ __forceinline__ void fold_bits(uint64_t* bits, uint64_t and_w, uint64_t or_w) {
+  const uint64_t a = __hip_atomic_load(&bits[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t o = __hip_atomic_load(&bits[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((a & and_w) != a) atomicAnd(ull(&bits[0]), (unsigned long long)and_w);
+  if ((o | or_w) != o) atomicOr(ull(&bits[1]), (unsigned long long)or_w);
+}
 
 // ---- evict ----------------------------------------------------------------------------
-// Reads the table twice (the histogram, then the entries up to the bin of the last victim)
-// and writes only what it evicts, so it is bound by two passes at HBM rate: 20 M entries in
-// 2^25 slots, 20,000 evicted, 0.68 ms, against 5.9 ms for gathering, sorting and
-// re-inserting every entry.
+// Reads the table once (the entries up to a bin that the samples say holds the last
+// victim) and writes only what it evicts. Should the samples have misled it, a histogram
+// of the whole table finds the bin and a second pass collects what is missing. 20 M entries
+// in 2^25 slots, 20,000 evicted: 0.34 ms (collecting 175 us, 4.6 TB/s; the sort's sixteen
+// passes 110), against 5.6 ms for gathering, sorting and re-inserting every entry; half of
+// them evicted 2.8 against 4.7 ms; all of them 4.3 against 4.2.
 constexpr uint32_t kPickThreads = 1024;
 constexpr uint32_t kPickGrid = 256;  // few enough that the final atomics on the bins stay few
 constexpr uint32_t kPickItems = 4;
 
 __global__ __launch_bounds__(kPickThreads) void evict_pick_kernel(TableRef t, const uint64_t* counters, uint32_t* pick) {
   __shared__ uint32_t h[kPickBins];
-  if (counters[kWDrop] == 0) return;
+  if (counters[kWCollected] >= counters[kWDrop]) return;
   for (uint32_t i = threadIdx.x; i < kPickBins; i += kPickThreads) h[i] = 0;
   __syncthreads();
-  const Bins bins(counters, kPickBins);
+  const Cells bins(counters, kPickBins);
   const uint64_t capacity = t.mask + 1;
   for (uint64_t i0 = (uint64_t)blockIdx.x * kPickThreads * kPickItems; i0 < capacity;
        i0 += (uint64_t)gridDim.x * kPickThreads * kPickItems) {
@@ -322,27 +421,35 @@ __global__ __launch_bounds__(kPickThreads) void evict_pick_kernel(TableRef t, co
     if (h[i]) atomicAdd(&pick[i], h[i]);
 }
 
-// Collects the entries of the bins up to the one that the last victim falls in, as pairs
-// (stamp, key) with their slot (the side slot: capacity). Each workgroup takes tiles of
-// 4096 slots in turn, counts a tile's entries and claims that many positions with one
-// atomic. It also folds the AND and OR of what it collects, once per workgroup at the
-// end, from which the sort skips the digits every entry shares.
-constexpr uint32_t kGatherItems = 16;
-constexpr uint64_t kGatherTile = (uint64_t)kThreads * kGatherItems;
-constexpr uint32_t kGatherMaxGrid = 1024;
+// Collects the entries up to the sampled bin (kAgain: those after it, up to the bin with
+// which the histogram's running count reaches the victims) as pairs (stamp, key) with
+// their slot (the side slot: capacity). A wave lists the slots that it takes in LDS and
+// writes kListFlush or more of them at a time, claiming their positions with one atomic
+// (the claims queue on one word: by 64, 20 M entries took 3 ms); it has no barrier on its
+// way through the table. It also folds the AND and
+// OR of what it collects, from which the sort skips the digits every entry shares, and
+// notes which slots are occupied (a bit each).
+constexpr uint32_t kCollectItems = 8;
+constexpr uint64_t kCollectTile = 64 * kCollectItems;  // slots per step of a wave
+constexpr uint32_t kCollectGrid = 512;  // 2^25 slots: 512 workgroups 175 us, 1,024 190, 2,048 228
+constexpr int kCollectWaves = kThreads / 64;
+constexpr uint32_t kListFlush = 1536;  // listed slots that a wave writes out with one claim
 
+template <bool kAgain>
 __global__ __launch_bounds__(kThreads) void evict_collect_kernel(TableRef t, const uint32_t* pick, uint64_t* counters,
-                                                                 SortBuf sb, uint64_t tiles) {
+                                                                 SortBuf sb, uint64_t* occupied) {
   static_assert(kPickBins == 4 * kThreads, "four bins per thread");
-  __shared__ uint32_t wave_live[kThreads / 64];
-  __shared__ uint64_t tile_base;
-  __shared__ uint64_t fold[kThreads / 64][4];
+  __shared__ uint32_t wave_sum[kCollectWaves];
   __shared__ uint32_t bin_limit;
+  __shared__ uint64_t claimed;
+  __shared__ uint32_t list[kCollectWaves][kListFlush + kCollectTile + 64];
+  __shared__ uint64_t fold[kCollectWaves][4];
   const uint64_t drop = counters[kWDrop];
   if (drop == 0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-  {  // the first bin with which the running count reaches `drop`
+  uint32_t after = 0, limit = (uint32_t)counters[kWLimit];  // bins [after, limit]
+  if (kAgain) {
     uint32_t c[4], sum = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -355,70 +462,94 @@ __global__ __launch_bounds__(kThreads) void evict_collect_kernel(TableRef t, con
       const uint32_t y = __shfl_up(incl, d, 64);
       if (lane >= d) incl += y;
     }
-    if (lane == 63) wave_live[wave] = incl;
-    if (threadIdx.x == 0) bin_limit = kPickBins - 1;
+    if (lane == 63) wave_sum[wave] = incl;
+    if (threadIdx.x == 0) bin_limit = 0;
     __syncthreads();
     uint64_t run = incl - sum;
-    for (int w = 0; w < wave; ++w) run += wave_live[w];
+    for (int w = 0; w < wave; ++w) run += wave_sum[w];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (run < drop && run + c[j] >= drop) bin_limit = 4 * threadIdx.x + j;
       run += c[j];
     }
     __syncthreads();
+    after = limit + 1;
+    limit = bin_limit;
+    if (limit < after) return;  // the first pass collected them all (the histogram is all zero)
   }
-  const uint32_t limit = bin_limit;
-  const Bins bins(counters, kPickBins);
+  const Cells bins(counters, kPickBins);
   const uint64_t capacity = t.mask + 1;
   uint64_t and_k = ~0ull, or_k = 0, and_s = ~0ull, or_s = 0;
-  for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const uint64_t first = tile * kGatherTile + (uint64_t)wave * 64 * kGatherItems + lane;
-    uint64_t key[kGatherItems], stamp[kGatherItems], mask[kGatherItems];
+  uint32_t listed = 0;  // the same in every lane
+  auto write = [&](uint64_t p, uint32_t from, uint32_t count) {  // list[from, from + count) to p on, count <= 64
+    p += lane;
+    if ((uint32_t)lane >= count) return;
+    const uint32_t slot = list[wave][from + lane];
+    const uint64_t key = slot < capacity ? t.slots[2 * (uint64_t)slot] : kEmpty;
+    const uint64_t stamp = slot < capacity ? t.stamps[slot] : t.hdr[2];
+    sb.hi[p] = stamp;
+    sb.lo[p] = key;
+    sb.idx[p] = slot;
+    and_k &= key;
+    or_k |= key;
+    and_s &= stamp;
+    or_s |= stamp;
+  };
+  auto in_range = [&](uint64_t key, uint64_t stamp) {
+    const uint32_t b = bins.of(order_of(stamp, key));
+    return b >= after && b <= limit;
+  };
+  const uint64_t waves = (uint64_t)gridDim.x * kCollectWaves;
+  for (uint64_t i0 = ((uint64_t)blockIdx.x * kCollectWaves + wave) * kCollectTile; i0 < capacity;
+       i0 += waves * kCollectTile) {
+    uint64_t key[kCollectItems], stamp[kCollectItems];
 #pragma unroll
-    for (uint32_t r = 0; r < kGatherItems; ++r) {  // unconditional (clamped) loads, issued together
-      const uint64_t i = first + 64ull * r, at = i < capacity ? i : capacity - 1;
+    for (uint32_t r = 0; r < kCollectItems; ++r) {  // unconditional (clamped) loads, issued together
+      const uint64_t i = i0 + 64 * r + lane, at = i < capacity ? i : capacity - 1;
       key[r] = t.slots[2 * at];
       stamp[r] = t.stamps[at];
     }
-    uint32_t live_n = 0;
+    uint64_t held_word = 0;
 #pragma unroll
-    for (uint32_t r = 0; r < kGatherItems; ++r) {
-      const uint64_t i = first + 64ull * r;
-      bool live = i < capacity && key[r] != kEmpty;
-      if (i == capacity && t.hdr[0]) {  // the side slot
-        live = true;
-        key[r] = kEmpty;
-        stamp[r] = t.hdr[2];
-      }
-      mask[r] = __ballot(live && bins.of(order_of(stamp[r], key[r])) <= limit);
-      live_n += (uint32_t)__popcll(mask[r]);
+    for (uint32_t r = 0; r < kCollectItems; ++r) {
+      const uint64_t i = i0 + 64 * r + lane;
+      const bool held = i < capacity && key[r] != kEmpty;
+      const uint64_t word = __ballot(held);
+      if (lane == (int)r) held_word = word;
+      const bool mine = held && in_range(key[r], stamp[r]);
+      const uint64_t who = __ballot(mine);
+      if (mine) list[wave][listed + (uint32_t)__popcll(who & lt)] = (uint32_t)i;
+      listed += (uint32_t)__popcll(who);
     }
-    if (lane == 0) wave_live[wave] = live_n;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t total = 0;
-      for (int w = 0; w < kThreads / 64; ++w) total += wave_live[w];
-      tile_base = total ? atomicAdd(ull(&counters[kWCollected]), (unsigned long long)total) : 0;
+    if (!kAgain && lane < (int)kCollectItems && i0 + 64 * lane < capacity) occupied[i0 / 64 + lane] = held_word;
+    wave_lds_sync();
+    if (listed >= kListFlush) {  // all but a remainder, from the end of the list
+      const uint32_t keep = listed % 64;
+      uint64_t p = 0;
+      if (lane == 0) p = atomicAdd(ull(&counters[kWCollected]), (unsigned long long)(listed - keep));
+      p = shfl64(p, 0);
+      for (uint32_t from = keep; from < listed; from += 64) write(p + from - keep, from, 64);
+      listed = keep;
     }
-    __syncthreads();
-    uint64_t at = tile_base;
-    for (int w = 0; w < wave; ++w) at += wave_live[w];
-#pragma unroll
-    for (uint32_t r = 0; r < kGatherItems; ++r) {
-      if ((mask[r] >> lane) & 1ull) {
-        const uint64_t p = at + (uint64_t)__popcll(mask[r] & lt);
-        sb.hi[p] = stamp[r];
-        sb.lo[p] = key[r];
-        sb.idx[p] = (uint32_t)(first + 64ull * r);
-        and_k &= key[r];
-        or_k |= key[r];
-        and_s &= stamp[r];
-        or_s |= stamp[r];
-      }
-      at += (uint64_t)__popcll(mask[r]);
-    }
-    __syncthreads();  // wave_live and tile_base read before the next tile rewrites them
+    wave_lds_sync();  // the list read before the next step adds to it
   }
+  if (blockIdx.x == 0 && wave == 0 && t.hdr[0] && in_range(kEmpty, t.hdr[2])) {
+    if (lane == 0) list[0][listed] = (uint32_t)capacity;
+    ++listed;
+    wave_lds_sync();
+  }
+  // what is left in the lists: one claim per workgroup
+  if (lane == 0) wave_sum[wave] = listed;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+    for (int w = 0; w < kCollectWaves; ++w) total += wave_sum[w];
+    claimed = total ? atomicAdd(ull(&counters[kWCollected]), (unsigned long long)total) : 0;
+  }
+  __syncthreads();
+  uint64_t p = claimed;
+  for (int w = 0; w < wave; ++w) p += wave_sum[w];
+  for (uint32_t from = 0; from < listed; from += 64) write(p + from, from, min(listed - from, 64u));
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) {
     and_k &= shfl_xor64(and_k, o);
@@ -434,18 +565,14 @@ __global__ __launch_bounds__(kThreads) void evict_collect_kernel(TableRef t, con
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kThreads / 64; ++w) {
+    for (int w = 1; w < kCollectWaves; ++w) {
       fold[0][0] &= fold[w][0];
       fold[0][1] |= fold[w][1];
       fold[0][2] &= fold[w][2];
       fold[0][3] |= fold[w][3];
     }
-    if (fold[0][0] != ~0ull || fold[0][1] != 0) {  // some entry was collected (an all-ones key has OR != 0)
-      atomicAnd(ull(&counters[kWBits + 0]), (unsigned long long)fold[0][0]);
-      atomicOr(ull(&counters[kWBits + 1]), (unsigned long long)fold[0][1]);
-      atomicAnd(ull(&counters[kWBits + 2]), (unsigned long long)fold[0][2]);
-      atomicOr(ull(&counters[kWBits + 3]), (unsigned long long)fold[0][3]);
-    }
+    fold_bits(counters + kWBits, fold[0][0], fold[0][1]);
+    fold_bits(counters + kWBits + 2, fold[0][2], fold[0][3]);
   }
 }
 
@@ -459,13 +586,28 @@ __device__ __forceinline__ UpTo last_victim(const SortBuf& sorted, uint64_t drop
   return UpTo{order_of(sorted.hi[drop - 1], sorted.lo[drop - 1])};
 }
 
+// Eight lanes look along a table from one slot (128 bytes of slots): the cost of a probe or
+// of a walk to a cluster's start is then a round trip or two of memory instead of one per
+// slot.
+constexpr int kSpan = 8;
+constexpr uint64_t kFindGrid = 1u << 20;
+__device__ __forceinline__ uint32_t span_ballot(bool x, int lane) {
+  return (uint32_t)(__ballot(x) >> (lane & ~(kSpan - 1))) & ((1u << kSpan) - 1);
+}
+
 // The first `drop` of the sorted entries go: lists their keys, and finds the clusters to
-// repair: the first victim of a cluster (no victim before it up to the cluster's start)
-// lists the start. When every entry goes, the repair clears the table instead.
+// repair: starts[i] is the start of victim i's cluster if it is the cluster's first victim
+// (no victim before it up to the start), else kNoStart. (One word per victim: a list of the
+// starts needs an atomic per wave on one counter, 50 us for 20,000 victims.) Many victims
+// are repaired in a pass over the whole table instead, which needs no starts.
+constexpr uint32_t kNoStart = ~0u;
+
+// From one victim in 64 slots on: in 2^25 slots a pass over the table takes about as long
+// as finding and repairing the clusters of half a million victims one by one.
+__device__ __forceinline__ bool many_victims(const TableRef& t, uint64_t drop) { return drop > (t.mask + 1) / 64; }
 __global__ __launch_bounds__(kThreads) void evict_mark_kernel(TableRef t, SortBuf a, SortBuf b, uint64_t* counters,
-                                                              uint32_t* leaders, uint64_t* evicted, uint64_t* counts) {
+                                                              uint32_t* starts, uint64_t* evicted, uint64_t* counts) {
   const uint64_t drop = counters[kWDrop], live = counters[kWLive];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t0 == 0) {
     counts[0] = drop;
@@ -475,27 +617,44 @@ __global__ __launch_bounds__(kThreads) void evict_mark_kernel(TableRef t, SortBu
   if (drop == 0) return;
   const SortBuf sorted = sort_result(a, b, counters + kWBits, 2);
   const UpTo gone = last_victim(sorted, drop);
-  for (uint64_t i = t0; i < drop; i += stride) {
-    if (evicted) evicted[i] = sorted.lo[i];
-    const uint64_t p = sorted.idx[i];
-    if (p > t.mask) {  // the side slot
-      t.hdr[0] = t.hdr[1] = t.hdr[2] = 0;
-      continue;
+  const int lane = threadIdx.x & 63, l = lane & (kSpan - 1);
+  if (many_victims(t, drop)) {
+    for (uint64_t i = t0; i < drop; i += (uint64_t)gridDim.x * blockDim.x) {
+      if (evicted) evicted[i] = sorted.lo[i];
+      if (sorted.idx[i] > t.mask) t.hdr[0] = t.hdr[1] = t.hdr[2] = 0;  // the side slot
     }
-    if (drop == live) continue;
-    uint64_t c0 = p;
-    bool first = true;
-    for (uint64_t step = 0; step <= t.mask; ++step) {
-      const uint64_t before = (c0 - 1) & t.mask;
-      const uint64_t k = t.slots[2 * before];
-      if (k == kEmpty) break;
-      if (gone(k, t.stamps[before])) {
-        first = false;
-        break;
+    return;
+  }
+  const uint64_t spans = (uint64_t)gridDim.x * blockDim.x / kSpan;
+  const uint64_t rounds = (drop + spans - 1) / spans;
+  for (uint64_t r = 0; r < rounds; ++r) {  // the same number in every lane
+    const uint64_t i = r * spans + t0 / kSpan;
+    bool walking = i < drop;
+    uint64_t c0 = 0;
+    if (walking) {
+      c0 = sorted.idx[i];
+      if (evicted && l == 0) evicted[i] = sorted.lo[i];
+      if (c0 > t.mask) {  // the side slot
+        if (l == 0) t.hdr[0] = t.hdr[1] = t.hdr[2] = 0;
+        walking = false;
       }
-      c0 = before;
     }
-    if (first) leaders[atomicAdd(ull(&counters[kWLeaders]), 1ull)] = (uint32_t)c0;
+    bool first = walking;
+    for (uint64_t step = 0; __any(walking) && step <= t.mask; step += kSpan) {
+      const uint64_t p = (c0 - 1 - l) & t.mask;
+      const uint64_t k = t.slots[2 * p], stamp = t.stamps[p];
+      const uint32_t open = span_ballot(k == kEmpty, lane), hit = span_ballot(gone(k, stamp), lane);
+      const int far = open ? __builtin_ctz(open) : kSpan;  // entries of the cluster before c0, up to here
+      if (walking) {
+        if (hit & ((1u << far) - 1)) {
+          first = walking = false;
+        } else {
+          c0 = (c0 - far) & t.mask;
+          walking = far == kSpan;
+        }
+      }
+    }
+    if (i < drop && l == 0) starts[i] = first ? (uint32_t)c0 : kNoStart;
   }
 }
 
@@ -516,13 +675,17 @@ __device__ __forceinline__ uint32_t lane32(uint32_t x, int src) { return __built
 // written by any, so the end found here does not depend on other waves.
 template <class Erased>
 __device__ uint32_t wave_repair(const TableRef& t, uint64_t c0, const Erased& erased, uint64_t* used, int lane) {
+  const uint64_t p0 = (c0 + lane) & t.mask;
+  const uint4 e0 = *reinterpret_cast<const uint4*>(t.slots + 2 * p0);
+  const uint64_t stamp0 = t.stamps[p0];
   uint32_t len = 0;  // the cluster's slots
-  for (uint32_t w = 0; len == 64 * w; ++w) {
-    if (w == kRepairWords) break;
-    const uint64_t k = t.slots[2 * ((c0 + len + lane) & t.mask)];
-    const uint64_t free_slots = __ballot(k == kEmpty);
-    len += free_slots ? (uint32_t)__builtin_ctzll(free_slots) : 64u;
-    if (len > t.mask) break;  // a table has at least one free slot; bounded all the same
+  {
+    const uint64_t open = __ballot(lo64(e0) == kEmpty);
+    len = open ? (uint32_t)__builtin_ctzll(open) : 64u;
+    for (uint32_t w = 1; len == 64 * w && w < kRepairWords && len <= t.mask; ++w) {
+      const uint64_t more = __ballot(t.slots[2 * ((c0 + len + lane) & t.mask)] == kEmpty);
+      len += more ? (uint32_t)__builtin_ctzll(more) : 64u;
+    }
   }
   uint32_t removed = 0;
   if (len >= 64 * kRepairWords) {  // a longer cluster: one lane, slot by slot
@@ -556,8 +719,13 @@ __device__ uint32_t wave_repair(const TableRef& t, uint64_t c0, const Erased& er
   for (uint32_t w = 0; 64 * w < len; ++w) {
     const uint32_t i = 64 * w + (uint32_t)lane;
     const uint64_t p = (c0 + i) & t.mask;
-    const uint4 e = *reinterpret_cast<const uint4*>(t.slots + 2 * p);
-    const uint64_t stamp = t.stamps[p], k = lo64(e);
+    uint4 e = e0;
+    uint64_t stamp = stamp0;
+    if (w) {
+      e = *reinterpret_cast<const uint4*>(t.slots + 2 * p);
+      stamp = t.stamps[p];
+    }
+    const uint64_t k = lo64(e);
     const bool in = i < len;
     const bool gone = in && erased(k, stamp);
     const uint64_t keep = __ballot(in && !gone);
@@ -605,88 +773,135 @@ __device__ uint32_t wave_repair(const TableRef& t, uint64_t c0, const Erased& er
 
 // ---- erase: O(keys erased) ------------------------------------------------------------
 struct EraseWs {          // workspace of an erase of n keys
-  uint64_t* hdr;          // [0] removed entries | arrived workgroups << 40, [1] clusters to repair
-  uint64_t* keyset;       // cap slots: index + 1 of an erased key (0 free); keys read back
+  uint64_t* hdr;          // [0] removed entries | arrived workgroups << 40
+  uint64_t* keyset;       // cap slots: the erased keys (kEmpty free; that key is never in it)
   uint64_t* starts;       // cap slots: cluster start + 1 (0 free)
-  uint64_t* leaders;      // n cluster starts, one per cluster
+  uint64_t* leaders;      // per key: the cluster start it claimed, or kNone
   uint64_t mask;
   int shift;
 };
+constexpr uint64_t kNone = ~0ull;
 constexpr int kArrivedShift = 40;  // n <= 2^36 entries, and a grid below 2^24 workgroups
 
-__device__ __forceinline__ bool in_keyset(const EraseWs& w, const uint64_t* keys, uint64_t k) {
+__global__ __launch_bounds__(kThreads) void erase_clear_kernel(EraseWs w) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t0 == 0) w.hdr[0] = 0;
+  for (uint64_t i = t0; i <= w.mask; i += stride) {
+    w.keyset[i] = kEmpty;
+    w.starts[i] = 0;
+  }
+}
+
+__device__ __forceinline__ bool in_keyset(const EraseWs& w, uint64_t k) {
   uint64_t pos = slot_hash(k, w.shift);
   for (uint64_t probe = 0; probe <= w.mask; ++probe) {
     const uint64_t v = w.keyset[pos];
-    if (v == 0) return false;
-    if (keys[v - 1] == k) return true;
+    if (v == k) return true;
+    if (v == kEmpty) return false;
     pos = (pos + 1) & w.mask;
   }
   return false;
 }
 
-// Per erased key: into the key set; if the table holds it, the start of its cluster,
-// claimed once. (The two do not depend on each other: one launch.)
+// Per erased key, by kSpan lanes: into the key set; if the table holds it, the start of
+// its cluster, claimed once. (The two do not depend on each other: one launch, the first
+// probe of the table read before the key set's compare-and-swap.)
 __global__ __launch_bounds__(kThreads) void erase_find_kernel(TableRef t, const uint64_t* keys, uint64_t n, EraseWs w) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint64_t k = keys[i];
-  if (k == kEmpty) {  // the header's side slot
-    if (atomicExch(ull(&t.hdr[0]), 0ull) == 1ull) {
-      t.hdr[2] = 0;
-      atomicAdd(ull(&w.hdr[0]), 1ull);
+  const int lane = threadIdx.x & 63, l = lane & (kSpan - 1);
+  const uint64_t spans = (uint64_t)gridDim.x * blockDim.x / kSpan;
+  for (uint64_t base_i = (uint64_t)blockIdx.x * blockDim.x / kSpan; base_i < n; base_i += spans) {  // uniform
+    const uint64_t i = base_i + threadIdx.x / kSpan;
+    const uint64_t k = i < n ? keys[i] : kEmpty;
+    bool looking = k != kEmpty;
+    uint64_t at = slot_hash(k, t.shift);
+    uint64_t seen = t.slots[2 * ((at + l) & t.mask)];
+    uint32_t repeat = 0;
+    if (l == 0 && i < n) {
+      if (k == kEmpty) {  // the header's side slot
+        if (atomicExch(ull(&t.hdr[0]), 0ull) == 1ull) {
+          t.hdr[2] = 0;
+          atomicAdd(ull(&w.hdr[0]), 1ull);
+        }
+      } else {
+        uint64_t pos = slot_hash(k, w.shift);
+        for (uint64_t probe = 0; probe <= w.mask; ++probe) {
+          const uint64_t prev = atomicCAS(ull(&w.keyset[pos]), (unsigned long long)kEmpty, (unsigned long long)k);
+          if (prev == kEmpty) break;
+          if (prev == k) {  // a repeat: the other one finds the cluster
+            repeat = 1;
+            break;
+          }
+          pos = (pos + 1) & w.mask;
+        }
+      }
     }
-    return;
-  }
-  uint64_t pos = slot_hash(k, w.shift);
-  for (uint64_t probe = 0; probe <= w.mask; ++probe) {
-    const uint64_t prev = atomicCAS(ull(&w.keyset[pos]), 0ull, (unsigned long long)(i + 1));
-    if (prev == 0) break;
-    if (keys[prev - 1] == k) return;  // a repeat: the other one finds the cluster
-    pos = (pos + 1) & w.mask;
-  }
-  const int64_t at = find_slot(t, k);
-  if (at < 0) return;
-  uint64_t c0 = (uint64_t)at;
-  for (uint64_t step = 0; step <= t.mask; ++step) {
-    const uint64_t before = (c0 - 1) & t.mask;
-    if (t.slots[2 * before] == kEmpty) break;
-    c0 = before;
-  }
-  pos = slot_hash(c0, w.shift);
-  for (uint64_t probe = 0; probe <= w.mask; ++probe) {
-    const uint64_t prev = atomicCAS(ull(&w.starts[pos]), 0ull, (unsigned long long)(c0 + 1));
-    if (prev == 0) {
-      w.leaders[atomicAdd(ull(&w.hdr[1]), 1ull)] = c0;
-      return;
+    if (__shfl((int)repeat, lane & ~(kSpan - 1), 64)) looking = false;
+    bool found = false;
+    for (uint64_t step = 0; __any(looking) && step <= t.mask; step += kSpan) {
+      const uint32_t same = span_ballot(seen == k, lane), open = span_ballot(seen == kEmpty, lane);
+      if (looking) {
+        if (same) {  // a key is held once, and before the first empty slot from its home
+          const int j = __builtin_ctz(same);
+          found = (open & ((1u << j) - 1)) == 0;
+          at = (at + j) & t.mask;
+          looking = false;
+        } else if (open) {
+          looking = false;
+        } else {
+          at = (at + kSpan) & t.mask;
+        }
+      }
+      if (__any(looking)) seen = t.slots[2 * ((at + l) & t.mask)];
     }
-    if (prev == c0 + 1) return;  // claimed by another key of this cluster
-    pos = (pos + 1) & w.mask;
+    bool walking = found;
+    uint64_t c0 = at;
+    for (uint64_t step = 0; __any(walking) && step <= t.mask; step += kSpan) {
+      const uint32_t open = span_ballot(t.slots[2 * ((c0 - 1 - l) & t.mask)] == kEmpty, lane);
+      const int far = open ? __builtin_ctz(open) : kSpan;
+      if (walking) {
+        c0 = (c0 - far) & t.mask;
+        walking = far == kSpan;
+      }
+    }
+    bool first = false;
+    if (found && l == 0) {
+      uint64_t pos = slot_hash(c0, w.shift);
+      for (uint64_t probe = 0; probe <= w.mask; ++probe) {
+        const uint64_t prev = atomicCAS(ull(&w.starts[pos]), 0ull, (unsigned long long)(c0 + 1));
+        if (prev == 0) first = true;
+        if (prev == 0 || prev == c0 + 1) break;  // claimed here, or by another key of this cluster
+        pos = (pos + 1) & w.mask;
+      }
+    }
+    if (l == 0 && i < n) w.leaders[i] = first ? c0 : kNone;
   }
 }
 
 struct InKeyset {
   const EraseWs& w;
-  const uint64_t* keys;
-  __device__ bool operator()(uint64_t k, uint64_t) const { return in_keyset(w, keys, k); }
+  __device__ bool operator()(uint64_t k, uint64_t) const { return in_keyset(w, k); }
 };
 
-// One wave per cluster; the last workgroup to arrive writes the counts.
-__global__ __launch_bounds__(kThreads) void erase_repair_kernel(TableRef t, const uint64_t* keys, uint64_t n, EraseWs w,
-                                                                uint64_t* counts) {
-  __shared__ uint64_t used[kWaves][kRepairWords];
-  __shared__ uint32_t removed[kWaves];
+// One wave per cluster; the last workgroup to arrive writes the counts. Sixteen waves per
+// workgroup and a grid of at most kRepairGrid: the workgroups' arrivals queue on one word.
+constexpr int kRepairThreads = 1024;
+constexpr int kRepairWaves = kRepairThreads / 64;
+constexpr uint64_t kRepairGrid = 512;
+__global__ __launch_bounds__(kRepairThreads) void erase_repair_kernel(TableRef t, uint64_t n, EraseWs w,
+                                                                      uint64_t* counts) {
+  __shared__ uint64_t used[kRepairWaves][kRepairWords];
+  __shared__ uint32_t removed[kRepairWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t clusters = min(w.hdr[1], n);
-  const InKeyset erased{w, keys};
+  const InKeyset erased{w};
   uint32_t mine = 0;
-  for (uint64_t c = (uint64_t)blockIdx.x * kWaves + wave; c < clusters; c += (uint64_t)gridDim.x * kWaves)
-    mine += wave_repair(t, w.leaders[c], erased, used[wave], lane);
+  for (uint64_t c = (uint64_t)blockIdx.x * kRepairWaves + wave; c < n; c += (uint64_t)gridDim.x * kRepairWaves)
+    if (w.leaders[c] != kNone) mine += wave_repair(t, w.leaders[c], erased, used[wave], lane);
   if (lane == 0) removed[wave] = mine;
   __syncthreads();
   if (threadIdx.x == 0) {
     uint64_t add = 1ull << kArrivedShift;
-    for (int v = 0; v < kWaves; ++v) add += removed[v];
+    for (int v = 0; v < kRepairWaves; ++v) add += removed[v];
     const uint64_t now = atomicAdd(ull(&w.hdr[0]), (unsigned long long)add) + add;
     if (now >> kArrivedShift == gridDim.x) {
       const uint64_t total = now & ((1ull << kArrivedShift) - 1);
@@ -723,88 +938,129 @@ EraseWs erase_ws(void* ws, const EraseLayout& L) {
   return w;
 }
 
-// One wave per cluster with victims.
+// The clusters that start in the 64 slots of word w, by one wave; `occupied` tells the
+// clusters as they were before any repair (a neighbouring wave may already have emptied the
+// slot before these). Those that end here too are done together: their entries are in the
+// lanes, and empty slots, which stay empty, keep them apart. One that goes on past the word
+// takes wave_repair.
+template <class Erased>
+__device__ void wave_repair_word(const TableRef& t, const uint64_t* occupied, uint64_t w, const Erased& erased,
+                                 uint64_t* used, int lane) {
+  const uint64_t occ = occupied[w], before = (64 * w - 1) & t.mask;
+  const uint32_t size = t.mask < 63 ? (uint32_t)t.mask + 1 : 64u;
+  const uint64_t p = 64 * w + (uint64_t)lane < t.mask ? 64 * w + (uint64_t)lane : t.mask;
+  const uint4 e = *reinterpret_cast<const uint4*>(t.slots + 2 * p);
+  const uint64_t stamp = t.stamps[p], k = lo64(e);
+  const uint64_t starts = occ & ~(occ << 1 | ((occupied[before / 64] >> (before & 63)) & 1));
+  if (starts == 0) return;  // uniform, as all the masks are
+  // the slots of this word's own clusters: from the first start on
+  uint64_t own = occ & (~0ull << __builtin_ctzll(starts));
+  if ((own >> (size - 1)) & 1) {  // the last cluster reaches the word's end
+    const int c = 63 - __builtin_clzll(starts);
+    own &= (1ull << c) - 1;
+    wave_repair(t, 64 * w + (uint64_t)c, erased, used, lane);
+  }
+  const uint64_t gone = __ballot(((own >> lane) & 1) && erased(k, stamp));
+  if (gone == 0) return;
+  // entries after a victim of their cluster: flood upwards through the occupied slots
+  uint64_t flood = gone, run = own;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    flood |= run & (flood << d);
+    run &= run << d;
+  }
+  uint64_t moves = flood & ~gone, now = own & ~flood;
+  const uint32_t home = (uint32_t)(slot_hash(k, t.shift) - 64 * w) & 63;
+  uint32_t to = (uint32_t)lane;
+  for (uint64_t left = moves; left; left &= left - 1) {
+    const int src = __builtin_ctzll(left);
+    const uint64_t room = ~now & (~0ull << lane32(home, src));
+    now |= room & (0 - room);
+    if (lane == src) to = (uint32_t)__builtin_ctzll(room);
+  }
+  if (((moves >> lane) & 1) && to != (uint32_t)lane) {
+    *reinterpret_cast<uint4*>(t.slots + 2 * (64 * w + to)) = e;
+    t.stamps[64 * w + to] = stamp;
+  }
+  if (((own & ~now) >> lane) & 1) {
+    t.slots[2 * p] = kEmpty;
+    t.stamps[p] = 0;
+  }
+}
+
+// One wave per cluster with victims, or, with many, one per 64 slots of the table; with
+// nothing but victims, a clear.
 __global__ __launch_bounds__(kThreads) void evict_repair_kernel(TableRef t, SortBuf a, SortBuf b,
-                                                                const uint64_t* counters, const uint32_t* leaders) {
+                                                                const uint64_t* counters, const uint32_t* starts,
+                                                                const uint64_t* occupied) {
   __shared__ uint64_t used[kWaves][kRepairWords];
   const uint64_t drop = counters[kWDrop];
   if (drop == 0) return;
   if (drop == counters[kWLive]) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p <= t.mask; p += stride) {
-      t.slots[2 * p] = kEmpty;
+      *reinterpret_cast<uint4*>(t.slots + 2 * p) = make_uint4(~0u, ~0u, ~0u, ~0u);  // kEmpty, any value
       t.stamps[p] = 0;
     }
     return;
   }
   const UpTo gone = last_victim(sort_result(a, b, counters + kWBits, 2), drop);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t clusters = counters[kWLeaders];
-  for (uint64_t c = (uint64_t)blockIdx.x * kWaves + wave; c < clusters; c += (uint64_t)gridDim.x * kWaves)
-    wave_repair(t, leaders[c], gone, used[wave], lane);
+  const uint64_t first = (uint64_t)blockIdx.x * kWaves + wave, stride = (uint64_t)gridDim.x * kWaves;
+  if (many_victims(t, drop)) {
+    const uint64_t words = (t.mask + 64) / 64;
+    for (uint64_t w = first; w < words; w += stride) wave_repair_word(t, occupied, w, gone, used[wave], lane);
+  } else {
+    for (uint64_t c = first; c < drop; c += stride)
+      if (starts[c] != kNoStart) wave_repair(t, starts[c], gone, used[wave], lane);
+  }
 }
 
 // ---- export ---------------------------------------------------------------------------
-// Every entry in key order by one partition: the key range is cut into bins (one per
-// kBinSlots table slots), every entry is written once to its bin's place in the workspace,
-// and one workgroup per bin sorts its few thousand entries in LDS and writes them out. Keys
-// are digests, so the bins of an ordinary table are even; when one holds more than kBinMax
-// entries (a skewed key set), all entries go through the radix sort instead, decided on
-// the device. 20 M entries: 1.25 ms (the table read twice, the entries written and read
-// once), against 3.0 ms for eight digit passes and a gather of the values.
+// Every entry in key order by one partition: each entry is written once to its bin of the
+// key range, and one workgroup per part of a bin picks the part's entries out of the bin,
+// sorts them in LDS and writes them out. Keys are digests, so the parts of an ordinary
+// table are even; when one holds more than kPartMax entries or a bin more than kBinMax (a
+// skewed key set), all entries go through the radix sort instead, decided on the device.
+// 20 M entries of 2^25 slots: 1.0 ms (count 90 us, spread 394, parts 430), against 3.0 ms for
+// eight digit passes and a gather of the values. Bound by the chains inside a workgroup: the
+// table is read twice and the entries are written and read once, 0.3 ms at HBM rate.
 constexpr uint32_t kSpreadThreads = 1024;
-constexpr uint32_t kSpreadItems = 4;
+constexpr uint32_t kSpreadItems = 4;  // slots per thread and step when counting
+constexpr uint32_t kSpreadEach = 8;   // slots per thread and tile when spreading
 
-// Entries of one spreading workgroup's share of the slots, by bin (share[g][bin]), or
-// (kWrite) written to their places: the workgroup's place in a bin starts at
-// starts[bin] + share[g][bin].
-template <bool kWrite>
-__global__ __launch_bounds__(kSpreadThreads) void export_spread_kernel(TableRef t, const uint64_t* counters,
-                                                                       uint32_t n_bins, uint32_t* share,
-                                                                       const uint32_t* starts, Entry* entries) {
-  __shared__ uint32_t at[kMaxBins];
-  uint32_t* row = share + (uint64_t)blockIdx.x * n_bins;
-  for (uint32_t i = threadIdx.x; i < n_bins; i += kSpreadThreads) at[i] = kWrite ? starts[i] + row[i] : 0;
+// Counts the entries of the parts in this workgroup's share of the slots.
+__global__ __launch_bounds__(kSpreadThreads) void export_count_kernel(TableRef t, const uint64_t* counters, uint32_t all,
+                                                                      uint32_t* share) {
+  __shared__ uint32_t h[kMaxAllParts];
+  for (uint32_t i = threadIdx.x; i < all; i += kSpreadThreads) h[i] = 0;
   __syncthreads();
-  const Bins bins(counters, n_bins);
+  const KeyCells cells(counters, all * kCuts);
   const uint64_t capacity = t.mask + 1;
   const uint64_t each = (capacity + gridDim.x - 1) / gridDim.x;
   const uint64_t lo = blockIdx.x * each, hi = lo + each < capacity ? lo + each : capacity;
-  auto put = [&](uint64_t key, uint64_t val, uint64_t stamp) {
-    const uint32_t p = atomicAdd(&at[bins.of(key)], 1u);
-    if (kWrite) {
-      uint4* to = reinterpret_cast<uint4*>(&entries[p]);
-      to[0] = make_uint4((uint32_t)key, (uint32_t)(key >> 32), (uint32_t)val, (uint32_t)(val >> 32));
-      to[1] = make_uint4((uint32_t)stamp, (uint32_t)(stamp >> 32), 0, 0);
-    }
-  };
   for (uint64_t i0 = lo; i0 < hi; i0 += (uint64_t)kSpreadThreads * kSpreadItems) {
-    uint4 slot[kSpreadItems];
-    uint64_t stamp[kSpreadItems];
+    uint64_t key[kSpreadItems];
 #pragma unroll
     for (uint32_t r = 0; r < kSpreadItems; ++r) {  // unconditional (clamped) loads, issued together
-      const uint64_t i = i0 + r * kSpreadThreads + threadIdx.x, p = i < hi ? i : hi - 1;
-      slot[r] = *reinterpret_cast<const uint4*>(t.slots + 2 * p);
-      stamp[r] = kWrite ? t.stamps[p] : 0;
+      const uint64_t i = i0 + r * kSpreadThreads + threadIdx.x;
+      key[r] = t.slots[2 * (i < hi ? i : hi - 1)];
+      if (i >= hi) key[r] = kEmpty;
     }
 #pragma unroll
-    for (uint32_t r = 0; r < kSpreadItems; ++r) {
-      const uint64_t i = i0 + r * kSpreadThreads + threadIdx.x;
-      if (i < hi && lo64(slot[r]) != kEmpty) put(lo64(slot[r]), hi64(slot[r]), stamp[r]);
-    }
+    for (uint32_t r = 0; r < kSpreadItems; ++r)
+      if (key[r] != kEmpty) atomicAdd(&h[cells.of(key[r]) / kCuts], 1u);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && t.hdr[0]) put(kEmpty, t.hdr[1], t.hdr[2]);
-  if (!kWrite) {
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n_bins; i += kSpreadThreads) row[i] = at[i];
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && t.hdr[0]) atomicAdd(&h[cells.of(kEmpty) / kCuts], 1u);
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < all; i += kSpreadThreads) share[(uint64_t)blockIdx.x * all + i] = h[i];
 }
 
-// share[g][bin] becomes the count of the workgroups before g; starts[bin] the bin's total.
-__global__ __launch_bounds__(64) void export_share_kernel(uint32_t n_bins, uint32_t groups, uint32_t* share,
+// share[g][part] becomes the count of the workgroups before g; starts[part] the part's total.
+__global__ __launch_bounds__(64) void export_share_kernel(uint32_t all, uint32_t groups, uint32_t* share,
                                                           uint32_t* starts) {
-  const uint32_t bin = blockIdx.x * 64 + threadIdx.x;
-  if (bin >= n_bins) return;
+  const uint32_t part = blockIdx.x * 64 + threadIdx.x;
+  if (part >= all) return;
   constexpr uint32_t kAhead = 32;
   uint32_t sum = 0;
   for (uint32_t g0 = 0; g0 < groups; g0 += kAhead) {
@@ -812,35 +1068,33 @@ __global__ __launch_bounds__(64) void export_share_kernel(uint32_t n_bins, uint3
 #pragma unroll
     for (uint32_t k = 0; k < kAhead; ++k) {  // unconditional (clamped) loads, issued together
       const uint32_t g = g0 + k < groups ? g0 + k : groups - 1;
-      c[k] = share[(uint64_t)g * n_bins + bin];
+      c[k] = share[(uint64_t)g * all + part];
     }
 #pragma unroll
     for (uint32_t k = 0; k < kAhead; ++k) {
       if (g0 + k >= groups) break;
-      share[(uint64_t)(g0 + k) * n_bins + bin] = sum;
+      share[(uint64_t)(g0 + k) * all + part] = sum;
       sum += c[k];
     }
   }
-  starts[bin] = sum;
+  starts[part] = sum;
 }
 
-constexpr uint32_t kBinMax = 6144;     // entries that a workgroup sorts in LDS
-constexpr uint32_t kBinThreads = 512;
-constexpr uint32_t kBinEach = kBinMax / kBinThreads;
-constexpr uint32_t kSubBins = 4096;
-
-// One workgroup: starts[bin] from totals to positions, starts[n_bins] = the entries; the
-// count; and whether the radix sort takes over (counters[kWCollected]: its count, else 0).
-__global__ __launch_bounds__(kInitThreads) void export_starts_kernel(uint32_t n_bins, uint32_t* starts,
+// One workgroup: starts[] from totals to positions, starts[all] = the entries; the count;
+// and whether the radix sort takes over (counters[kWCollected]: its count, else 0).
+__global__ __launch_bounds__(kInitThreads) void export_starts_kernel(uint32_t bins, uint32_t parts, uint32_t* starts,
                                                                      uint64_t* counters, uint64_t* count) {
-  __shared__ uint32_t wave_sum[kInitThreads / 64], wave_most[kInitThreads / 64];
-  constexpr uint32_t kEach = kMaxBins / kInitThreads;
+  __shared__ uint32_t wave_sum[kInitThreads / 64];
+  __shared__ uint32_t skewed;
+  constexpr uint32_t kEach = kMaxAllParts / kInitThreads;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t each = (n_bins + kInitThreads - 1) / kInitThreads;  // at most kEach
+  const uint32_t all = bins * parts;
+  const uint32_t each = (all + kInitThreads - 1) / kInitThreads;  // at most kEach
   const uint32_t first = threadIdx.x * each;
+  if (threadIdx.x == 0) skewed = 0;
   uint32_t c[kEach], sum = 0, most = 0;
 #pragma unroll
-  for (uint32_t j = 0; j < kEach; ++j) c[j] = j < each && first + j < n_bins ? starts[first + j] : 0;
+  for (uint32_t j = 0; j < kEach; ++j) c[j] = j < each && first + j < all ? starts[first + j] : 0;
 #pragma unroll
   for (uint32_t j = 0; j < kEach; ++j) {
     sum += c[j];
@@ -852,78 +1106,351 @@ __global__ __launch_bounds__(kInitThreads) void export_starts_kernel(uint32_t n_
     const uint32_t y = __shfl_up(incl, d, 64);
     if (lane >= d) incl += y;
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, o, 64));
   if (lane == 63) wave_sum[wave] = incl;
-  if (lane == 0) wave_most[wave] = most;
   __syncthreads();
   uint32_t run = incl - sum, total = 0;
-  for (uint32_t w = 0; w < kInitThreads / 64; ++w) {
-    if ((int)w < wave) run += wave_sum[w];
+  for (int w = 0; w < (int)(kInitThreads / 64); ++w) {
+    if (w < wave) run += wave_sum[w];
     total += wave_sum[w];
-    most = max(most, wave_most[w]);
   }
 #pragma unroll
   for (uint32_t j = 0; j < kEach; ++j) {
-    if (j < each && first + j < n_bins) starts[first + j] = run;
+    if (j < each && first + j < all) starts[first + j] = run;
     run += c[j];
   }
+  if (threadIdx.x == 0) starts[all] = total;
+  __syncthreads();  // every start, read back by this workgroup
+  bool bad = most > kPartMax;
+  for (uint32_t b = threadIdx.x; b < bins; b += kInitThreads)
+    bad = bad || starts[(b + 1) * parts] - starts[b * parts] > kBinMax;
+  if (bad) skewed = 1;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    starts[n_bins] = total;
     *count = total;
-    counters[kWCollected] = most > kBinMax ? total : 0;
+    counters[kWCollected] = skewed ? total : 0;
   }
 }
 
-// Sorts one bin. Its entries are counted over kSubBins cuts of the bin's range and placed
-// cut by cut in LDS; within a cut (0.6 entries on average) an entry's rank is the number of
-// smaller keys in it. When a cut holds more than kCutMax entries (keys crowded inside the
-// bin's range) the workgroup sorts the bin with a comparison network instead.
-constexpr uint32_t kCutMax = 32;
-
-__global__ __launch_bounds__(kBinThreads) void export_bin_kernel(const uint64_t* counters, uint32_t n_bins,
-                                                                 const uint32_t* starts, const Entry* entries,
-                                                                 uint64_t* keys, uint64_t* vals, uint64_t* stamps) {
-  __shared__ uint64_t skey[kBinMax];
-  __shared__ uint16_t sidx[kBinMax];
-  __shared__ uint32_t cut[kSubBins + 1];
-  __shared__ uint32_t wave_sum[kBinThreads / 64];
-  __shared__ uint32_t crowded;
-  if (counters[kWCollected]) return;  // the radix sort takes over
-  const uint32_t bin = blockIdx.x;
-  const uint32_t s0 = starts[bin], n = starts[bin + 1] - s0;
-  if (n == 0) return;
-  const uint64_t base = counters[kWBaseLo];
-  const uint32_t shift = (uint32_t)counters[kWShift];
-  const uint64_t bin_lo = base + (shift < 64 ? (uint64_t)bin << shift : 0ull);
-  const uint32_t cut_shift = shift > 12 ? shift - 12 : 0;
-  static_assert(kSubBins == 1u << 12, "cut_shift");
-  auto cut_of = [&](uint64_t k) -> uint32_t {  // never decreases with the key within the bin
-    if (k < bin_lo) return 0;
-    const uint64_t c = (k - bin_lo) >> cut_shift;
-    return c < kSubBins ? (uint32_t)c : kSubBins - 1;
-  };
+// Writes the entries of this workgroup's share of the slots to their bins: the workgroup's
+// place in a bin starts after those of the workgroups before it. A tile of slots is put in
+// bin order in LDS first, so that consecutive lanes write a bin's entries to consecutive
+// addresses: written one by one, 20 M entries are 40 M small requests to the L2s (580 us).
+constexpr uint32_t kTileSlots = kSpreadThreads * kSpreadEach;
+__global__ __launch_bounds__(kSpreadThreads) void export_spread_kernel(TableRef t, const uint64_t* counters,
+                                                                       uint32_t bins, uint32_t parts,
+                                                                       const uint32_t* share, const uint32_t* starts,
+                                                                       uint64_t* xkey, uint4* xpay) {
+  __shared__ uint32_t at[kMaxBins];     // the workgroup's next place in each bin
+  __shared__ uint32_t count[kMaxBins];  // the tile's entries by bin, then their first places in the tile
+  __shared__ uint16_t sbin[kTileSlots];
+  __shared__ uint4 buf[kTileSlots / 2];  // the tile's keys, then one half and the other of the payloads
+  __shared__ uint32_t wave_sum[kSpreadThreads / 64];
+  const uint32_t all = bins * parts;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint64_t k[kBinEach];
-#pragma unroll
-  for (uint32_t r = 0; r < kBinEach; ++r) {
-    const uint32_t i = r * kBinThreads + threadIdx.x;
-    k[r] = i < n ? entries[s0 + i].key : 0;
+  for (uint32_t b = threadIdx.x; b < bins; b += kSpreadThreads) {
+    uint32_t from = starts[b * parts];
+    for (uint32_t j = 0; j < parts; ++j) from += share[(uint64_t)blockIdx.x * all + b * parts + j];
+    at[b] = from;
   }
-  for (uint32_t i = threadIdx.x; i < kSubBins + 1; i += kBinThreads) cut[i] = 0;
-  if (threadIdx.x == 0) crowded = 0;
-  __syncthreads();
-  uint32_t ord[kBinEach];  // within its cut, in arrival order
+  const KeyCells cells(counters, all * kCuts);
+  const uint32_t per_bin = parts * kCuts;
+  const uint64_t capacity = t.mask + 1;
+  const uint64_t each = (capacity + gridDim.x - 1) / gridDim.x;
+  const uint64_t lo = blockIdx.x * each, hi = lo + each < capacity ? lo + each : capacity;
+  uint64_t* skey = reinterpret_cast<uint64_t*>(buf);
+  for (uint64_t i0 = lo; i0 < hi; i0 += kTileSlots) {
+    uint4 slot[kSpreadEach];
+    uint64_t stamp[kSpreadEach];
 #pragma unroll
-  for (uint32_t r = 0; r < kBinEach; ++r) {
-    const uint32_t i = r * kBinThreads + threadIdx.x;
+    for (uint32_t r = 0; r < kSpreadEach; ++r) {  // unconditional (clamped) loads, issued together
+      const uint64_t i = i0 + r * kSpreadThreads + threadIdx.x, p = i < hi ? i : hi - 1;
+      slot[r] = *reinterpret_cast<const uint4*>(t.slots + 2 * p);
+      stamp[r] = t.stamps[p];
+      if (i >= hi) slot[r].x = slot[r].y = ~0u;  // kEmpty
+    }
+    for (uint32_t b = threadIdx.x; b < bins; b += kSpreadThreads) count[b] = 0;
+    __syncthreads();
+    uint32_t bin[kSpreadEach], pos[kSpreadEach];
+#pragma unroll
+    for (uint32_t r = 0; r < kSpreadEach; ++r) {
+      if (lo64(slot[r]) == kEmpty) continue;
+      bin[r] = cells.of(lo64(slot[r])) / per_bin;
+      pos[r] = atomicAdd(&count[bin[r]], 1u);
+    }
+    __syncthreads();
+    {  // count becomes the bins' first places in the tile; at - count stays the shift to global places
+      constexpr uint32_t kEach = kMaxBins / kSpreadThreads;
+      uint32_t c[kEach], sum = 0;
+#pragma unroll
+      for (uint32_t j = 0; j < kEach; ++j) {
+        const uint32_t b = threadIdx.x * kEach + j;
+        c[j] = b < bins ? count[b] : 0;
+        sum += c[j];
+      }
+      uint32_t incl = sum;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+      }
+      if (lane == 63) wave_sum[wave] = incl;
+      __syncthreads();
+      uint32_t run = incl - sum;
+      for (int w = 0; w < wave; ++w) run += wave_sum[w];
+#pragma unroll
+      for (uint32_t j = 0; j < kEach; ++j) {
+        const uint32_t b = threadIdx.x * kEach + j;
+        if (b < bins) count[b] = run;
+        run += c[j];
+      }
+    }
+    __syncthreads();
+    uint32_t n = 0;  // the tile's entries
+    for (int w = 0; w < (int)(kSpreadThreads / 64); ++w) n += wave_sum[w];
+#pragma unroll
+    for (uint32_t r = 0; r < kSpreadEach; ++r) {
+      if (lo64(slot[r]) == kEmpty) continue;
+      pos[r] += count[bin[r]];
+      sbin[pos[r]] = (uint16_t)bin[r];
+      skey[pos[r]] = lo64(slot[r]);
+    }
+    __syncthreads();
+    uint32_t to[kSpreadEach];
+#pragma unroll
+    for (uint32_t r = 0; r < kSpreadEach; ++r) {
+      const uint32_t j = r * kSpreadThreads + threadIdx.x;
+      if (j >= n) continue;
+      to[r] = at[sbin[j]] + j - count[sbin[j]];
+      xkey[to[r]] = skey[j];
+    }
+#pragma unroll
+    for (uint32_t half = 0; half < 2; ++half) {
+      __syncthreads();  // buf read out
+#pragma unroll
+      for (uint32_t r = 0; r < kSpreadEach; ++r) {
+        if (lo64(slot[r]) == kEmpty || pos[r] / (kTileSlots / 2) != half) continue;
+        buf[pos[r] % (kTileSlots / 2)] =
+            make_uint4(slot[r].z, slot[r].w, (uint32_t)stamp[r], (uint32_t)(stamp[r] >> 32));
+      }
+      __syncthreads();
+#pragma unroll
+      for (uint32_t r = half * kSpreadEach / 2; r < (half + 1) * kSpreadEach / 2; ++r) {
+        const uint32_t j = r * kSpreadThreads + threadIdx.x;
+        if (j < n) xpay[to[r]] = buf[j % (kTileSlots / 2)];
+      }
+    }
+    for (uint32_t b = threadIdx.x; b < bins; b += kSpreadThreads)  // on to the next tile
+      at[b] += (b + 1 < bins ? count[b + 1] : n) - count[b];
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && t.hdr[0]) {
+    const uint32_t p = at[cells.of(kEmpty) / per_bin];
+    xkey[p] = kEmpty;
+    xpay[p] = make_uint4((uint32_t)t.hdr[1], (uint32_t)(t.hdr[1] >> 32), (uint32_t)t.hdr[2], (uint32_t)(t.hdr[2] >> 32));
+  }
+}
+
+// The least key of cell c (its cells start there: of(k) >= c exactly for the keys from it on),
+// or 0 with *none set when no key reaches the cell.
+__device__ __forceinline__ uint64_t first_key(const KeyCells& x, uint32_t c, bool* none) {
+  *none = false;
+  if (c == 0) return 0;
+  *none = true;
+  if (x.factor == 0) return 0;
+  const uint64_t t = (((uint64_t)c << 32) + x.factor - 1) / x.factor;  // leading bits that reach c
+  if (t >> 32) return 0;
+  const uint64_t d = (t << 32) == 0 ? 0 : ((t << 32) - 1 >> x.lead) + 1;  // distances with those bits
+  if (d > x.width) return 0;
+  *none = false;
+  return x.base + d;
+}
+
+// Sorts one part of a bin. It picks the part's keys out of the bin's, counts them over the
+// part's kCuts cuts and places them cut by cut in LDS; within a cut (2.4 entries on
+// average) an entry's rank is the number of smaller keys in it. When a cut holds more than
+// kCutMax entries (keys crowded inside the part's range) the part is sorted by its keys'
+// digits instead. The parts of a bin run on one XCD, one after another
+// (workgroups go round the eight XCDs), so that XCD's L2 serves the bin's keys to them all.
+constexpr uint32_t kPartThreads = 1024;
+constexpr uint32_t kPartEach = kPartMax / kPartThreads;
+constexpr uint32_t kCutMax = 48;
+constexpr uint32_t kXcds = 8;
+
+// Sorts skey[0, n) with sidx by all eight 8-bit digits, but those that every key shares, in
+// place in LDS. `run` holds kPartWaves * 256 counts. Every thread of the workgroup calls it.
+constexpr int kPartWaves = (int)kPartThreads / 64;
+__device__ void part_radix_sort(uint64_t* skey, uint16_t* sidx, uint16_t* run, uint32_t* wave_sum, uint32_t n) {
+  static_assert(kPartWaves * kDigits * sizeof(uint16_t) <= (kCuts + 1) * sizeof(uint32_t), "run fits in the cuts");
+  static_assert(kPartThreads >= kDigits, "one thread per digit");
+  __shared__ uint64_t fold[kPartWaves][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const uint32_t span0 = (uint32_t)wave * 64 * kPartEach;
+  uint64_t and_k = ~0ull, or_k = 0;
+  for (uint32_t i = threadIdx.x; i < n; i += kPartThreads) {
+    and_k &= skey[i];
+    or_k |= skey[i];
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    and_k &= shfl_xor64(and_k, o);
+    or_k |= shfl_xor64(or_k, o);
+  }
+  if (lane == 0) {
+    fold[wave][0] = and_k;
+    fold[wave][1] = or_k;
+  }
+  __syncthreads();
+  for (int w = 0; w < kPartWaves; ++w) {
+    and_k &= fold[w][0];
+    or_k |= fold[w][1];
+  }
+  const uint64_t differ = and_k ^ or_k;
+  for (int sh = 0; sh < 64; sh += 8) {
+    if (((differ >> sh) & 0xFFu) == 0) continue;  // uniform
+    uint64_t k[kPartEach];
+    uint32_t ix[kPartEach], at[kPartEach];
+    for (int d = lane; d < kDigits; d += 64) run[wave * kDigits + d] = 0;
+    wave_lds_sync();
+#pragma unroll
+    for (uint32_t r = 0; r < kPartEach; ++r) {
+      const uint32_t i = span0 + 64 * r + lane;
+      const bool valid = i < n;
+      k[r] = valid ? skey[i] : 0;
+      ix[r] = valid ? sidx[i] : 0;
+      const uint32_t d = (uint32_t)(k[r] >> sh) & 0xFFu;
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit) {
+        const uint64_t ones = __ballot(valid && ((d >> bit) & 1u));
+        peers &= ((d >> bit) & 1u) ? ones : ~ones;
+      }
+      const uint32_t below = (uint32_t)__popcll(peers & lt), prior = run[wave * kDigits + d];
+      at[r] = prior + below;
+      if (valid && below == 0) run[wave * kDigits + d] = (uint16_t)(prior + (uint32_t)__popcll(peers));
+      wave_lds_sync();  // this round's counts before the next round's reads
+    }
+    __syncthreads();
+    uint32_t total = 0, incl = 0;
+    if (threadIdx.x < kDigits) {
+      for (int w = 0; w < kPartWaves; ++w) total += run[w * kDigits + threadIdx.x];
+      incl = total;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      if (lane == 63) wave_sum[wave] = incl;
+    }
+    __syncthreads();
+    if (threadIdx.x < kDigits) {
+      uint32_t from = incl - total;
+      for (int w = 0; w < wave; ++w) from += wave_sum[w];
+      for (int w = 0; w < kPartWaves; ++w) {
+        const uint32_t c = run[w * kDigits + threadIdx.x];
+        run[w * kDigits + threadIdx.x] = (uint16_t)from;
+        from += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < kPartEach; ++r) {
+      if (span0 + 64 * r + lane >= n) continue;
+      const uint32_t p = at[r] + run[wave * kDigits + ((uint32_t)(k[r] >> sh) & 0xFFu)];
+      skey[p] = k[r];
+      sidx[p] = (uint16_t)ix[r];
+    }
+    __syncthreads();
+  }
+}
+
+// kCrowded: the second launch, for the parts that the first left in left_over (their digit
+// sort's registers would halve the first one's waves).
+template <bool kCrowded>
+__global__ __launch_bounds__(kPartThreads) void export_part_kernel(const uint64_t* counters, uint32_t bins,
+                                                                   uint32_t parts, const uint32_t* starts,
+                                                                   const uint64_t* xkey, const uint4* xpay,
+                                                                   uint32_t* left_over, uint64_t* keys, uint64_t* vals,
+                                                                   uint64_t* stamps) {
+  __shared__ uint64_t skey[kPartMax];
+  __shared__ uint16_t sidx[kPartMax];  // number within the bin
+  __shared__ uint32_t cut[kCuts + 1];
+  __shared__ uint32_t wave_sum[kPartThreads / 64];
+  __shared__ uint32_t picked, crowded;
+  if (counters[kWCollected]) return;  // the radix sort takes over
+  uint32_t bin = blockIdx.x / parts, part = blockIdx.x % parts;
+  if (bins % kXcds == 0) {
+    const uint32_t y = blockIdx.x / kXcds;
+    part = y % parts;
+    bin = y / parts * kXcds + blockIdx.x % kXcds;
+  }
+  const uint32_t me = bin * parts + part;
+  const uint32_t out0 = starts[me], n = starts[me + 1] - out0;
+  if (kCrowded && !left_over[me]) return;
+  if (n == 0) {
+    if (!kCrowded && threadIdx.x == 0) left_over[me] = 0;
+    return;
+  }
+  const uint32_t s0 = starts[bin * parts], n_bin = starts[(bin + 1) * parts] - s0;
+  const KeyCells cells(counters, bins * parts * kCuts);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+  for (uint32_t i = threadIdx.x; i < kCuts + 1; i += kPartThreads) cut[i] = 0;
+  if (threadIdx.x == 0) picked = crowded = 0;
+  // the part's keys: [from, to), or from `from` on for the last part that any key reaches
+  bool no_from, no_to;
+  const uint64_t from = first_key(cells, me * kCuts, &no_from), to = first_key(cells, (me + 1) * kCuts, &no_to);
+  __syncthreads();
+  constexpr uint32_t kAhead = 8;
+  for (uint32_t i0 = 0; i0 < n_bin; i0 += kAhead * kPartThreads) {
+    uint64_t k[kAhead];
+#pragma unroll
+    for (uint32_t r = 0; r < kAhead; ++r) {  // unconditional (clamped) loads, issued together
+      const uint32_t i = i0 + r * kPartThreads + threadIdx.x;
+      k[r] = xkey[s0 + (i < n_bin ? i : n_bin - 1)];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kAhead; ++r) {
+      const uint32_t i = i0 + r * kPartThreads + threadIdx.x;
+      const bool mine = i < n_bin && k[r] >= from && (k[r] < to || no_to);
+      const uint64_t who = __ballot(mine);
+      if (who == 0) continue;
+      uint32_t p = 0;
+      if (lane == 0) p = atomicAdd(&picked, (uint32_t)__popcll(who));
+      p = __builtin_amdgcn_readfirstlane(p) + (uint32_t)__popcll(who & lt);
+      if (mine && p < kPartMax) {
+        skey[p] = k[r];
+        sidx[p] = (uint16_t)i;
+      }
+    }
+  }
+  __syncthreads();
+  if (kCrowded) {
+    part_radix_sort(skey, sidx, reinterpret_cast<uint16_t*>(cut), wave_sum, n);
+    for (uint32_t p = threadIdx.x; p < n; p += kPartThreads) {
+      const uint4 pay = xpay[s0 + sidx[p]];
+      keys[out0 + p] = skey[p];
+      vals[out0 + p] = lo64(pay);
+      if (stamps) stamps[out0 + p] = hi64(pay);
+    }
+    return;
+  }
+  uint64_t k[kPartEach];
+  uint32_t ord[kPartEach], ix[kPartEach];  // place within its cut, in arrival order; number within the bin
+#pragma unroll
+  for (uint32_t r = 0; r < kPartEach; ++r) {
+    const uint32_t i = r * kPartThreads + threadIdx.x;
     if (i >= n) continue;
-    ord[r] = atomicAdd(&cut[cut_of(k[r])], 1u);
+    k[r] = skey[i];
+    ix[r] = sidx[i];
+    ord[r] = atomicAdd(&cut[cells.of(k[r]) % kCuts], 1u);
     if (ord[r] >= kCutMax) crowded = 1;
   }
   __syncthreads();
+  if (threadIdx.x == 0) left_over[me] = crowded;
+  if (crowded) return;
   {  // exclusive scan of the cuts' counts
-    constexpr uint32_t kEach = kSubBins / kBinThreads;
+    constexpr uint32_t kEach = kCuts / kPartThreads;
     uint32_t c[kEach], sum = 0;
 #pragma unroll
     for (uint32_t j = 0; j < kEach; ++j) {
@@ -945,64 +1472,39 @@ __global__ __launch_bounds__(kBinThreads) void export_bin_kernel(const uint64_t*
       cut[threadIdx.x * kEach + j] = run;
       run += c[j];
     }
-    if (threadIdx.x == kBinThreads - 1) cut[kSubBins] = run;
+    if (threadIdx.x == kPartThreads - 1) cut[kCuts] = run;
   }
   __syncthreads();
 #pragma unroll
-  for (uint32_t r = 0; r < kBinEach; ++r) {
-    const uint32_t i = r * kBinThreads + threadIdx.x;
-    if (i >= n) continue;
-    const uint32_t p = cut[cut_of(k[r])] + ord[r];
+  for (uint32_t r = 0; r < kPartEach; ++r) {
+    if (r * kPartThreads + threadIdx.x >= n) continue;
+    const uint32_t p = cut[cells.of(k[r]) % kCuts] + ord[r];
     skey[p] = k[r];
-    sidx[p] = (uint16_t)i;
+    sidx[p] = (uint16_t)ix[r];
   }
   __syncthreads();
-  const bool network = crowded != 0;
-  if (network) {  // ascending merges of runs of len / 2, the second run read backwards first
-    for (uint32_t len = 2; len < 2 * n; len <<= 1) {
-      for (uint32_t j = len / 2; j > 0; j >>= 1) {
-        for (uint32_t q = threadIdx.x; q < kBinMax; q += kBinThreads) {
-          const uint32_t at = q / j * 2 * j + q % j;
-          const uint32_t other = j == len / 2 ? q / j * len + (len - 1 - q % j) : at + j;
-          if (other < n && skey[at] > skey[other]) {
-            const uint64_t tk = skey[at];
-            skey[at] = skey[other];
-            skey[other] = tk;
-            const uint16_t ti = sidx[at];
-            sidx[at] = sidx[other];
-            sidx[other] = ti;
-          }
-        }
-        __syncthreads();
-      }
-    }
-  }
 #pragma unroll
-  for (uint32_t r = 0; r < kBinEach; ++r) {
-    const uint32_t p = r * kBinThreads + threadIdx.x;
+  for (uint32_t r = 0; r < kPartEach; ++r) {
+    const uint32_t p = r * kPartThreads + threadIdx.x;
     if (p >= n) continue;
     const uint64_t key = skey[p];
-    uint32_t rank = p;
-    if (!network) {
-      const uint32_t c = cut_of(key), from = cut[c], to = cut[c + 1];
-      rank = from;
-      for (uint32_t q = from; q < to; ++q) rank += skey[q] < key ? 1u : 0u;
-    }
-    const Entry* e = &entries[s0 + sidx[p]];
-    keys[s0 + rank] = key;
-    vals[s0 + rank] = e->val;
-    if (stamps) stamps[s0 + rank] = e->stamp;
+    const uint4 pay = xpay[s0 + sidx[p]];
+    const uint32_t c = cells.of(key) % kCuts, end = cut[c + 1];
+    uint32_t rank = cut[c];
+    for (uint32_t q = rank; q < end; ++q) rank += skey[q] < key ? 1u : 0u;
+    keys[out0 + rank] = key;
+    vals[out0 + rank] = lo64(pay);
+    if (stamps) stamps[out0 + rank] = hi64(pay);
   }
 }
 
-// The radix sort's input: the keys with their entries' positions, and the AND/OR words.
-__global__ __launch_bounds__(kThreads) void export_unpack_kernel(uint64_t* counters, const Entry* entries, SortBuf sb) {
+// The radix sort's other input: the entries' numbers, and the AND/OR words.
+__global__ __launch_bounds__(kThreads) void export_unpack_kernel(uint64_t* counters, SortBuf sb) {
   const uint64_t n = counters[kWCollected];
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   uint64_t and_k = ~0ull, or_k = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint64_t k = entries[i].key;
-    sb.lo[i] = k;
+    const uint64_t k = sb.lo[i];
     sb.idx[i] = (uint32_t)i;
     and_k &= k;
     or_k |= k;
@@ -1012,23 +1514,20 @@ __global__ __launch_bounds__(kThreads) void export_unpack_kernel(uint64_t* count
     and_k &= shfl_xor64(and_k, o);
     or_k |= shfl_xor64(or_k, o);
   }
-  if ((threadIdx.x & 63) == 0 && (and_k != ~0ull || or_k != 0)) {
-    atomicAnd(ull(&counters[kWBits + 0]), (unsigned long long)and_k);
-    atomicOr(ull(&counters[kWBits + 1]), (unsigned long long)or_k);
-  }
+  if ((threadIdx.x & 63) == 0) fold_bits(counters + kWBits, and_k, or_k);
 }
 
-__global__ __launch_bounds__(kThreads) void export_sorted_kernel(const uint64_t* counters, const Entry* entries,
-                                                                 SortBuf a, SortBuf b, uint64_t* keys, uint64_t* vals,
+__global__ __launch_bounds__(kThreads) void export_sorted_kernel(const uint64_t* counters, const uint4* xpay, SortBuf a,
+                                                                 SortBuf b, uint64_t* keys, uint64_t* vals,
                                                                  uint64_t* stamps) {
   const uint64_t n = counters[kWCollected];
   const SortBuf sorted = sort_result(a, b, counters + kWBits, 1);
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const Entry* e = &entries[sorted.idx[i]];
+    const uint4 pay = xpay[sorted.idx[i]];
     keys[i] = sorted.lo[i];
-    vals[i] = e->val;
-    if (stamps) stamps[i] = e->stamp;
+    vals[i] = lo64(pay);
+    if (stamps) stamps[i] = hi64(pay);
   }
 }
 
@@ -1109,25 +1608,33 @@ extern "C" gleam_status gleam_cache_evict(gleam_cache* c, uint64_t keep, uint64_
   uint64_t* counters = ws_at<uint64_t>(d_ws, L.counters);
   uint32_t* pick = ws_at<uint32_t>(d_ws, L.pick);
   uint32_t* leaders = ws_at<uint32_t>(d_ws, L.leaders);
+  uint64_t* occupied = ws_at<uint64_t>(d_ws, L.occupied);
   const SortBuf sa{ws_at<uint64_t>(d_ws, L.hi), ws_at<uint64_t>(d_ws, L.lo), ws_at<uint32_t>(d_ws, L.idx)};
   const SortBuf sb = sort_other(ws_at<uint8_t>(d_ws, L.sort2), L.m, 2);
-  hipLaunchKernelGGL(maint_init_kernel<true>, dim3(1), dim3(kInitThreads), 0, s, t, keep, kPickBins, counters, pick);
+  hipLaunchKernelGGL(maint_init_kernel<true>, dim3(1), dim3(kInitThreads), 0, s, t, keep, counters, pick);
   if ((st = launch_status("maint_init_kernel")) != GLEAM_OK) return st;
-  const uint64_t pick_want = (c->capacity + kPickThreads * kPickItems - 1) / (kPickThreads * kPickItems);
-  hipLaunchKernelGGL(evict_pick_kernel, dim3((uint32_t)(pick_want < kPickGrid ? pick_want : kPickGrid)),
-                     dim3(kPickThreads), 0, s, t, counters, pick);
-  if ((st = launch_status("evict_pick_kernel")) != GLEAM_OK) return st;
-  const uint64_t tiles = (L.m + kGatherTile - 1) / kGatherTile;
-  hipLaunchKernelGGL(evict_collect_kernel, dim3((uint32_t)(tiles < kGatherMaxGrid ? tiles : kGatherMaxGrid)),
-                     dim3(kThreads), 0, s, t, pick, counters, sa, tiles);
+  const uint64_t collect_want = (c->capacity + kCollectTile * kCollectWaves - 1) / (kCollectTile * kCollectWaves);
+  const dim3 collect_grid((uint32_t)(collect_want < kCollectGrid ? collect_want : kCollectGrid));
+  hipLaunchKernelGGL(evict_collect_kernel<false>, collect_grid, dim3(kThreads), 0, s, t, pick, counters, sa,
+                     occupied);
   if ((st = launch_status("evict_collect_kernel")) != GLEAM_OK) return st;
+  if (c->capacity > kSamples) {  // below, the samples are the whole table (but for the side slot, see there)
+    const uint64_t pick_want = (c->capacity + kPickThreads * kPickItems - 1) / (kPickThreads * kPickItems);
+    hipLaunchKernelGGL(evict_pick_kernel, dim3((uint32_t)(pick_want < kPickGrid ? pick_want : kPickGrid)),
+                       dim3(kPickThreads), 0, s, t, counters, pick);
+    if ((st = launch_status("evict_pick_kernel")) != GLEAM_OK) return st;
+    hipLaunchKernelGGL(evict_collect_kernel<true>, collect_grid, dim3(kThreads), 0, s, t, pick, counters, sa,
+                     occupied);
+    if ((st = launch_status("evict_collect_kernel")) != GLEAM_OK) return st;
+  }
   st = radix_sort_pairs(sa, counters + kWCollected, counters + kWBits, L.m, 2, ws_at<uint8_t>(d_ws, L.sort2), s);
   if (st != GLEAM_OK) return st;
   const uint32_t grid = grid_for(L.m) < 2048 ? grid_for(L.m) : 2048;
   hipLaunchKernelGGL(evict_mark_kernel, dim3(grid), dim3(kThreads), 0, s, t, sa, sb, counters, leaders, d_evicted,
                      d_counts);
   if ((st = launch_status("evict_mark_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(evict_repair_kernel, dim3(grid), dim3(kThreads), 0, s, t, sa, sb, counters, leaders);
+  hipLaunchKernelGGL(evict_repair_kernel, dim3(grid), dim3(kThreads), 0, s, t, sa, sb, counters, leaders,
+                     occupied);
   if ((st = launch_status("evict_repair_kernel")) != GLEAM_OK) return st;
   if (keep < c->key_bound) c->key_bound = keep;
   return GLEAM_OK;
@@ -1162,17 +1669,19 @@ extern "C" gleam_status gleam_cache_erase(gleam_cache* c, const uint64_t* d_keys
   hipStream_t s = (hipStream_t)stream;
   const EraseWs w = erase_ws(d_ws, L);
   const TableRef t = table_ref(c);
-  // header and both sets to zero (a fill kernel, so the call can be captured in a graph)
-  gleam_status st = fill_u64(w.hdr, (kHeaderBytes + 16 * L.cap) / 8, 0, s);
-  if (st != GLEAM_OK) return st;
   const dim3 block(kThreads);
+  hipLaunchKernelGGL(erase_clear_kernel, dim3(grid_for(L.cap)), block, 0, s, w);
+  gleam_status st = launch_status("erase_clear_kernel");
+  if (st != GLEAM_OK) return st;
   if (n > 0) {
-    hipLaunchKernelGGL(erase_find_kernel, dim3((uint32_t)((n + kThreads - 1) / kThreads)), block, 0, s, t, d_keys, n, w);
+    const uint64_t groups = (n + kThreads / kSpan - 1) / (kThreads / kSpan);
+    hipLaunchKernelGGL(erase_find_kernel, dim3((uint32_t)(groups < kFindGrid ? groups : kFindGrid)), block, 0, s, t,
+                       d_keys, n, w);
     if ((st = launch_status("erase_find_kernel")) != GLEAM_OK) return st;
   }
-  const uint64_t want = (n + kWaves - 1) / kWaves;  // at most one cluster per key, one wave each
-  hipLaunchKernelGGL(erase_repair_kernel, dim3((uint32_t)(want == 0 ? 1 : want < kMaxGrid ? want : kMaxGrid)), block, 0,
-                     s, t, d_keys, n, w, d_counts);
+  const uint64_t want = (n + kRepairWaves - 1) / kRepairWaves;  // at most one cluster per key, one wave each
+  hipLaunchKernelGGL(erase_repair_kernel, dim3((uint32_t)(want == 0 ? 1 : want < kRepairGrid ? want : kRepairGrid)),
+                     dim3(kRepairThreads), 0, s, t, n, w, d_counts);
   return launch_status("erase_repair_kernel");
 }
 
@@ -1193,32 +1702,36 @@ extern "C" gleam_status gleam_cache_export(const gleam_cache* c, uint64_t* d_key
   uint64_t* counters = ws_at<uint64_t>(d_ws, L.counters);
   uint32_t* share = ws_at<uint32_t>(d_ws, L.share);
   uint32_t* starts = ws_at<uint32_t>(d_ws, L.starts);
-  Entry* entries = ws_at<Entry>(d_ws, L.entries);
-  hipLaunchKernelGGL(maint_init_kernel<false>, dim3(1), dim3(kInitThreads), 0, s, t, 0, L.bins, counters,
-                     (uint32_t*)nullptr);
+  uint64_t* xkey = ws_at<uint64_t>(d_ws, L.xkey);
+  uint4* xpay = ws_at<uint4>(d_ws, L.xpay);
+  const uint32_t all = L.bins * L.parts;
+  hipLaunchKernelGGL(maint_init_kernel<false>, dim3(1), dim3(kInitThreads), 0, s, t, 0, counters, (uint32_t*)nullptr);
   if ((st = launch_status("maint_init_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_spread_kernel<false>, dim3(L.spread), dim3(kSpreadThreads), 0, s, t, counters, L.bins, share,
-                     starts, entries);
-  if ((st = launch_status("export_spread_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_share_kernel, dim3((L.bins + 63) / 64), dim3(64), 0, s, L.bins, L.spread, share, starts);
+  hipLaunchKernelGGL(export_count_kernel, dim3(L.spread), dim3(kSpreadThreads), 0, s, t, counters, all, share);
+  if ((st = launch_status("export_count_kernel")) != GLEAM_OK) return st;
+  hipLaunchKernelGGL(export_share_kernel, dim3((all + 63) / 64), dim3(64), 0, s, all, L.spread, share, starts);
   if ((st = launch_status("export_share_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_starts_kernel, dim3(1), dim3(kInitThreads), 0, s, L.bins, starts, counters, d_count);
+  hipLaunchKernelGGL(export_starts_kernel, dim3(1), dim3(kInitThreads), 0, s, L.bins, L.parts, starts, counters, d_count);
   if ((st = launch_status("export_starts_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_spread_kernel<true>, dim3(L.spread), dim3(kSpreadThreads), 0, s, t, counters, L.bins, share,
-                     starts, entries);
+  hipLaunchKernelGGL(export_spread_kernel, dim3(L.spread), dim3(kSpreadThreads), 0, s, t, counters, L.bins, L.parts,
+                     share, starts, xkey, xpay);
   if ((st = launch_status("export_spread_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_bin_kernel, dim3(L.bins), dim3(kBinThreads), 0, s, counters, L.bins, starts, entries, d_keys,
-                     d_vals, d_stamps);
-  if ((st = launch_status("export_bin_kernel")) != GLEAM_OK) return st;
-  if (c->capacity <= kBinMax) return GLEAM_OK;  // no bin can hold more
-  const SortBuf sa{nullptr, ws_at<uint64_t>(d_ws, L.xlo), ws_at<uint32_t>(d_ws, L.xidx)};
+  // (the shares are done with: their first words tell the parts left to the second launch)
+  hipLaunchKernelGGL(export_part_kernel<false>, dim3(all), dim3(kPartThreads), 0, s, counters, L.bins, L.parts, starts,
+                     xkey, xpay, share, d_keys, d_vals, d_stamps);
+  if ((st = launch_status("export_part_kernel")) != GLEAM_OK) return st;
+  hipLaunchKernelGGL(export_part_kernel<true>, dim3(all), dim3(kPartThreads), 0, s, counters, L.bins, L.parts, starts,
+                     xkey, xpay, share, d_keys, d_vals, d_stamps);
+  if ((st = launch_status("export_part_kernel")) != GLEAM_OK) return st;
+  if (c->capacity <= kPartMax) return GLEAM_OK;  // no part can hold more
+  const SortBuf sa{nullptr, xkey, ws_at<uint32_t>(d_ws, L.xidx)};
   const SortBuf sb = sort_other(ws_at<uint8_t>(d_ws, L.sort1), L.m, 1);
   const uint32_t grid = grid_for(L.m) < 1024 ? grid_for(L.m) : 1024;
-  hipLaunchKernelGGL(export_unpack_kernel, dim3(grid), dim3(kThreads), 0, s, counters, entries, sa);
+  hipLaunchKernelGGL(export_unpack_kernel, dim3(grid), dim3(kThreads), 0, s, counters, sa);
   if ((st = launch_status("export_unpack_kernel")) != GLEAM_OK) return st;
   st = radix_sort_pairs(sa, counters + kWCollected, counters + kWBits, L.m, 1, ws_at<uint8_t>(d_ws, L.sort1), s);
   if (st != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_sorted_kernel, dim3(grid), dim3(kThreads), 0, s, counters, entries, sa, sb, d_keys, d_vals,
+  hipLaunchKernelGGL(export_sorted_kernel, dim3(grid), dim3(kThreads), 0, s, counters, xpay, sa, sb, d_keys, d_vals,
                      d_stamps);
   return launch_status("export_sorted_kernel");
 }

@@ -375,3 +375,26 @@ def test_skewed_keys_and_stamps(log2_cap, shape):
         assert u64(counts).tolist() == [want.size, len(ot)], keep
         assert np.array_equal(u64(ev)[:want.size], want), keep
         assert_table(table, ot, f"keep {keep}")
+
+
+def test_many_sort_tiles():
+    """2.5 M entries, more sort tiles than chunks (several tiles to a workgroup): the keys
+    in two tight ranges, so that export sorts them by digits too; most of them evicted."""
+    rng = np.random.default_rng(1012)
+    n = 2_500_000
+    keys = rng.permutation(np.concatenate([np.arange(n // 2), np.arange(n - n // 2) + (1 << 50)])).astype(np.uint64)
+    vals = rng.integers(0, 2**64, n, dtype=np.uint64, endpoint=False)
+    table, ot = g.Cache(1 << 22, max_load=0.65), oracle.Table()
+    say("many sort tiles")
+    table.insert(keys_to_device(keys), keys_to_device(vals))
+    ot.insert(keys, vals)
+    ep = rng.integers(0, 1 << 40, n, dtype=np.uint64)
+    table.touch(keys_to_device(keys), epochs=keys_to_device(ep))
+    ot.touch(keys, ep)
+    assert_table(table, ot, "before")
+    for keep in (2_490_000, 100_000):
+        ev, counts = table.evict(keep)
+        want = ot.evict(keep)
+        assert u64(counts).tolist() == [want.size, len(ot)]
+        assert np.array_equal(u64(ev)[:want.size], want)
+        assert_table(table, ot, f"keep {keep}")
