@@ -19,21 +19,28 @@
 // memory (5 instead of 18 at 208k intervals), and end and bias sit side by side so the
 // final step is one 16-byte load and needs no start.
 //
-// An update never re-sorts the intervals it keeps (they are already in order):
-//   1. removal ranges are sorted by start, with a running maximum of their last
-//      addresses, so one binary search tells whether an interval meets any of them;
-//      the survivors are compacted, in order, into the workspace (one scan);
-//   2. only the valid additions are sorted (the library's radix sort, radix_sort.h;
-//      invalid ones take the key kNone and sort last);
-//   3. an addition meets an earlier-starting addition iff the running maximum of ends
-//      just before it passes its start, a later-starting one iff the next start comes
-//      before its end, and a survivor iff the last survivor starting at or before its
-//      last address ends after its start (survivors are disjoint, so their ends are
-//      sorted too); additions that meet nothing are kept (a scan numbers them);
-//   4. the two sorted runs are merged by rank: a survivor lands at its own index plus
-//      the kept additions that start before it, a kept addition at its own number plus
-//      the survivors that start before it. Nothing is written unless everything fits
-//      the capacity, so a refused call changes nothing.
+// An update never re-sorts the intervals it keeps (they are already in order). It is bound
+// by its launches and their chains of dependent reads, so it takes four:
+//   1. the removals and the additions are sorted by start in chunks of 2,048, a workgroup
+//      per chunk in LDS, each with the running maximum of its ends (more than 16 chunks:
+//      one chunk of everything, by the library's radix sort, radix_sort.h; invalid
+//      additions take the key kNone and sort last);
+//   2. an interval meets a removal of a chunk iff the furthest end among those that start
+//      at or before its last address reaches its start: a wave narrows each chunk to its
+//      64 intervals first and nearly always finds none. Every interval gets a keep bit and
+//      is copied to the workspace; tiles of 1,024 count their survivors;
+//   3. an addition meets another one by the same rule over the chunks of additions, and a
+//      survivor iff there are survivors (a difference of ranks) among the intervals from
+//      the first that ends after its start to the last that starts before its end.
+//      Additions that meet nothing are kept and numbered within their chunk;
+//   4. the sorted runs are merged by rank: a survivor lands at its own rank plus the kept
+//      additions that start before it, a kept addition at its number among all kept ones
+//      plus the survivors before it. Nothing is written unless everything fits the
+//      capacity, so a refused call changes nothing.
+// 209 k intervals, one task's tensors (161 to 2,000) out and another's in: 28 us of kernels,
+// against 93 us for eleven launches with bitonic sorts (up to 41 us of them for 2,000
+// additions) and a scan and a compaction of their own; 8,000 out and in 64 us a call in
+// address order and 120 in any order, against 258 through the radix sorts.
 
 #include <new>
 
@@ -68,13 +75,32 @@ MapRef map_ref(const gleam_remap* m) {
   return MapRef{hdr, start, et, reinterpret_cast<uint64_t*>(et + m->capacity), m->capacity};
 }
 
+// Chunks of the sorted removals and additions, and tiles of the intervals.
+constexpr int kSmallThreads = 1024;
+constexpr uint32_t kSmall = 2 * kSmallThreads;
+// Up to 16 chunks: 32,768 of each. A batch in no order makes every wave search every chunk:
+// 32,000 out and in take 252 us so (80 in address order), through the radix sorts 305 before
+// the update took four launches and about 200 with them.
+constexpr uint64_t kMaxChunked = 16ull * kSmall;
+constexpr int kTileThreads = 1024;
+constexpr uint64_t kTile = kTileThreads;
+constexpr uint64_t kTileWords = kTile / 64;
+// Tile counts that a workgroup scans in LDS on its way (4 M intervals); more take a launch.
+constexpr uint32_t kLdsTiles = 4096;
+
+uint64_t chunk_of(uint64_t n) { return n <= kMaxChunked ? kSmall : n; }
+
 // Workspace of one update (cap = capacity, A = additions, R = removal ranges).
 struct UpdLayout {
-  size_t hdr;                                // [0] R, [1] A (the sorts' counts); [4..7] R's key bits, [8..11] A's
-  size_t keep, kpos, s_start, s_et;         // cap: survivor flag, its scan, compacted survivors
-  size_t ka, aidx, kb, vb, aend, amax, acc, apos;  // A: sort keys/indices, sorted keys/indices, ends, running max, kept flag, scan
-  size_t rka, ridx, rkb, rvb, rmax;         // R: sort keys/indices, sorted starts, their last addresses, running max
-  size_t sort, partial, total;              // the sort's second buffer and counts; the scans' tile totals
+  uint64_t tiles;
+  size_t hdr;                            // [0] R, [1] A (the sorts' counts); [4..7] R's key bits, [8..11] A's; [12] intervals before
+  size_t keep, wpre, tcount, tbase;      // cap: keep bits, survivors of the tile before each word; tile counts, their scan
+  size_t s_start, s_et;                  // cap: the intervals as they were
+  size_t kb, vb, aend, amax, acc, apos, srank;  // A: sorted keys/indices, ends, running max, kept flag, number, survivors before
+  size_t rkb, rmax;                      // R: sorted starts, running max of last addresses
+  size_t partial;                        // the scans' tile totals
+  size_t ka, aidx, rka, ridx, last, sort;  // past kMaxChunked: the radix sorts' buffers
+  size_t total;
 };
 
 UpdLayout upd_layout(uint64_t cap, uint64_t n_add, uint64_t n_del) {
@@ -85,28 +111,35 @@ UpdLayout upd_layout(uint64_t cap, uint64_t n_add, uint64_t n_del) {
     off = (off + bytes + 255) & ~(size_t)255;
     return o;
   };
+  L.tiles = (cap + kTile - 1) / kTile;
   L.hdr = take(256);
-  L.keep = take(8 * cap);
-  L.kpos = take(8 * cap);
+  L.keep = take(8 * L.tiles * kTileWords);
+  L.wpre = take(4 * L.tiles * kTileWords);
+  L.tcount = take(8 * (L.tiles + 1));
+  L.tbase = take(8 * (L.tiles + 1));
   L.s_start = take(8 * cap);
   L.s_et = take(16 * cap);
-  L.ka = take(8 * sort_capacity(n_add));
-  L.aidx = take(4 * sort_capacity(n_add));
   L.kb = take(8 * n_add);
   L.vb = take(8 * n_add);
   L.aend = take(8 * n_add);
   L.amax = take(8 * n_add);
   L.acc = take(8 * n_add);
   L.apos = take(8 * n_add);
-  L.rka = take(8 * sort_capacity(n_del));
-  L.ridx = take(4 * sort_capacity(n_del));
+  L.srank = take(8 * n_add);
   L.rkb = take(8 * n_del);
-  L.rvb = take(8 * n_del);
   L.rmax = take(8 * n_del);
-  const uint64_t ar = n_add > n_del ? n_add : n_del;
-  const uint64_t most = cap > ar ? cap : ar;
-  L.sort = take(sort_layout(ar, 1).total);
-  L.partial = take(8 * scan_tiles(most));
+  const uint64_t ra = n_add > kMaxChunked ? n_add : 0, rd = n_del > kMaxChunked ? n_del : 0;
+  const uint64_t most = ra > rd ? ra : rd;
+  L.partial = take(8 * scan_tiles(most > L.tiles + 1 ? most : L.tiles + 1));
+  L.ka = L.aidx = L.rka = L.ridx = L.last = L.sort = off;
+  if (most) {
+    L.ka = take(8 * sort_capacity(ra));
+    L.aidx = take(4 * sort_capacity(ra));
+    L.rka = take(8 * sort_capacity(rd));
+    L.ridx = take(4 * sort_capacity(rd));
+    L.last = take(8 * rd);
+    L.sort = take(sort_layout(most, 1).total);
+  }
   L.total = off;
   return L;
 }
@@ -123,31 +156,44 @@ uint32_t fold_grid(uint64_t n) {
   return g < 256 ? g : 256;
 }
 
-// Number of entries of the ascending keys[0, n) that are <= x (upper bound).
-__device__ __forceinline__ uint64_t count_le(const uint64_t* keys, uint64_t n, uint64_t x) {
-  uint64_t lo = 0, hi = n;
+// Entries of the ascending keys[lo, hi) that are <= x (kLe) or < x, plus lo.
+template <bool kLe>
+__device__ __forceinline__ uint64_t count_below(const uint64_t* keys, uint64_t lo, uint64_t hi, uint64_t x) {
   while (lo < hi) {
     const uint64_t mid = lo + ((hi - lo) >> 1);
-    if (keys[mid] <= x) lo = mid + 1;
+    const uint64_t k = keys[mid];
+    if (kLe ? k <= x : k < x) lo = mid + 1;
     else hi = mid;
   }
   return lo;
 }
 
-// Number of entries of the ascending keys[0, n) that are < x (lower bound).
-__device__ __forceinline__ uint64_t count_lt(const uint64_t* keys, uint64_t n, uint64_t x) {
+// The same over keys[0, n) for an x that is the same in every lane, by the whole wave: 64
+// pivots a round, so 2,048 entries take two dependent reads. Every lane calls it.
+template <bool kLe>
+__device__ __forceinline__ uint64_t wave_count_below(const uint64_t* keys, uint64_t n, uint64_t x, int lane) {
   uint64_t lo = 0, hi = n;
-  while (lo < hi) {
-    const uint64_t mid = lo + ((hi - lo) >> 1);
-    if (keys[mid] < x) lo = mid + 1;
-    else hi = mid;
+  while (hi - lo > 64) {
+    const uint64_t step = (hi - lo + 63) / 64, idx = lo + (uint64_t)lane * step;
+    const uint64_t k = keys[idx < hi ? idx : hi - 1];
+    const uint64_t c = (uint64_t)__popcll(__ballot(idx < hi && (kLe ? k <= x : k < x)));
+    if (c == 0) return lo;
+    hi = min(lo + c * step, hi);
+    lo += (c - 1) * step + 1;
   }
-  return lo;
+  if (lo == hi) return lo;
+  const uint64_t idx = lo + (uint64_t)lane;
+  const uint64_t k = keys[idx < hi ? idx : hi - 1];
+  return lo + (uint64_t)__popcll(__ballot(idx < hi && (kLe ? k <= x : k < x)));
 }
 
-// Removal ranges as sort key = first address, value = last address (clipped at 2^64 - 1);
-// an empty range takes the key kNone and is never found.
-// Counts of the two sorts and the AND/OR words of their keys (see radix_sort.h).
+__device__ __forceinline__ uint64_t uniform64(uint64_t x, int lane) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Batches past kMaxChunked. Counts of the two sorts and the AND/OR words of their keys (see radix_sort.h).
 __global__ void update_init_kernel(uint64_t* hdr, uint64_t r, uint64_t n_add) {
   const int t = threadIdx.x;
   if (t < 12) hdr[t] = t == 0 ? r : t == 1 ? n_add : (t == 4 || t == 8) ? ~0ull : 0ull;
@@ -208,32 +254,6 @@ __global__ void removal_unpack_kernel(SortBuf a, SortBuf b, const uint64_t* bits
   }
 }
 
-// keep[p] = 1 for an interval that meets no removal range.
-__global__ void survive_kernel(MapRef map, const uint64_t* rkey, const uint64_t* rmax, uint64_t r, uint64_t* keep) {
-  const uint64_t count = map.hdr[0];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < map.cap; p += stride) {
-    uint64_t k = 0;
-    if (p < count) {
-      const uint64_t s = map.start[p], last = map.et[p].x - 1;
-      // the removals starting at or before `last`: does the furthest of them reach s?
-      const uint64_t q = r ? count_le(rkey, r, last) : 0;
-      k = (q && rmax[q - 1] >= s) ? 0 : 1;
-    }
-    keep[p] = k;
-  }
-}
-
-__global__ void compact_kernel(MapRef map, const uint64_t* keep, const uint64_t* kpos, uint64_t* s_start,
-                               ulonglong2* s_et) {
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < map.cap; p += stride) {
-    if (!keep[p]) continue;
-    s_start[kpos[p]] = map.start[p];
-    s_et[kpos[p]] = map.et[p];
-  }
-}
-
 // Sort key of addition j: its start if valid, else kNone (status INVALID).
 __global__ __launch_bounds__(kThreads) void addition_prep_kernel(const uint64_t* a_start, const uint64_t* a_len,
                                                                  const uint64_t* a_target, uint64_t n_add,
@@ -270,255 +290,460 @@ __global__ void addition_unpack_kernel(SortBuf a, SortBuf b, const uint64_t* bit
   }
 }
 
-// Keep a valid addition that meets no other valid addition and no survivor.
-__global__ void addition_classify_kernel(const uint64_t* key, const uint64_t* val, const uint64_t* aend,
-                                         const uint64_t* amax, uint64_t n_add, const uint64_t* s_start,
-                                         const ulonglong2* s_et, const uint64_t* keep, const uint64_t* kpos,
-                                         uint64_t cap, uint8_t* status, uint64_t* acc) {
-  const uint64_t n_surv = kpos[cap - 1] + keep[cap - 1];
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n_add; k += stride) {
-    const uint64_t s = key[k];
-    uint64_t a = 0;
-    if (s != kNone) {
-      const uint64_t e = aend[k];
-      bool clash = (k > 0 && amax[k - 1] > s) || (k + 1 < n_add && key[k + 1] < e);
-      if (!clash) {
-        const uint64_t q = count_le(s_start, n_surv, e - 1);
-        clash = q && s_et[q - 1].x > s;
-      }
-      a = clash ? 0 : 1;
-      if (status) status[val[k]] = clash ? GLEAM_REMAP_OVERLAP : GLEAM_REMAP_ADDED;
-    }
-    acc[k] = a;
+// ---- chunks sorted in LDS ---------------------------------------------------------------
+struct ChunkLds {
+  uint64_t key[2][kSmall];
+  uint64_t val[kSmall];  // by original place: a removal's last address, an addition's length
+  uint32_t idx[2][kSmall];
+  uint64_t wave[kSmallThreads / 64];
+};
+
+// Sorts (key[0][i], idx[0][i] = i), i < n <= kSmall, by key, stably; returns the buffer that
+// holds the result. Batches usually come in address order (a task's tensors as they were
+// packed), which one pass sees. Else each wave sorts two runs of 64 in registers, and pairs
+// of sorted runs are merged by rank: each entry finds its place in the other run by a
+// binary search, one barrier per doubling. Every thread of the workgroup calls it.
+__device__ int sort_chunk(ChunkLds& L, uint32_t n) {
+  const uint32_t t = threadIdx.x;
+  const int lane = t & 63;
+  bool bad = false;
+  for (uint32_t i = t; i + 1 < n; i += kSmallThreads) bad |= L.key[0][i] > L.key[0][i + 1];
+  if (!__syncthreads_or(bad)) return 0;
+  const uint32_t i0 = (t / 64) * 128 + lane;
+  uint64_t k[2];
+  uint32_t id[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {  // places past n sort after every entry: kNone, and the higher index
+    id[h] = i0 + 64 * h;
+    k[h] = id[h] < n ? L.key[0][id[h]] : kNone;
   }
-}
-
-// Batches of at most kSmall removals or additions (a task's allocations, its tensors) are
-// handled by one 1024-lane workgroup in LDS instead of the several launches of the
-// device-wide sort and scans: a bitonic sort of (key, index) pairs and Hillis-Steele
-// scans over at most 2048 entries.
-constexpr int kSmallThreads = 1024;
-constexpr uint32_t kSmall = 2 * kSmallThreads;
-
-__device__ __forceinline__ uint32_t pow2_at_least(uint32_t n) {  // n <= kSmall
-  uint32_t p = 1;
-  while (p < n) p <<= 1;
-  return p;
-}
-
-// Sort the pairs (key[i], idx[i]), i < n, ascending by key and then by idx. The indices
-// are distinct, so this is a total order and the result is what a stable sort by key
-// gives. n is a power of two <= kSmall; every lane of the workgroup calls it.
-__device__ void bitonic_sort(uint64_t* key, uint32_t* idx, uint32_t n) {
-  for (uint32_t k = 2; k <= n; k <<= 1) {
-    for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-      const uint32_t t = threadIdx.x;  // pair t of n / 2 <= kSmallThreads
-      if (t < n / 2) {
-        const uint32_t i = ((t & ~(j - 1)) << 1) | (t & (j - 1));  // bit j of i is clear
-        const uint32_t l = i | j;
-        const uint64_t ki = key[i], kl = key[l];
-        const uint32_t ii = idx[i], il = idx[l];
-        const bool greater = ki > kl || (ki == kl && ii > il);
-        if (greater == ((i & k) == 0)) {  // out of order for this run's direction
-          key[i] = kl;
-          key[l] = ki;
-          idx[i] = il;
-          idx[l] = ii;
+#pragma unroll
+  for (int size = 2; size <= 64; size <<= 1) {
+#pragma unroll
+    for (int d = size >> 1; d > 0; d >>= 1) {
+      const bool low = (lane & d) == 0, up = (lane & size) == 0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint64_t ok = shfl_xor64(k[h], d);
+        const uint32_t oi = (uint32_t)__shfl_xor((int)id[h], d, 64);
+        const bool less = ok < k[h] || (ok == k[h] && oi < id[h]);  // the other one comes first
+        if (less == (low == up)) {
+          k[h] = ok;
+          id[h] = oi;
         }
       }
-      __syncthreads();
     }
   }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (i0 + 64 * h < n) {
+      L.key[0][i0 + 64 * h] = k[h];
+      L.idx[0][i0 + 64 * h] = id[h];
+    }
+  }
+  __syncthreads();
+  int b = 0;
+  for (uint32_t run = 64; run < n; run *= 2, b ^= 1) {
+    for (uint32_t i = t; i < n; i += kSmallThreads) {
+      const uint32_t r = i / run, left = (r & ~1u) * run, other = (r ^ 1) * run;
+      const uint64_t x = L.key[b][i];
+      const uint32_t end = min(other + run, n);
+      uint32_t c = 0;
+      if (other < end)
+        c = (uint32_t)((r & 1) ? count_below<true>(L.key[b], other, end, x) : count_below<false>(L.key[b], other, end, x)) - other;
+      const uint32_t to = left + (i - r * run) + c;
+      L.key[b ^ 1][to] = x;
+      L.idx[b ^ 1][to] = L.idx[b][i];
+    }
+    __syncthreads();
+  }
+  return b;
 }
 
-// In-place inclusive scan of buf[0, n) (n <= kSmall) with `op`; every lane of the
-// workgroup calls it; lane t owns entries t and t + kSmallThreads.
+// Inclusive scan over the workgroup of two consecutive values per thread. Every thread
+// calls it; `wave` is kSmallThreads / 64 words of LDS.
 template <class Op>
-__device__ void block_scan(uint64_t* buf, uint32_t n, Op op) {
-  const uint32_t i0 = threadIdx.x, i1 = threadIdx.x + kSmallThreads;
-  for (uint32_t off = 1; off < n; off <<= 1) {
-    uint64_t v0 = 0, v1 = 0;
-    if (i0 < n) v0 = i0 >= off ? op(buf[i0 - off], buf[i0]) : buf[i0];
-    if (i1 < n) v1 = i1 >= off ? op(buf[i1 - off], buf[i1]) : buf[i1];
-    __syncthreads();
-    if (i0 < n) buf[i0] = v0;
-    if (i1 < n) buf[i1] = v1;
-    __syncthreads();
+__device__ __forceinline__ void scan_pairs(uint64_t* v, Op op, uint64_t* wave) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint64_t incl = op(v[0], v[1]);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t y = shfl_up64(incl, d);
+    if (lane >= d) incl = op(y, incl);
   }
+  __syncthreads();  // `wave` of an earlier scan read by every thread
+  if (lane == 63) wave[w] = incl;
+  __syncthreads();
+  uint64_t before = 0;
+  for (int x = 0; x < w; ++x) before = op(before, wave[x]);
+  const uint64_t prev = shfl_up64(incl, 1);
+  if (lane) before = op(before, prev);
+  v[0] = op(before, v[0]);
+  v[1] = op(v[0], v[1]);
 }
 
-struct MaxOp {
-  __device__ uint64_t operator()(uint64_t a, uint64_t b) const { return a > b ? a : b; }
+struct Batches {  // the arguments of one update
+  const uint64_t *r_start, *r_len, *a_start, *a_len, *a_target;
+  uint64_t n_del, n_add;
+  uint8_t* status;
 };
-struct AddOp {
-  __device__ uint64_t operator()(uint64_t a, uint64_t b) const { return a + b; }
+struct Removals {  // sorted, in chunks of `chunk`
+  uint64_t *key, *max;
+  uint64_t n, chunk;
+};
+struct Additions {  // sorted, in chunks of `chunk`
+  uint64_t *key, *idx, *end, *max, *acc, *pos, *srank;
+  uint64_t n, chunk;
 };
 
-// Removal ranges sorted by start, with the running maximum of their last addresses
-// (what the radix sort and the scan produce for larger batches).
-__global__ void __launch_bounds__(kSmallThreads)
-removals_small_kernel(const uint64_t* d_start, const uint64_t* d_len, uint32_t r, uint64_t* rkey, uint64_t* rmax) {
-  __shared__ uint64_t key[kSmall], last[kSmall], buf[kSmall];
-  __shared__ uint32_t idx[kSmall];
-  const uint32_t n = pow2_at_least(r);
+// One workgroup per chunk: `r_chunks` of the removals, then those of the additions.
+__global__ __launch_bounds__(kSmallThreads) void sort_chunks_kernel(Batches in, Removals R, Additions A,
+                                                                    uint32_t r_chunks) {
+  __shared__ ChunkLds L;
+  const bool removals = blockIdx.x < r_chunks;
+  const uint64_t first = (uint64_t)(removals ? blockIdx.x : blockIdx.x - r_chunks) * kSmall;
+  const uint32_t n = (uint32_t)min((removals ? in.n_del : in.n_add) - first, (uint64_t)kSmall);
   for (uint32_t i = threadIdx.x; i < n; i += kSmallThreads) {
-    uint64_t k = kNone, l = 0;  // padding sorts after every range
-    if (i < r) {
-      const uint64_t s = d_start[i], len = d_len[i];
+    uint64_t k, v;
+    if (removals) {
+      const uint64_t s = in.r_start[first + i], len = in.r_len[first + i];
       k = len ? s : kNone;
-      l = len ? (len - 1 > kNone - s ? kNone : s + len - 1) : 0;
+      v = len ? (len - 1 > kNone - s ? kNone : s + len - 1) : 0;
+    } else {
+      const uint64_t s = in.a_start[first + i], len = in.a_len[first + i], to = in.a_target[first + i];
+      const bool valid = len != 0 && len <= kNone - s && len <= kNone - to;
+      if (!valid && in.status) in.status[first + i] = GLEAM_REMAP_INVALID;
+      k = valid ? s : kNone;
+      v = valid ? len : 0;
     }
-    key[i] = k;
-    last[i] = l;
-    idx[i] = i;
+    L.key[0][i] = k;
+    L.idx[0][i] = i;
+    L.val[i] = v;
   }
   __syncthreads();
-  bitonic_sort(key, idx, n);
-  for (uint32_t i = threadIdx.x; i < r; i += kSmallThreads) {
-    rkey[i] = key[i];
-    buf[i] = last[idx[i]];
+  const int b = sort_chunk(L, n);
+  uint64_t e[2], m[2], k[2];
+  uint32_t id[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t i = 2 * threadIdx.x + h;
+    k[h] = i < n ? L.key[b][i] : kNone;
+    id[h] = i < n ? L.idx[b][i] : 0;
+    e[h] = i < n ? L.val[id[h]] : 0;
+    if (!removals && k[h] != kNone) e[h] += k[h];  // an invalid addition ends at 0
+    m[h] = e[h];
   }
-  __syncthreads();
-  block_scan(buf, r, MaxOp());
-  for (uint32_t i = threadIdx.x; i < r; i += kSmallThreads) rmax[i] = buf[i];
-}
-
-// Additions sorted, checked against each other and the survivors, and numbered: the
-// same outputs (kb, vb, aend, acc, apos) and statuses as the batched path.
-__global__ void __launch_bounds__(kSmallThreads)
-additions_small_kernel(const uint64_t* a_start, const uint64_t* a_len, const uint64_t* a_target, uint32_t n_add,
-                       uint8_t* status, const uint64_t* s_start, const ulonglong2* s_et, const uint64_t* keep,
-                       const uint64_t* kpos, uint64_t cap, uint64_t* kb, uint64_t* vb, uint64_t* aend,
-                       uint64_t* acc, uint64_t* apos) {
-  __shared__ uint64_t key[kSmall], buf[kSmall];
-  __shared__ uint32_t idx[kSmall];
-  const uint64_t n_surv = kpos[cap - 1] + keep[cap - 1];
-  const uint32_t n = pow2_at_least(n_add);
-  for (uint32_t j = threadIdx.x; j < n; j += kSmallThreads) {
-    uint64_t k = kNone;  // invalid additions and padding sort last (padding after them)
-    if (j < n_add) {
-      const uint64_t s = a_start[j], len = a_len[j], t = a_target[j];
-      const bool valid = len != 0 && len <= kNone - s && len <= kNone - t;
-      if (!valid && status) status[j] = GLEAM_REMAP_INVALID;
-      if (valid) k = s;
+  scan_pairs(m, ScanMax(), L.wave);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t i = 2 * threadIdx.x + h;
+    if (i >= n) continue;
+    if (removals) {
+      R.key[first + i] = k[h];
+      R.max[first + i] = m[h];
+    } else {
+      A.key[first + i] = k[h];
+      A.idx[first + i] = first + id[h];
+      A.end[first + i] = e[h];
+      A.max[first + i] = m[h];
     }
-    key[j] = k;
-    idx[j] = j;
-  }
-  __syncthreads();
-  bitonic_sort(key, idx, n);
-  uint64_t e[2] = {0, 0};
-  for (uint32_t h = 0; h < 2; ++h) {
-    const uint32_t k = threadIdx.x + h * kSmallThreads;
-    if (k >= n_add) continue;
-    e[h] = key[k] == kNone ? 0 : key[k] + a_len[idx[k]];
-    kb[k] = key[k];
-    vb[k] = idx[k];
-    aend[k] = e[h];
-    buf[k] = e[h];
-  }
-  __syncthreads();
-  block_scan(buf, n_add, MaxOp());  // buf[k] = running maximum of ends through k
-  uint64_t a[2] = {0, 0};
-  for (uint32_t h = 0; h < 2; ++h) {
-    const uint32_t k = threadIdx.x + h * kSmallThreads;
-    if (k >= n_add || key[k] == kNone) continue;
-    const uint64_t s = key[k];
-    bool clash = (k > 0 && buf[k - 1] > s) || (k + 1 < n_add && key[k + 1] < e[h]);
-    if (!clash) {
-      const uint64_t q = count_le(s_start, n_surv, e[h] - 1);
-      clash = q && s_et[q - 1].x > s;
-    }
-    a[h] = clash ? 0 : 1;
-    if (status) status[idx[k]] = clash ? GLEAM_REMAP_OVERLAP : GLEAM_REMAP_ADDED;
-  }
-  __syncthreads();  // every lane has read buf
-  for (uint32_t h = 0; h < 2; ++h) {
-    const uint32_t k = threadIdx.x + h * kSmallThreads;
-    if (k < n_add) {
-      acc[k] = a[h];
-      buf[k] = a[h];
-    }
-  }
-  __syncthreads();
-  block_scan(buf, n_add, AddOp());  // inclusive count of kept additions
-  for (uint32_t h = 0; h < 2; ++h) {
-    const uint32_t k = threadIdx.x + h * kSmallThreads;
-    if (k < n_add) apos[k] = buf[k] - a[h];
   }
 }
 
-struct Totals {
-  uint64_t n_surv, n_acc, total, S;
-  bool fits;
+// ---- survivors --------------------------------------------------------------------------
+struct Kept {            // the intervals as they were, and which of them stay
+  uint64_t* count;       // [0]
+  uint64_t* word;        // keep bits
+  uint32_t* wpre;        // survivors of the word's tile before the word
+  uint64_t* tcount;      // survivors of each tile
+  uint64_t* tbase;       // and their exclusive scan, with the total after the last
+  uint64_t* start;
+  ulonglong2* et;
 };
 
-__device__ __forceinline__ Totals totals(const uint64_t* keep, const uint64_t* kpos, uint64_t cap,
-                                         const uint64_t* acc, const uint64_t* apos, uint64_t n_add) {
-  Totals t;
-  t.n_surv = kpos[cap - 1] + keep[cap - 1];
-  t.n_acc = n_add ? apos[n_add - 1] + acc[n_add - 1] : 0;
-  t.total = t.n_surv + t.n_acc;
-  t.fits = t.total <= cap;
-  t.S = t.total > kFence ? (t.total + kFence - 1) / kFence : 1;
-  return t;
-}
-
-__device__ __forceinline__ void place(const MapRef& map, uint64_t q, uint64_t s, ulonglong2 et, uint64_t S) {
-  map.start[q] = s;
-  map.et[q] = et;
-  if (q % S == 0) map.fence[q / S] = s;
-}
-
-// Survivor i lands at i + (kept additions that start before it).
-__global__ void place_survivors_kernel(MapRef map, const uint64_t* s_start, const ulonglong2* s_et,
-                                       const uint64_t* keep, const uint64_t* kpos, const uint64_t* key,
-                                       const uint64_t* acc, const uint64_t* apos, uint64_t n_add) {
-  const Totals t = totals(keep, kpos, map.cap, acc, apos, n_add);
-  if (!t.fits) return;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < t.n_surv; i += stride) {
-    const uint64_t s = s_start[i];
-    const uint64_t k = count_lt(key, n_add, s);  // additions (any status) starting before s
-    const uint64_t before = k < n_add ? apos[k] : t.n_acc;
-    place(map, i + before, s, s_et[i], t.S);
-  }
-}
-
-// Kept addition k lands at its number among kept additions + (survivors that start
-// before it); when the result would not fit, it is FULL instead.
-__global__ void place_additions_kernel(MapRef map, const uint64_t* s_start, const uint64_t* keep,
-                                       const uint64_t* kpos, const uint64_t* key, const uint64_t* val,
-                                       const uint64_t* aend, const uint64_t* acc, const uint64_t* apos,
-                                       uint64_t n_add, const uint64_t* a_target, uint8_t* status) {
-  const Totals t = totals(keep, kpos, map.cap, acc, apos, n_add);
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n_add; k += stride) {
-    if (!acc[k]) continue;
-    if (t.fits) {
-      const uint64_t s = key[k];
-      place(map, apos[k] + count_lt(s_start, t.n_surv, s), s, make_ulonglong2(aend[k], a_target[val[k]] - s),
-            t.S);
-    } else if (status) {
-      status[val[k]] = GLEAM_REMAP_FULL;
+__global__ __launch_bounds__(kTileThreads) void survive_kernel(MapRef map, Removals R, Kept K) {
+  __shared__ uint32_t wcount[kTileWords];
+  const uint64_t count = map.hdr[0];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t p0 = (uint64_t)blockIdx.x * kTile + 64 * wave, p = p0 + lane;
+  if (blockIdx.x == 0 && threadIdx.x == 0) K.count[0] = count;
+  bool stay = p < count;
+  if (p0 < count) {  // the wave's intervals lie between `first` and `last`
+    const uint64_t at = stay ? p : count - 1;
+    const uint64_t s = map.start[at];
+    const ulonglong2 et = map.et[at];
+    const uint64_t first = uniform64(s, 0), last = uniform64(et.x, 63) - 1;
+    for (uint64_t c = 0; c < R.n; c += R.chunk) {
+      const uint64_t n = min(R.chunk, R.n - c);
+      const uint64_t *key = R.key + c, *max = R.max + c;
+      if (key[0] > last || max[n - 1] < first) continue;
+      const uint64_t hi = wave_count_below<true>(key, n, last, lane);
+      if (hi == 0 || max[hi - 1] < first) continue;
+      const uint64_t lo = wave_count_below<true>(key, hi, first, lane);
+      const uint64_t q = count_below<true>(key, lo, hi, et.x - 1);
+      if (q && max[q - 1] >= s) stay = false;
+    }
+    if (p < count) {
+      K.start[p] = s;
+      K.et[p] = et;
     }
   }
+  const uint64_t word = __ballot(stay);
+  if (lane == 0) wcount[wave] = (uint32_t)__popcll(word);
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+  for (int w = 0; w < (int)kTileWords; ++w) {
+    before += w < wave ? wcount[w] : 0;
+    total += wcount[w];
+  }
+  if (lane == 0) {
+    K.word[p0 / 64] = word;
+    K.wpre[p0 / 64] = before;
+  }
+  if (threadIdx.x == 0) {
+    K.tcount[blockIdx.x] = total;
+    if (blockIdx.x == gridDim.x - 1) K.tcount[gridDim.x] = 0;
+  }
 }
 
-// Header and counts, after both placements.
-__global__ void finish_kernel(MapRef map, const uint64_t* keep, const uint64_t* kpos, const uint64_t* acc,
-                              const uint64_t* apos, uint64_t n_add, uint64_t* counts) {
-  const Totals t = totals(keep, kpos, map.cap, acc, apos, n_add);
-  const uint64_t before = map.hdr[0];
-  counts[0] = t.fits ? t.total : before;
-  counts[1] = t.fits ? t.n_acc : 0;
-  counts[2] = t.fits ? before - t.n_surv : 0;
-  counts[3] = n_add - (t.fits ? t.n_acc : 0);
-  if (t.fits) {
-    map.hdr[0] = t.total;
-    map.hdr[1] = t.S;
-    map.hdr[2] = (t.total + t.S - 1) / t.S;
+// Survivors among the first i intervals; `base` the exclusive scan of the tile counts.
+template <class T>
+__device__ __forceinline__ uint64_t survivors_before(const Kept& K, const T* base, uint64_t i) {
+  const uint64_t b = base[i / kTile];
+  if (i % kTile == 0) return b;  // (i may be the end of the last tile)
+  const uint64_t w = K.word[i / 64];
+  return b + K.wpre[i / 64] + (uint64_t)__popcll(w & ((1ull << (i & 63)) - 1));
+}
+
+// ---- additions --------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t top_bit(uint32_t x) {  // largest power of two <= x (x >= 1)
+  return 1u << (31 - __builtin_clz(x));
+}
+
+// Does a valid addition [s, e), entry k of the chunk at c, meet another one of its chunk
+// (of one that starts before it, the furthest end; the next one's start)?
+__device__ __forceinline__ bool meets_own_chunk(const Additions& A, uint64_t c, uint64_t n, uint64_t k, uint64_t s,
+                                                uint64_t e) {
+  return (k > 0 && A.max[c + k - 1] > s) || (k + 1 < n && A.key[c + k + 1] < e);
+}
+
+// One workgroup per chunk of the additions (one also when there are none): which are kept,
+// their numbers within the chunk and the survivors before each. Without `scanned` the tile
+// counts are scanned here, by every workgroup for itself; the first one stores the scan.
+__global__ __launch_bounds__(kSmallThreads) void classify_chunks_kernel(Kept K, Additions A, Batches in,
+                                                                        uint32_t tiles, uint32_t scanned) {
+  __shared__ uint32_t base[kLdsTiles + 1];
+  __shared__ uint64_t wave[kSmallThreads / 64];
+  const uint32_t t = threadIdx.x;
+  const uint64_t c = (uint64_t)blockIdx.x * kSmall;
+  const uint32_t n = A.n ? (uint32_t)min(A.n - c, (uint64_t)kSmall) : 0;
+  uint64_t k[2], s[2], e[2], id[2];
+  bool valid[2], clash[2] = {false, false};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    k[h] = 2 * t + h;
+    const uint64_t at = c + (k[h] < n ? k[h] : 0);
+    s[h] = n ? A.key[at] : kNone;
+    e[h] = n ? A.end[at] : 0;
+    id[h] = n ? A.idx[at] : 0;
+    valid[h] = k[h] < n && s[h] != kNone;
+    if (valid[h]) clash[h] = meets_own_chunk(A, c, n, k[h], s[h], e[h]);
+  }
+  if (!scanned) {
+    static_assert(kLdsTiles == 4 * kSmallThreads, "four tiles per thread");
+    uint64_t v[4], pair[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = 4 * t + j < tiles ? K.tcount[4 * t + j] : 0;
+    pair[0] = v[0] + v[1];
+    pair[1] = v[2] + v[3];
+    scan_pairs(pair, ScanSum(), wave);
+    const uint64_t x[4] = {pair[0] - v[0] - v[1], pair[0] - v[1], pair[0], pair[1] - v[3]};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      base[4 * t + j] = (uint32_t)x[j];
+      if (blockIdx.x == 0 && 4 * t + j <= tiles) K.tbase[4 * t + j] = x[j];
+    }
+    if (t == kSmallThreads - 1) {  // the end of the last tile, where there are kLdsTiles of them
+      base[kLdsTiles] = (uint32_t)pair[1];
+      if (blockIdx.x == 0 && tiles == kLdsTiles) K.tbase[kLdsTiles] = pair[1];
+    }
+  }
+  if (n == 0) return;
+  // other chunks, four at a time so that their searches wait together
+  for (uint64_t c0 = 0; c0 < A.n; c0 += 4 * kSmall) {
+    const uint64_t* key[4];
+    uint32_t len[4], q[2][4];
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint64_t cj = c0 + j * kSmall;
+      len[j] = cj < A.n && cj != c ? (uint32_t)min(A.n - cj, (uint64_t)kSmall) : 0;
+      key[j] = A.key + (len[j] ? cj : 0);
+      q[0][j] = q[1][j] = 0;
+      // (sorted chunks: this one's entries lie between its first start and its furthest end)
+      if (len[j] && (key[j][0] >= A.max[c + n - 1] || A.max[cj + len[j] - 1] <= A.key[c])) len[j] = 0;
+      any |= len[j] != 0;
+    }
+    if (!any) continue;
+    for (uint32_t step = kSmall; step; step >>= 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (q[h][j] + step <= len[j] && key[j][q[h][j] + step - 1] < e[h]) q[h][j] += step;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (valid[h] && q[h][j] && A.max[c0 + j * kSmall + q[h][j] - 1] > s[h]) clash[h] = true;
+  }
+  // The intervals that start before the end (i1) and those that start at or before the
+  // start (i0). The wave's 128 additions lie between its first start and the furthest end,
+  // and usually few intervals do: the wave finds those, each lane its own among them.
+  const uint32_t w0 = t / 64 * 128;
+  uint64_t i0[2] = {0, 0}, i1[2] = {0, 0};
+  if (w0 < n) {
+    const uint64_t count = K.count[0], first = A.key[c + w0], furthest = A.max[c + min(w0 + 127, n - 1)];
+    if (first != kNone) {
+      const int lane = t & 63;
+      const uint64_t lo = wave_count_below<true>(K.start, count, first, lane);
+      const uint64_t len = wave_count_below<true>(K.start, count, furthest - 1, lane) - lo;
+      for (uint64_t step = len ? top_bit((uint32_t)len) : 0; step; step >>= 1) {  // len <= 2^31
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (i1[h] + step <= len && K.start[lo + i1[h] + step - 1] < e[h]) i1[h] += step;
+          if (i0[h] + step <= len && K.start[lo + i0[h] + step - 1] <= s[h]) i0[h] += step;
+        }
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        i1[h] += lo;
+        i0[h] += lo;
+        if (valid[h] && i0[h] && K.et[i0[h] - 1].x > s[h]) --i0[h];  // those that end at or before the start
+      }
+    }
+  }
+  __syncthreads();  // the tile bases
+  uint64_t a[2] = {0, 0};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (!valid[h]) continue;
+    const uint64_t before = scanned ? survivors_before(K, K.tbase, i0[h]) : survivors_before(K, base, i0[h]);
+    const uint64_t up_to = scanned ? survivors_before(K, K.tbase, i1[h]) : survivors_before(K, base, i1[h]);
+    if (up_to > before) clash[h] = true;
+    a[h] = clash[h] ? 0 : 1;
+    A.srank[c + k[h]] = before;
+    if (in.status) in.status[id[h]] = clash[h] ? GLEAM_REMAP_OVERLAP : GLEAM_REMAP_ADDED;
+  }
+  uint64_t sum[2] = {a[0], a[1]};
+  scan_pairs(sum, ScanSum(), wave);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (k[h] >= n) continue;
+    A.acc[c + k[h]] = a[h];
+    A.pos[c + k[h]] = sum[h] - a[h];
+  }
+}
+
+// The same over the whole device, for one chunk of every addition; the numbers come from a
+// scan of `acc`.
+__global__ __launch_bounds__(kThreads) void classify_all_kernel(Kept K, Additions A, Batches in) {
+  const uint64_t count = K.count[0];
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t k = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; k < A.n; k += stride) {
+    const uint64_t s = A.key[k];
+    uint64_t a = 0;
+    if (s != kNone) {
+      const uint64_t e = A.end[k];
+      const uint64_t i1 = count_below<true>(K.start, 0, count, e - 1);
+      uint64_t i0 = count_below<true>(K.start, 0, i1, s);
+      if (i0 && K.et[i0 - 1].x > s) --i0;
+      const uint64_t before = survivors_before(K, K.tbase, i0);
+      const bool clash = meets_own_chunk(A, 0, A.n, k, s, e) || survivors_before(K, K.tbase, i1) > before;
+      a = clash ? 0 : 1;
+      A.srank[k] = before;
+      if (in.status) in.status[A.idx[k]] = clash ? GLEAM_REMAP_OVERLAP : GLEAM_REMAP_ADDED;
+    }
+    A.acc[k] = a;
+  }
+}
+
+// ---- merge ------------------------------------------------------------------------------
+// Kept additions among the first k of the chunk at c (of n).
+__device__ __forceinline__ uint64_t kept_before(const Additions& A, uint64_t c, uint64_t n, uint64_t k) {
+  return k < n ? A.pos[c + k] : A.pos[c + n - 1] + A.acc[c + n - 1];
+}
+
+// Workgroups [0, tiles): the survivors of a tile each; the others the additions. When
+// the result would not fit, the kept additions are FULL instead. The first one also writes
+// the header and the counts.
+__global__ __launch_bounds__(kTileThreads) void place_kernel(MapRef map, Kept K, Additions A, Batches in,
+                                                             uint32_t tiles, uint64_t* counts) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t before = K.count[0], n_surv = K.tbase[tiles];
+  uint64_t n_acc = 0;
+  for (uint64_t c = 0; c < A.n; c += A.chunk) {
+    const uint64_t n = min(A.chunk, A.n - c);
+    n_acc += kept_before(A, c, n, n);
+  }
+  const uint64_t total = n_surv + n_acc;
+  const bool fits = total <= map.cap;
+  const uint64_t S = total > kFence ? (total + kFence - 1) / kFence : 1;
+  auto place = [&](uint64_t q, uint64_t s, ulonglong2 et) {
+    map.start[q] = s;
+    map.et[q] = et;
+    if (q % S == 0) map.fence[q / S] = s;
+  };
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    counts[0] = fits ? total : before;
+    counts[1] = fits ? n_acc : 0;
+    counts[2] = fits ? before - n_surv : 0;
+    counts[3] = A.n - (fits ? n_acc : 0);
+    if (fits) {
+      map.hdr[0] = total;
+      map.hdr[1] = S;
+      map.hdr[2] = (total + S - 1) / S;
+    }
+  }
+  if (blockIdx.x < tiles) {
+    const uint64_t p0 = (uint64_t)blockIdx.x * kTile + 64 * wave, p = p0 + lane;
+    if (!fits || p0 >= before) return;  // the wave
+    const uint64_t at = p < before ? p : before - 1;
+    const uint64_t s = K.start[at], word = K.word[p0 / 64];
+    const uint64_t first = uniform64(s, 0), last = uniform64(s, 63);
+    uint64_t q = K.tbase[blockIdx.x] + K.wpre[p0 / 64] + (uint64_t)__popcll(word & ((1ull << lane) - 1));
+    for (uint64_t c = 0; c < A.n; c += A.chunk) {
+      const uint64_t n = min(A.chunk, A.n - c);
+      const uint64_t* key = A.key + c;
+      if (key[0] >= last) continue;
+      uint64_t lo = n, hi = n;  // the entries that start before every survivor of the wave, and any
+      if (key[n - 1] >= first) {
+        lo = wave_count_below<false>(key, n, first, lane);
+        hi = wave_count_below<false>(key, n, last, lane);
+      }
+      q += kept_before(A, c, n, lo == hi ? lo : count_below<false>(key, lo, hi, s));
+    }
+    if ((word >> lane) & 1) place(q, s, K.et[p]);
+    return;
+  }
+  for (uint64_t k = (uint64_t)(blockIdx.x - tiles) * kTile + threadIdx.x; k < A.n;
+       k += (uint64_t)(gridDim.x - tiles) * kTile) {
+    if (!A.acc[k]) continue;
+    if (!fits) {
+      if (in.status) in.status[A.idx[k]] = GLEAM_REMAP_FULL;
+      continue;
+    }
+    const uint64_t s = A.key[k], own = k / A.chunk * A.chunk;
+    uint64_t q = A.srank[k] + A.pos[k];
+    for (uint64_t c = 0; c < A.n; c += A.chunk) {
+      if (c == own) continue;
+      const uint64_t n = min(A.chunk, A.n - c);
+      const uint64_t* key = A.key + c;
+      if (key[0] >= s) continue;
+      q += kept_before(A, c, n, key[n - 1] < s ? n : count_below<false>(key, 0, n, s));
+    }
+    place(q, s, make_ulonglong2(A.end[k], in.a_target[A.idx[k]] - s));
   }
 }
 
@@ -529,10 +754,6 @@ __global__ void finish_kernel(MapRef map, const uint64_t* keep, const uint64_t* 
 // that the lanes of a wave take together. Each global step is a different cache line
 // for nearly every lane, so the kernel is bound by the L2's request rate, not by bytes
 // or by latency (carrying several addresses per lane measured no faster).
-__device__ __forceinline__ uint32_t top_bit(uint32_t x) {  // largest power of two <= x (x >= 1)
-  return 1u << (31 - __builtin_clz(x));
-}
-
 __global__ void __launch_bounds__(kTranslateThreads)
 translate_kernel(MapRef map, const uint64_t* addr, uint64_t n, uint64_t* out) {
   __shared__ uint64_t fence[kFence];
@@ -589,7 +810,7 @@ gleam_status hip_call(hipError_t e, const char* what) {
 // Loads this file's GPU code object on the current device (gleam_preload).
 hipError_t preload_remap() {
   hipFuncAttributes attr;
-  return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&update_init_kernel));
+  return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&export_kernel));
 }
 
 }  // namespace gleam
@@ -684,19 +905,27 @@ extern "C" gleam_status gleam_remap_update(gleam_remap* m, const uint64_t* d_del
   const MapRef map = map_ref(m);
   const uint64_t cap = m->capacity;
   gleam_status st;
-  hipLaunchKernelGGL(update_init_kernel, dim3(1), dim3(64), 0, s, hdr, n_del, n_add);
-  if ((st = launch_status("update_init_kernel")) != GLEAM_OK) return st;
+  const Batches in{d_del_start, d_del_len, d_add_start, d_add_len, d_add_target, n_del, n_add, d_add_status};
+  const Removals R{at(L.rkb), at(L.rmax), n_del, chunk_of(n_del)};
+  const Additions A{at(L.kb), at(L.vb), at(L.aend), at(L.amax), at(L.acc), at(L.apos), at(L.srank),
+                    n_add, chunk_of(n_add)};
+  const Kept K{hdr + 12, at(L.keep), reinterpret_cast<uint32_t*>(b + L.wpre), at(L.tcount), at(L.tbase),
+               at(L.s_start), reinterpret_cast<ulonglong2*>(b + L.s_et)};
+  const bool many_del = n_del > kMaxChunked, many_add = n_add > kMaxChunked;
+  const uint32_t tiles = (uint32_t)L.tiles;
 
-  // 1. removals, survivors
-  const uint64_t* rkey = nullptr;
-  const uint64_t* rmax = nullptr;
-  if (n_del > 0 && n_del <= kSmall) {
-    hipLaunchKernelGGL(removals_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, d_del_start, d_del_len,
-                       (uint32_t)n_del, at(L.rkb), at(L.rmax));
-    if ((st = launch_status("removals_small_kernel")) != GLEAM_OK) return st;
-    rkey = at(L.rkb);
-    rmax = at(L.rmax);
-  } else if (n_del > 0) {
+  // 1. both batches sorted
+  const uint32_t r_chunks = many_del ? 0 : (uint32_t)((n_del + kSmall - 1) / kSmall);
+  const uint32_t a_chunks = many_add ? 0 : (uint32_t)((n_add + kSmall - 1) / kSmall);
+  if (r_chunks + a_chunks > 0) {
+    hipLaunchKernelGGL(sort_chunks_kernel, dim3(r_chunks + a_chunks), dim3(kSmallThreads), 0, s, in, R, A, r_chunks);
+    if ((st = launch_status("sort_chunks_kernel")) != GLEAM_OK) return st;
+  }
+  if (many_del || many_add) {
+    hipLaunchKernelGGL(update_init_kernel, dim3(1), dim3(64), 0, s, hdr, n_del, n_add);
+    if ((st = launch_status("update_init_kernel")) != GLEAM_OK) return st;
+  }
+  if (many_del) {
     const SortBuf ra{nullptr, at(L.rka), reinterpret_cast<uint32_t*>(b + L.ridx)};
     const SortBuf rb = sort_other(sort_ws, n_del, 1);
     hipLaunchKernelGGL(removal_prep_kernel, dim3(fold_grid(n_del)), dim3(kThreads), 0, s, d_del_start, d_del_len,
@@ -704,58 +933,45 @@ extern "C" gleam_status gleam_remap_update(gleam_remap* m, const uint64_t* d_del
     if ((st = launch_status("removal_prep_kernel")) != GLEAM_OK) return st;
     if ((st = radix_sort_pairs(ra, hdr, hdr + 4, n_del, 1, sort_ws, s)) != GLEAM_OK) return st;
     hipLaunchKernelGGL(removal_unpack_kernel, dim3(grid_for(n_del)), dim3(kThreads), 0, s, ra, rb, hdr + 4,
-                       d_del_start, d_del_len, n_del, at(L.rkb), at(L.rvb));
+                       d_del_start, d_del_len, n_del, R.key, at(L.last));
     if ((st = launch_status("removal_unpack_kernel")) != GLEAM_OK) return st;
-    if ((st = device_scan<ScanMax, false>(at(L.rvb), at(L.rmax), n_del, partial, s)) != GLEAM_OK) return st;
-    rkey = at(L.rkb);
-    rmax = at(L.rmax);
+    if ((st = device_scan<ScanMax, false>(at(L.last), R.max, n_del, partial, s)) != GLEAM_OK) return st;
   }
-  const dim3 block(kThreads), gcap(grid_for(cap)), gadd(grid_for(n_add));
-  hipLaunchKernelGGL(survive_kernel, gcap, block, 0, s, map, rkey, rmax, n_del, at(L.keep));
-  if ((st = launch_status("survive_kernel")) != GLEAM_OK) return st;
-  if ((st = device_scan<ScanSum, true>(at(L.keep), at(L.kpos), cap, partial, s)) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(compact_kernel, gcap, block, 0, s, map, at(L.keep), at(L.kpos), at(L.s_start),
-                     reinterpret_cast<ulonglong2*>(at(L.s_et)));
-  if ((st = launch_status("compact_kernel")) != GLEAM_OK) return st;
-
-  // 2-3. additions: sorted, checked against each other and the survivors, numbered
-  if (n_add > 0 && n_add <= kSmall) {
-    hipLaunchKernelGGL(additions_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, d_add_start, d_add_len,
-                       d_add_target, (uint32_t)n_add, d_add_status, at(L.s_start),
-                       reinterpret_cast<const ulonglong2*>(at(L.s_et)), at(L.keep), at(L.kpos), cap, at(L.kb),
-                       at(L.vb), at(L.aend), at(L.acc), at(L.apos));
-    if ((st = launch_status("additions_small_kernel")) != GLEAM_OK) return st;
-  } else if (n_add > 0) {
+  if (many_add) {
     const SortBuf aa{nullptr, at(L.ka), reinterpret_cast<uint32_t*>(b + L.aidx)};
     const SortBuf ab = sort_other(sort_ws, n_add, 1);
-    hipLaunchKernelGGL(addition_prep_kernel, dim3(fold_grid(n_add)), block, 0, s, d_add_start, d_add_len,
+    hipLaunchKernelGGL(addition_prep_kernel, dim3(fold_grid(n_add)), dim3(kThreads), 0, s, d_add_start, d_add_len,
                        d_add_target, n_add, d_add_status, aa.lo, aa.idx, hdr + 8);
     if ((st = launch_status("addition_prep_kernel")) != GLEAM_OK) return st;
     if ((st = radix_sort_pairs(aa, hdr + 1, hdr + 8, n_add, 1, sort_ws, s)) != GLEAM_OK) return st;
-    hipLaunchKernelGGL(addition_unpack_kernel, gadd, block, 0, s, aa, ab, hdr + 8, d_add_len, n_add, at(L.kb),
-                       at(L.vb), at(L.aend));
+    hipLaunchKernelGGL(addition_unpack_kernel, dim3(grid_for(n_add)), dim3(kThreads), 0, s, aa, ab, hdr + 8,
+                       d_add_len, n_add, A.key, A.idx, A.end);
     if ((st = launch_status("addition_unpack_kernel")) != GLEAM_OK) return st;
-    if ((st = device_scan<ScanMax, false>(at(L.aend), at(L.amax), n_add, partial, s)) != GLEAM_OK) return st;
-    hipLaunchKernelGGL(addition_classify_kernel, gadd, block, 0, s, at(L.kb), at(L.vb), at(L.aend), at(L.amax),
-                       n_add, at(L.s_start), reinterpret_cast<const ulonglong2*>(at(L.s_et)), at(L.keep),
-                       at(L.kpos), cap, d_add_status, at(L.acc));
-    if ((st = launch_status("addition_classify_kernel")) != GLEAM_OK) return st;
-    if ((st = device_scan<ScanSum, true>(at(L.acc), at(L.apos), n_add, partial, s)) != GLEAM_OK) return st;
+    if ((st = device_scan<ScanMax, false>(A.end, A.max, n_add, partial, s)) != GLEAM_OK) return st;
   }
 
-  // 4. merge by rank into the storage (only if everything fits), then the header
-  hipLaunchKernelGGL(place_survivors_kernel, gcap, block, 0, s, map, at(L.s_start),
-                     reinterpret_cast<const ulonglong2*>(at(L.s_et)), at(L.keep), at(L.kpos), at(L.kb), at(L.acc),
-                     at(L.apos), n_add);
-  if ((st = launch_status("place_survivors_kernel")) != GLEAM_OK) return st;
-  if (n_add > 0) {
-    hipLaunchKernelGGL(place_additions_kernel, gadd, block, 0, s, map, at(L.s_start), at(L.keep), at(L.kpos),
-                       at(L.kb), at(L.vb), at(L.aend), at(L.acc), at(L.apos), n_add, d_add_target, d_add_status);
-    if ((st = launch_status("place_additions_kernel")) != GLEAM_OK) return st;
+  // 2. survivors
+  hipLaunchKernelGGL(survive_kernel, dim3(tiles), dim3(kTileThreads), 0, s, map, R, K);
+  if ((st = launch_status("survive_kernel")) != GLEAM_OK) return st;
+  const bool scanned = many_add || L.tiles > kLdsTiles;
+  if (scanned && (st = device_scan<ScanSum, true>(K.tcount, K.tbase, L.tiles + 1, partial, s)) != GLEAM_OK) return st;
+
+  // 3. additions checked against each other and the survivors, and numbered
+  if (many_add) {
+    hipLaunchKernelGGL(classify_all_kernel, dim3(grid_for(n_add)), dim3(kThreads), 0, s, K, A, in);
+    if ((st = launch_status("classify_all_kernel")) != GLEAM_OK) return st;
+    if ((st = device_scan<ScanSum, true>(A.acc, A.pos, n_add, partial, s)) != GLEAM_OK) return st;
+  } else {
+    hipLaunchKernelGGL(classify_chunks_kernel, dim3(a_chunks ? a_chunks : 1), dim3(kSmallThreads), 0, s, K, A, in,
+                       tiles, scanned ? 1u : 0u);
+    if ((st = launch_status("classify_chunks_kernel")) != GLEAM_OK) return st;
   }
-  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(1), 0, s, map, at(L.keep), at(L.kpos), at(L.acc), at(L.apos),
-                     n_add, d_counts);
-  return launch_status("finish_kernel");
+
+  // 4. merge by rank into the storage (only if everything fits), the header and the counts
+  const uint64_t groups = (n_add + kTile - 1) / kTile;
+  const uint32_t a_groups = (uint32_t)(groups < kMaxGrid ? groups : kMaxGrid);
+  hipLaunchKernelGGL(place_kernel, dim3(tiles + a_groups), dim3(kTileThreads), 0, s, map, K, A, in, tiles, d_counts);
+  return launch_status("place_kernel");
 }
 
 extern "C" gleam_status gleam_remap_translate(const gleam_remap* m, const uint64_t* d_addr, uint64_t n,

@@ -320,3 +320,53 @@ def test_update_replays_in_a_graph():
         out_s = rng.integers(region[1], space, 100, dtype=np.uint64)
         update_both(m, om, rem=(out_s, np.full(100, 300, np.uint64)),
                     add=(out_s + np.uint64(50), np.full(100, 10, np.uint64), np.full(100, k, np.uint64)))
+
+
+@pytest.mark.parametrize("order", ["sorted", "reversed", "shuffled"])
+@pytest.mark.parametrize("n_add,n_del", [(63, 65), (129, 64), (2049, 4097), (8193, 6143), (32_768, 32_769),
+                                         (32_769, 32_768)])
+def test_chunks_of_a_batch(n_add, n_del, order):
+    """Removals and additions are sorted in chunks of 2,048, up to 16 of them: edges of the
+    runs and chunks, in each order, with repeated starts, clashes inside a chunk and across
+    chunks, ranges that reach over many chunks, invalid additions and empty ranges."""
+    rng = np.random.default_rng([n_add, n_del, len(order)])
+    space = 1 << 26
+    m, om = g.Remap(1 << 17), oremap.RemapMap(1 << 17)
+    base = (rng.choice(space // 1024, 40_000, replace=False).astype(np.uint64) * np.uint64(1024),
+            rng.integers(1, 700, 40_000, dtype=np.uint64), rng.integers(0, 1 << 62, 40_000, dtype=np.uint64))
+    update_both(m, om, add=base)
+
+    def ordered(n, longest):
+        s = rng.integers(0, space, n, dtype=np.uint64)
+        s[rng.integers(0, n, n // 16)] = s[rng.integers(0, n, n // 16)]  # repeated starts
+        length = rng.integers(0, 200, n, dtype=np.uint64)
+        length[rng.integers(0, n, 3)] = longest
+        k = {"sorted": np.argsort(s), "reversed": np.argsort(s)[::-1], "shuffled": np.arange(n)}[order]
+        return s[k], length[k]
+
+    for step in range(2):
+        rem, (a_s, a_l) = ordered(n_del, space // 64), ordered(n_add, space // 512)
+        say("remap chunks n_add", n_add, "n_del", n_del, order, "step", step)
+        st, counts, est, ecounts = update_both(m, om, rem, (a_s, a_l, rng.integers(0, 1 << 62, n_add, dtype=np.uint64)))
+        assert np.array_equal(st, est), f"step {step}: statuses"
+        assert counts == ecounts, f"step {step}: counts"
+        assert_map(m, om, f"step {step}")
+
+
+@pytest.mark.parametrize("cap", [1 << 22, (1 << 22) + 1])
+def test_small_update_of_a_large_map(cap):
+    """At most 4,096 tiles of 1,024 intervals are scanned by the workgroups that number the
+    additions, more by a launch of their own: both sides, with the map full."""
+    rng = np.random.default_rng(cap)
+    start = np.arange(cap, dtype=np.uint64) * np.uint64(16)
+    m, om = g.Remap(cap), oremap.RemapMap(cap)
+    say("remap large: load", cap)
+    update_both(m, om, add=(start, np.full(cap, 8, np.uint64), np.arange(cap, dtype=np.uint64)))
+    gone = np.sort(rng.choice(start, 3000, replace=False))
+    for rem, add in (((gone, np.ones(gone.size, np.uint64)), ((), (), ())),
+                     (((), ()), (gone[:2500] + np.uint64(1), np.full(2500, 6, np.uint64), gone[:2500])),
+                     ((start[-5:], np.ones(5, np.uint64)), (start[-5:] + np.uint64(2), np.full(5, 9, np.uint64), gone[:5]))):
+        say("remap large: update", len(rem[0]), len(add[0]))
+        st, counts, est, ecounts = update_both(m, om, rem, add)
+        assert np.array_equal(st, est) and counts == ecounts
+        assert_map(m, om, "large")
