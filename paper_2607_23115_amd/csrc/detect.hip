@@ -73,12 +73,14 @@ __device__ __forceinline__ uint32_t wg_exclusive_scan(uint32_t x, uint32_t* wave
   return before + incl - x;
 }
 
-// Phase-1 probe of one block's digest (in the lane that computed it).
+// Stores a block's digest and probes the table for it (in the lane that computed it).
 struct TableProbe {
   TableRef t;
   uint8_t* status;
   uint64_t* ref;
-  __device__ __forceinline__ void operator()(uint64_t g, uint64_t key) const {
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t key, uint64_t) const {
+    if (!valid) return;
+    a.block_out[g] = key;
     uint64_t val = 0;
     if (table_find(t, key, &val)) {
       status[g] = GLEAM_HIT_CACHE;

@@ -47,8 +47,8 @@ constexpr int kThreads = 256;
 constexpr int kSoloPad = 24 << 10;  // takes the workgroup's LDS past 80 KiB: one per CU
 constexpr uint64_t kQuadTailSlots = 16384;
 
-template <bool kSolo>
-__global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a) {
+template <bool kSolo, typename Out>
+__global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
   constexpr int W = kThreads / 64;
   constexpr uint32_t GROUP = W * kLeavesPerWave;
   __shared__ __attribute__((aligned(16))) uint8_t lds[W * kWaveLds + (kSolo ? kSoloPad : 0)];
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a) {
   // W * kQuadLeaves slots per workgroup (see launch_fp).
   if (!kSolo && blockIdx.x >= a.items) {
     constexpr uint64_t kPerGroup = GROUP / (W * kQuadLeaves);
-    quad_pass<W, false>(a, a.items * kPerGroup + (blockIdx.x - a.items), lds, nullptr);
+    quad_pass<W, false>(a, a.items * kPerGroup + (blockIdx.x - a.items), lds, nullptr, out);
     return;
   }
 
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a) {
       }
       const uint64_t v = tree_reduce_lanes(d, p, n, G, 2);
       if (lpb <= kLeavesPerWave) {
-        if (even && p == 0 && g < a.n_blocks) a.block_out[g] = v;
+        out(a, even && p == 0 && g < a.n_blocks, g, v, lf.seg);
       } else {
         if (lane == 0) roots[0][wave] = v;
         __syncthreads();
@@ -105,14 +105,15 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a) {
             v2 = roots[0][lane];
           }
           v2 = tree_reduce_lanes(v2, lane & (G2 - 1), n2, G2);
-          if (lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks) a.block_out[g2] = v2;
+          out(a, lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks, g2, v2, head.seg);
         }
       }
     } else {
       // One block of LPB > GROUP leaves, GROUP slots at a time.
       const uint64_t g = item;
       const uint64_t s0 = uniform64(find_segment(a.blk_first, a.n_seg, g));
-      const uint32_t nleaf = locate(a, g, 0, s0).blk_leaves;
+      const Leaf head = locate(a, g, 0, s0);
+      const uint32_t nleaf = head.blk_leaves;
       const uint32_t groups = a.leaf_out ? lpb / GROUP : (nleaf + GROUP - 1) / GROUP;
       for (uint32_t grp = 0; grp < groups; ++grp) {
         const uint32_t k = grp * GROUP + (uint32_t)wave * kLeavesPerWave + (lane >> 1);
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a) {
       if (wave == 0) {
         const uint32_t n2 = (nleaf + kLeavesPerWave - 1) / kLeavesPerWave;  // <= kMaxRoots
         const uint64_t r = tree_reduce_lds(roots[0], roots[1], n2, lane);
-        if (lane == 0) a.block_out[g] = r;
+        out(a, lane == 0, g, r, head.seg);
       }
     }
   }
@@ -138,12 +139,115 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a) {
 // One workgroup of W waves per W * kQuadLeaves slots; LPB <= kQuadLeaves, so every wave
 // holds whole blocks. W = 1 for the smallest batches (more CUs then share the loads; each
 // wave loads all its stages into LDS at once), 4 otherwise.
-template <int W>
-__global__ __launch_bounds__(64 * W) void fp_quad_kernel(FpArgs a) {
+template <int W, typename Out>
+__global__ __launch_bounds__(64 * W) void fp_quad_kernel(FpArgs a, Out out) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[W == 1 ? kQuadDirectLds : W * kQuadWaveLds];
-  quad_pass<W, false, W == 1>(a, blockIdx.x, lds, nullptr);
+  quad_pass<W, false, W == 1>(a, blockIdx.x, lds, nullptr, out);
 }
 
+// ---- Comparison with recorded digests -------------------------------------------------
+// The kernels above with the comparison in the place of the store: the digests never reach
+// memory, and no second pass reads them (30,000 small copies: 80.6 to 76.4 us a call; 2.9 GB
+// of a decoder in 1 MiB blocks, located to the leaf: 474 to 428 us, most of it from
+// leaf_pass). A lane keeps the payload it found when it located its leaf: searching for it
+// again where digests differ cost the small copies 6 us.
+//
+// first_diff[s] = min(first_diff[s], x) for the lanes with `differs`. When every such lane
+// of the wave lies in one payload (all but the waves at payload boundaries), the wave
+// takes the minimum itself and one lane issues the atomic, unless the word is already as
+// low: a payload whose blocks all changed (a layer updated in place) would otherwise queue
+// one atomic per block on its word (262,144 leaves of one payload: 3.2 ms). Every lane of
+// the wave calls it.
+__device__ __forceinline__ void lower_first_diff(uint64_t* first_diff, uint64_t s, bool differs, uint64_t x) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t active = __ballot(differs);
+  if (active == 0) return;  // the wave
+  const int leader = __ffsll((unsigned long long)active) - 1;
+  const uint64_t s0 = shfl64(s, leader);
+  bool issue = differs;
+  uint64_t m = differs ? x : ~0ull;
+  if (__ballot(differs && s != s0) == 0) {  // one payload for every differing lane
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      const uint64_t y = shfl_xor64(m, o);
+      m = y < m ? y : m;
+    }
+    issue = lane == leader;
+  }
+  if (issue && m < __hip_atomic_load(&first_diff[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMin(reinterpret_cast<unsigned long long*>(&first_diff[s]), (unsigned long long)m);
+}
+
+// Block g: equal digests? The first differing block of each payload.
+struct CompareBlocks {
+  const uint64_t* recorded;
+  uint8_t* match;  // nullable
+  uint64_t* first_diff;
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t v, uint64_t s) const {
+    const bool same = !valid || recorded[g] == v;
+    if (valid && match) match[g] = same ? 1 : 0;
+    lower_first_diff(first_diff, s, !same, same ? 0 : g - a.blk_first[s]);
+  }
+};
+
+// Leaf slot (slot = g * LPB + k): equal digests? Slots past a short block's last leaf hold 0
+// on both sides, so they always agree. The first differing leaf of each payload by its index
+// within the payload, (g - blk_first[s]) * LPB + k.
+struct CompareLeaves {
+  const uint64_t* recorded;
+  uint8_t* match;  // nullable
+  uint64_t* first_diff;
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t slot, uint64_t v, uint64_t s) const {
+    const bool same = !valid || recorded[slot] == v;
+    if (valid && match) match[slot] = same ? 1 : 0;
+    lower_first_diff(first_diff, s, !same, same ? 0 : slot - (a.blk_first[s] << a.lpb_log2));
+  }
+};
+
+// The leaf digests of one wave's consecutive slots alone: no tree, so a workgroup takes the
+// same few slots in blocks of any size (1 MiB blocks by whole blocks end unevenly: 2,829 of
+// them are 11.05 rounds of the 256 CUs). `slot0` in slots.
+template <typename Out>
+__device__ __forceinline__ void leaf_pass(const FpArgs& a, uint64_t slot0, uint8_t* tile, int lane, const Out& out) {
+  const uint64_t slot = slot0 + (lane >> 1), g = slot >> a.lpb_log2;
+  const uint32_t k = (uint32_t)(slot & ((1u << a.lpb_log2) - 1));
+  const Leaf lf = locate_wave(a, slot0 >> a.lpb_log2, g, k, lane);
+  const uint64_t d = hash_slot(lf, tile, lane);
+  out(a, (lane & 1) == 0 && g < a.n_blocks, slot, lf.len ? d : 0, lf.seg);
+}
+
+template <bool kDirect, typename Out>
+__device__ __forceinline__ void leaf_pass_quad(const FpArgs& a, uint64_t slot0, uint8_t* tile, int lane,
+                                               const Out& out) {
+  const uint64_t slot = slot0 + (lane >> 2), g = slot >> a.lpb_log2;
+  const uint32_t k = (uint32_t)(slot & ((1u << a.lpb_log2) - 1));
+  const Leaf lf = locate_wave(a, slot0 >> a.lpb_log2, g, k, lane);
+  const uint64_t d = kDirect ? hash_slot_quad_direct(lf, tile, lane) : hash_slot_quad(lf, tile, lane);
+  out(a, (lane & 3) == 0 && g < a.n_blocks, slot, lf.len ? d : 0, lf.seg);
+}
+
+// Two lanes per leaf in the first a.items workgroups, four in those after them (as fp_kernel).
+template <typename Out>
+__global__ __launch_bounds__(kThreads) void fp_leaf_kernel(FpArgs a, Out out) {
+  constexpr int W = kThreads / 64;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[W * kWaveLds];
+  static_assert(kQuadWaveLds <= kWaveLds, "one tile per wave");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint8_t* tile = lds + wave * kWaveLds;
+  if (blockIdx.x < a.items) {
+    leaf_pass(a, uniform64(((uint64_t)blockIdx.x * W + wave) * kLeavesPerWave), tile, lane, out);
+  } else {
+    const uint64_t slot0 = a.items * W * kLeavesPerWave + ((blockIdx.x - a.items) * W + wave) * kQuadLeaves;
+    leaf_pass_quad<false>(a, uniform64(slot0), tile, lane, out);
+  }
+}
+
+// One-wave workgroups, every stage at once into LDS.
+template <typename Out>
+__global__ __launch_bounds__(64) void fp_leaf_small_kernel(FpArgs a, Out out) {
+  __shared__ __attribute__((aligned(16))) uint8_t lds[kQuadDirectLds];
+  leaf_pass_quad<true>(a, (uint64_t)blockIdx.x * kQuadLeaves, lds, threadIdx.x, out);
+}
 
 }  // namespace
 
@@ -167,7 +271,11 @@ gleam_status validate_batch(const gleam_batch* b, const char* who) {
   return GLEAM_OK;
 }
 
-gleam_status launch_fp(const gleam_batch* b, uint64_t* d_block_digest, uint64_t* d_leaf_digest, hipStream_t stream) {
+namespace {
+
+template <typename Out>
+gleam_status launch_fp_out(const gleam_batch* b, uint64_t* d_block_digest, uint64_t* d_leaf_digest, const Out& out,
+                           hipStream_t stream) {
   if (b->n_blocks == 0) return GLEAM_OK;
   const int lpb_log2 = log2_exact(b->block_bytes) - 12;
   const uint64_t lpb = 1ull << lpb_log2;
@@ -187,9 +295,9 @@ gleam_status launch_fp(const gleam_batch* b, uint64_t* d_block_digest, uint64_t*
     // 10.1 vs 11.2 us), 4-wave ones above two waves per CU (ResNet-50, 895 waves: 16.6 vs
     // 17.9 us with one-wave workgroups)
     if (waves <= 2ull * (uint64_t)cus) {
-      hipLaunchKernelGGL(fp_quad_kernel<1>, dim3((uint32_t)waves), dim3(64), 0, stream, a);
+      hipLaunchKernelGGL((fp_quad_kernel<1, Out>), dim3((uint32_t)waves), dim3(64), 0, stream, a, out);
     } else {
-      hipLaunchKernelGGL(fp_quad_kernel<4>, dim3((uint32_t)((waves + 3) / 4)), dim3(256), 0, stream, a);
+      hipLaunchKernelGGL((fp_quad_kernel<4, Out>), dim3((uint32_t)((waves + 3) / 4)), dim3(256), 0, stream, a, out);
     }
     return launch_status("fp_quad_kernel");
   }
@@ -220,17 +328,57 @@ gleam_status launch_fp(const gleam_batch* b, uint64_t* d_block_digest, uint64_t*
   FpArgs a{b->seg_addr, b->seg_len, b->blk_first, b->n_seg, b->n_blocks, d_block_digest, d_leaf_digest,
            (uint32_t)lpb_log2, items};
   if (solo)
-    hipLaunchKernelGGL(fp_kernel<true>, dim3((uint32_t)grid), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((fp_kernel<true, Out>), dim3((uint32_t)grid), dim3(kThreads), 0, stream, a, out);
   else
-    hipLaunchKernelGGL(fp_kernel<false>, dim3((uint32_t)grid), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((fp_kernel<false, Out>), dim3((uint32_t)grid), dim3(kThreads), 0, stream, a, out);
   return launch_status("fp_kernel");
 }
 
+}  // namespace
+
+gleam_status launch_fp(const gleam_batch* b, uint64_t* d_block_digest, uint64_t* d_leaf_digest, hipStream_t stream) {
+  return launch_fp_out(b, d_block_digest, d_leaf_digest, StoreBlocks{}, stream);
+}
+
+gleam_status launch_fp_compare(const gleam_batch* b, const uint64_t* recorded, uint8_t* match, uint64_t* first_diff,
+                               hipStream_t stream) {
+  return launch_fp_out(b, nullptr, nullptr, CompareBlocks{recorded, match, first_diff}, stream);
+}
+
+// The launch rules of launch_fp for blocks of up to 64 KiB, here for blocks of any size.
+gleam_status launch_leaf_compare(const gleam_batch* b, const uint64_t* recorded, uint8_t* match, uint64_t* first_diff,
+                                 hipStream_t stream) {
+  if (b->n_blocks == 0) return GLEAM_OK;
+  const int lpb_log2 = log2_exact(b->block_bytes) - 12;
+  const uint64_t slots = b->n_blocks << lpb_log2;
+  const CompareLeaves out{recorded, match, first_diff};
+  FpArgs a{b->seg_addr, b->seg_len, b->blk_first, b->n_seg, b->n_blocks, nullptr, nullptr, (uint32_t)lpb_log2, 0};
+  if (slots <= kQuadMaxSlots) {
+    int cus = 0;
+    gleam_status st = device_cu_count(&cus);
+    if (st != GLEAM_OK) return st;
+    const uint64_t waves = (slots + kQuadLeaves - 1) / kQuadLeaves;
+    if (waves <= 2ull * (uint64_t)cus) {
+      hipLaunchKernelGGL(fp_leaf_small_kernel<CompareLeaves>, dim3((uint32_t)waves), dim3(64), 0, stream, a, out);
+      return launch_status("fp_leaf_small_kernel");
+    }
+  }
+  constexpr uint64_t group = (kThreads / 64) * kLeavesPerWave, quad_group = (kThreads / 64) * kQuadLeaves;
+  if (slots > kQuadMaxSlots && (slots / kQuadLargePayloadSlots < b->n_seg || slots / quad_group >= 0x7fffffffull))
+    a.items = (slots - kQuadTailSlots) / group;
+  const uint64_t grid = a.items + (slots - a.items * group + quad_group - 1) / quad_group;
+  if (grid > 0x7fffffffull) {
+    set_error("fingerprint: batch needs more than 2^31 workgroups");
+    return GLEAM_E_UNSUPPORTED;
+  }
+  hipLaunchKernelGGL(fp_leaf_kernel<CompareLeaves>, dim3((uint32_t)grid), dim3(kThreads), 0, stream, a, out);
+  return launch_status("fp_leaf_kernel");
+}
 
 // Loads this file's GPU code object on the current device (gleam_preload).
 hipError_t preload_fp_chunks() {
   hipFuncAttributes attr;
-  return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&fp_kernel<true>));
+  return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&fp_kernel<true, StoreBlocks>));
 }
 
 }  // namespace gleam

@@ -54,6 +54,7 @@ struct Leaf {
   const uint8_t* addr;
   uint32_t len;        // 0: no leaf in this slot
   uint32_t blk_leaves; // leaves of the slot's block (0 past the batch)
+  uint64_t seg;        // the slot's payload
 };
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
@@ -71,7 +72,7 @@ __device__ __forceinline__ uint64_t lane64(uint64_t x, int src) {
 
 // Leaf k of block g, which lies in segment s.
 __device__ __forceinline__ Leaf locate_at(const FpArgs& a, uint64_t g, uint32_t k, uint64_t s) {
-  Leaf lf{nullptr, 0, 0};
+  Leaf lf{nullptr, 0, 0, s};
   if (g >= a.n_blocks) return lf;
   const uint32_t shift = 12 + a.lpb_log2;
   const uint64_t j = g - a.blk_first[s];
@@ -90,7 +91,7 @@ __device__ __forceinline__ Leaf locate_at(const FpArgs& a, uint64_t g, uint32_t 
 
 // Leaf k of block g. `s` is a segment with blk_first[s] <= g (a lower start for the walk).
 __device__ __forceinline__ Leaf locate(const FpArgs& a, uint64_t g, uint32_t k, uint64_t s) {
-  if (g >= a.n_blocks) return Leaf{nullptr, 0, 0};
+  if (g >= a.n_blocks) return Leaf{nullptr, 0, 0, 0};
   while (s + 1 < a.n_seg && a.blk_first[s + 1] <= g) ++s;
   return locate_at(a, g, k, s);
 }
@@ -99,7 +100,7 @@ __device__ __forceinline__ Leaf locate(const FpArgs& a, uint64_t g, uint32_t k, 
 // in every lane): the wave finds g_first's segment, then each lane its own (a wave of
 // small payloads spans many segments). Every lane must call this.
 __device__ __forceinline__ Leaf locate_wave(const FpArgs& a, uint64_t g_first, uint64_t g, uint32_t k, int lane) {
-  if (g_first >= a.n_blocks) return Leaf{nullptr, 0, 0};
+  if (g_first >= a.n_blocks) return Leaf{nullptr, 0, 0, 0};
   const uint64_t s0 = uniform64(wave_find_segment(a.blk_first, a.n_seg, g_first, lane));
   const uint64_t s = lane_segment(a.blk_first, a.n_seg, s0, g < a.n_blocks ? g : a.n_blocks - 1, lane);
   return locate_at(a, g, k, s);
@@ -531,18 +532,21 @@ __device__ __forceinline__ uint64_t hash_slot_quad_direct(const Leaf& lf, uint8_
 // block's byte length to blen[g]. With kDirect (W = 1), `lds` holds kQuadDirectLds bytes
 // and aligned waves load every stage at once; otherwise kQuadWaveLds per wave.
 //
-// With a Probe (the one-launch detect path), the lane holding a block's digest also probes
-// the resident table for it right away (its latency overlapping other waves' streaming):
-// a held digest gets status HIT_CACHE and its value as ref; any other gets kProbePending.
+// `out` takes the block digests: every lane of the wave calls it, with `valid` in the lanes
+// that hold a digest, and the payload that the block lies in. The one-launch detect path also probes the resident table there (its
+// latency overlapping other waves' streaming): a held digest gets status HIT_CACHE and its
+// value as ref; any other gets kProbePending.
 constexpr uint8_t kProbePending = 0xFF;
 
-struct NoProbe {
-  __device__ __forceinline__ void operator()(uint64_t, uint64_t) const {}
+struct StoreBlocks {
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t v, uint64_t) const {
+    if (valid) a.block_out[g] = v;
+  }
 };
 
-template <int W, bool kLen, bool kDirect = false, typename Probe = NoProbe>
+template <int W, bool kLen, bool kDirect = false, typename Out = StoreBlocks>
 __device__ __forceinline__ void quad_pass(const FpArgs& a, uint64_t group, uint8_t* lds, uint32_t* blen,
-                                          const Probe& probe = Probe()) {
+                                          const Out& out = Out()) {
   static_assert(!kDirect || W == 1, "the direct loads hold one wave's stages");
   constexpr uint64_t kQuadGroup = (uint64_t)W * kQuadLeaves;
   const int lane = threadIdx.x & 63;
@@ -559,10 +563,7 @@ __device__ __forceinline__ void quad_pass(const FpArgs& a, uint64_t group, uint8
   if (a.leaf_out && head && g < a.n_blocks) a.leaf_out[slot] = lf.len ? d : 0;
   if (kLen && head && g < a.n_blocks && lf.len && k + 1 == lf.blk_leaves) blen[g] = (k << 12) + lf.len;
   const uint64_t v = tree_reduce_lanes(d, k, lf.blk_leaves, lpb, 4);
-  if (head && k == 0 && g < a.n_blocks) {
-    a.block_out[g] = v;
-    probe(g, v);
-  }
+  out(a, head && k == 0 && g < a.n_blocks, g, v, lf.seg);
 }
 
 }  // namespace

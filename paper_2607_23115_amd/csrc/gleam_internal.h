@@ -81,6 +81,12 @@ gleam_status device_cu_count(int* cus);        // compute units of the current d
 gleam_status validate_batch(const gleam_batch* b, const char* who);
 // Block digests of a validated batch (the fingerprint kernel launch).
 gleam_status launch_fp(const gleam_batch* b, uint64_t* d_block_digest, uint64_t* d_leaf_digest, hipStream_t stream);
+// The current digests against recorded ones: match (nullable) per block or leaf slot, and
+// first_diff lowered to the first difference of each payload (fp_chunks.hip).
+gleam_status launch_fp_compare(const gleam_batch* b, const uint64_t* recorded, uint8_t* match, uint64_t* first_diff,
+                               hipStream_t stream);
+gleam_status launch_leaf_compare(const gleam_batch* b, const uint64_t* recorded, uint8_t* match, uint64_t* first_diff,
+                                 hipStream_t stream);
 
 // Fill n u64 words with value on stream (a kernel, so it can live in a captured graph).
 gleam_status fill_u64(uint64_t* p, uint64_t n, uint64_t value, hipStream_t stream);

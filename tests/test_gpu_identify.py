@@ -143,3 +143,42 @@ def test_identify_payloads_changed_throughout(block):
         torch.cuda.synchronize()
         times[label] = a.elapsed_time(b) / 5
     assert times["changed"] < 3 * times["same"] + 0.05, times
+
+
+@pytest.mark.parametrize("shape,block", [("one wave", 65536), ("few", 16384), ("few", 2 << 20), ("small payloads", 4096),
+                                         ("small payloads", 65536), ("large payloads", 1 << 20),
+                                         ("large payloads", 4096)])
+def test_identify_matches_the_digests_of_both_states(shape, block):
+    """The comparison runs inside the fingerprint kernels: in every launch they choose (one
+    and four waves per workgroup, two lanes per leaf with a four-lane end, whole blocks) the
+    matches, first differences and verdicts are those of the digests before and after."""
+    rng = np.random.default_rng([block, len(shape)])
+    lens = {"one wave": rng.integers(0, 5000, 40), "few": rng.integers(0, 40 * 4096, 300),
+            "small payloads": rng.integers(0, 6 * 4096, 40_000 if block == 4096 else 9000),
+            "large payloads": rng.integers(0, 64 << 20, 12)}[shape].astype(np.uint64)
+    offs = np.concatenate([[0], np.cumsum((lens + np.uint64(15)) // np.uint64(16) * np.uint64(16))[:-1]]).astype(np.uint64)
+    arena = torch.randint(0, 256, (int(offs[-1] + lens[-1]) + 16,), dtype=torch.uint8, device="cuda")
+    batch = g.Batch.from_arena(arena, offs, lens, block)
+    lpb = batch.leaves_per_block
+    say("identify both states", shape, block, "slots", batch.n_blocks * lpb)
+    blocks0, leaves0 = g.fp_chunks(batch, with_leaves=True)
+    change = np.flatnonzero((rng.random(lens.size) < 0.3) & (lens > 0))
+    at = (offs[change] + (rng.random(change.size) * lens[change]).astype(np.uint64)).astype(np.int64)
+    arena[torch.from_numpy(at).cuda()] ^= 1
+    blocks1, leaves1 = g.fp_chunks(batch, with_leaves=True)
+    regions = np.append(np.arange(0, lens.size, 7), lens.size).astype(np.uint64)
+    first = batch.host_first.astype(np.int64)
+    for got, before, after, per in ((g.identify_weights(batch, blocks0, regions), blocks0, blocks1, 1),
+                                    (g.identify_leaves(batch, leaves0, regions), leaves0, leaves1, lpb)):
+        torch.cuda.synchronize()
+        same = (u64(before) == u64(after)).reshape(-1)
+        want = np.full(lens.size, oracle.NO_DIFF, np.uint64)
+        bad = np.flatnonzero(~same)
+        seg = np.searchsorted(first, bad // per, side="right") - 1
+        for s in np.unique(seg):
+            want[s] = bad[seg == s][0] - first[s] * per
+        verdict = [int(np.all(want[a:b] == oracle.NO_DIFF)) for a, b in zip(regions[:-1].astype(int), regions[1:].astype(int))]
+        assert np.array_equal(got[0].cpu().numpy().reshape(-1) != 0, same)
+        assert np.array_equal(u64(got[1]), want)
+        assert got[2].cpu().numpy().tolist() == verdict
+    assert np.array_equal(np.flatnonzero(want != oracle.NO_DIFF), change)
