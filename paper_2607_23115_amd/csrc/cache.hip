@@ -116,25 +116,36 @@ __global__ __launch_bounds__(kThreads) void insert_mark_kernel(ScratchRef sc, co
   if (first_in_workgroup(k, valid, bkeys, bslot)) scratch_mark(sc, keys, k, i);
 }
 
+// The keys of the kProbeAhead slots from pos on, read together.
+__device__ __forceinline__ void read_ahead(const TableRef& t, uint64_t pos, uint64_t* ahead) {
+#pragma unroll
+  for (int j = 0; j < kProbeAhead; ++j) ahead[j] = t.slots[2 * ((pos + j) & t.mask)];
+}
+
+// Takes the slot for key k if it is free, and returns what it held before (kEmpty: k is in).
+__device__ __forceinline__ uint64_t take_slot(uint64_t* slot, uint64_t k, uint64_t val) {
+  const uint64_t seen = atomicCAS(ull(slot), (unsigned long long)kEmpty, (unsigned long long)k);
+  if (seen == kEmpty) slot[1] = val;
+  return seen;
+}
+
 // Puts key k (not kEmpty) and its value in the table unless it is held; true if it was not.
-// The home slot is tried with a compare-and-swap at once (in a table with room most keys go
-// there: one round trip); the slots after it are read first, and only one that reads free
-// costs a swap. A read that is out of date can only show a slot free that is not, and the
-// swap then tells.
-__device__ __forceinline__ bool insert_key(const TableRef& t, uint64_t k, uint64_t val) {
-  uint64_t pos = slot_hash(k, t.shift);
-  for (uint64_t probe = 0; probe <= t.mask; ++probe) {
-    uint64_t* slot = t.slots + 2 * pos;
-    uint64_t seen = probe ? *slot : kEmpty;
-    if (seen == kEmpty) {
-      seen = atomicCAS(ull(slot), (unsigned long long)kEmpty, (unsigned long long)k);
+// `ahead` has the keys read from slot pos of its probe sequence on; only a slot that reads
+// free costs a compare-and-swap. A read that is out of date can only show a slot free that
+// is not, and the swap then tells.
+__device__ __forceinline__ bool insert_key(const TableRef& t, uint64_t k, uint64_t val, uint64_t pos, uint64_t* ahead) {
+  for (uint64_t probe = 0; probe <= t.mask; probe += kProbeAhead) {
+    if (probe) read_ahead(t, pos, ahead);
+#pragma unroll
+    for (int j = 0; j < kProbeAhead; ++j) {
+      uint64_t seen = ahead[j];
       if (seen == kEmpty) {
-        slot[1] = val;
-        return true;
+        seen = take_slot(t.slots + 2 * ((pos + j) & t.mask), k, val);
+        if (seen == kEmpty) return true;
       }
+      if (seen == k) return false;  // already held: keep the existing value
     }
-    if (seen == k) return false;  // already held: keep the existing value
-    pos = (pos + 1) & t.mask;
+    pos = (pos + kProbeAhead) & t.mask;
   }
   return false;
 }
@@ -149,10 +160,14 @@ __global__ __launch_bounds__(kThreads) void insert_commit_kernel(TableRef t, Scr
   const bool valid = i < n;
   const uint64_t k = keys[valid ? i : n - 1];  // n >= 1; clamped so the loads are unconditional
   const uint64_t val = vals[valid ? i : n - 1];
+  // the table's slots are read while the scratch table's answer is on its way
+  const uint64_t home = k != kEmpty ? slot_hash(k, t.shift) : 0;
+  uint64_t ahead[kProbeAhead];
+  read_ahead(t, home, ahead);
   bool added = false;
   if (valid && scratch_min(sc, keys, k, i) == i) {  // else a lower index carries this key
     if (k != kEmpty) {
-      added = insert_key(t, k, val);
+      added = insert_key(t, k, val, home, ahead);
     } else if (atomicCAS(ull(&t.hdr[0]), 0ull, 1ull) == 0ull) {
       t.hdr[1] = val;
       added = true;
@@ -218,19 +233,24 @@ __global__ __launch_bounds__(kThreads) void lookup_probe_kernel(TableRef t, Scra
   }
 }
 
-// Lookups of up to kSmallKeys keys: one 1024-thread workgroup, with the dedup table in
+// Lookups of few keys: one 1024-thread workgroup, with the dedup table in
 // LDS (kSmallSlots slots of index + 1, 0 = free; the key is read back from `keys`), so
 // no clear pass and no device-scope atomics. Pass 1 probes the resident table (each
 // thread first issues the reads of all its keys' home slots) and marks non-hits in LDS;
 // pass 2 resolves them. At these sizes the cost is launches, not bytes. Measured per
-// call on MI355X (three-launch path / this): 256 keys 18.9 / 13.7 us, 4,096 keys 21.7 /
-// 16.0 us, 8,192 keys 21.3 / 20.2 us, 12,917 keys 21.3 / 35.5 us: past a few thousand
-// keys one CU cannot issue the table's scattered reads fast enough.
+// call on MI355X, the three launches about 19 us throughout: 1,000 keys 7.2 us in a table
+// of 2^21 slots at load 0.05, 11.8 at load 0.5, 14.3 in one of 2^25 at load 0.6; 2,000 keys
+// 9.8, 14.8 and 27.2; 4,000 keys 17.2, 34.4 and 42.0: one CU cannot issue the table's
+// scattered reads any faster. So 2,048 keys, 1,024 in a table of more than 2^22 slots.
+// (Lookups without a caller's workspace stay here up to kSmallKeys: the others share the
+// GPU's one scratch table.)
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallPerThread = 4;
 constexpr uint64_t kSmallKeys = (uint64_t)kSmallThreads * kSmallPerThread;  // 4,096
 constexpr uint32_t kSmallSlots = 2 * kSmallKeys;                              // 32 KiB of LDS
 constexpr int kSmallShift = 64 - 13;                                           // log2(kSmallSlots) = 13
+
+uint64_t small_lookup_keys(const gleam_cache* c) { return c->capacity > (1ull << 22) ? 1024 : 2048; }
 
 __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableRef t, const uint64_t* keys, uint64_t n,
                                                                      uint8_t* status, uint64_t* ref) {
@@ -388,7 +408,17 @@ __global__ __launch_bounds__(kSmallThreads) void insert_small_kernel(TableRef t,
       }
       continue;
     }
-    if (insert_key(t, k[j], val[j])) ++added;
+    // (one CU's scattered accesses are what bounds this: the home slot is tried at once, as
+    // most keys go there in a table with room; with the slots read first 1,000 keys took
+    // 12.6 us against 10.5 at load 0.05, 19.4 against 21.4 at load 0.5)
+    const uint64_t home = slot_hash(k[j], t.shift);
+    uint64_t seen = take_slot(t.slots + 2 * home, k[j], val[j]);
+    if (seen != kEmpty && seen != k[j]) {
+      uint64_t ahead[kProbeAhead];
+      read_ahead(t, (home + 1) & t.mask, ahead);
+      if (insert_key(t, k[j], val[j], (home + 1) & t.mask, ahead)) seen = kEmpty;
+    }
+    if (seen == kEmpty) ++added;
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) added += __shfl_xor(added, o, 64);
@@ -591,7 +621,7 @@ extern "C" gleam_status gleam_cache_lookup(const gleam_cache* c, const uint64_t*
     return GLEAM_E_UNSUPPORTED;
   }
   hipStream_t s = (hipStream_t)stream;
-  if (n <= kSmallKeys) {
+  if (n <= small_lookup_keys(c)) {
     hipLaunchKernelGGL(lookup_small_kernel, dim3(1), dim3(kSmallThreads), 0, s, table_ref(c), d_keys, n, d_status,
                        d_ref);
     return launch_status("lookup_small_kernel");

@@ -29,6 +29,7 @@
 
 #include "gleam_device.h"
 #include "gleam_internal.h"
+#include "gleam_table.h"
 #include "radix_sort.h"
 
 namespace gleam {
@@ -123,16 +124,28 @@ uint32_t grid_for(uint64_t n) {
 
 __device__ __forceinline__ unsigned long long* ull(uint64_t* p) { return reinterpret_cast<unsigned long long*>(p); }
 
-// Slot of key k in the table, or -1 (k != kEmpty).
-__device__ __forceinline__ int64_t find_slot(const TableRef& t, uint64_t k) {
-  uint64_t pos = slot_hash(k, t.shift);
-  for (uint64_t probe = 0; probe <= t.mask; ++probe) {
-    const uint64_t key = t.slots[2 * pos];
-    if (key == k) return (int64_t)pos;
-    if (key == kEmpty) return -1;
-    pos = (pos + 1) & t.mask;
+// Stamp word of key k (k != kEmpty) from slot pos of its probe sequence on, or null; *now
+// gets the stamp, read along with the key.
+__device__ __forceinline__ uint64_t* find_stamp(const TableRef& t, uint64_t k, uint64_t pos, uint64_t* now) {
+  for (uint64_t probe = 0; probe <= t.mask; probe += kProbeAhead) {
+    uint64_t key[kProbeAhead], stamp[kProbeAhead];
+#pragma unroll
+    for (int j = 0; j < kProbeAhead; ++j) {
+      const uint64_t at = (pos + j) & t.mask;
+      key[j] = t.slots[2 * at];
+      stamp[j] = __hip_atomic_load(&t.stamps[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int j = 0; j < kProbeAhead; ++j) {
+      if (key[j] == k) {
+        *now = stamp[j];
+        return &t.stamps[(pos + j) & t.mask];
+      }
+      if (key[j] == kEmpty) return nullptr;
+    }
+    pos = (pos + kProbeAhead) & t.mask;
   }
-  return -1;
+  return nullptr;
 }
 
 __device__ __forceinline__ uint64_t wave_sum(uint64_t x) {
@@ -203,11 +216,7 @@ __global__ __launch_bounds__(kThreads) void touch_kernel(TableRef t, const uint6
     } else if (home_key == k) {
       stamp = &t.stamps[home];
     } else if (home_key != kEmpty) {
-      const int64_t pos = find_slot(t, k);
-      if (pos >= 0) {
-        stamp = &t.stamps[pos];
-        if (lead) now = __hip_atomic_load(stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      stamp = find_stamp(t, k, (home + 1) & t.mask, &now);
     }
     if (stamp) {
       hit = 1;
