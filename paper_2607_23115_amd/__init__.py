@@ -22,7 +22,6 @@ synchronise the other streams that used it before dropping the object.
 
 from __future__ import annotations
 
-import contextlib
 import ctypes
 import os
 
@@ -131,7 +130,7 @@ def _check(status: int) -> None:
 
 
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor | None, name: str, dtypes, min_numel: int = 0, optional: bool = False):
@@ -141,7 +140,7 @@ def _dev(t: torch.Tensor | None, name: str, dtypes, min_numel: int = 0, optional
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a tensor on the GPU")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
@@ -180,16 +179,38 @@ def _torch_stream(stream, device) -> torch.cuda.Stream:
     return torch.cuda.ExternalStream(h, device=device)
 
 
-@contextlib.contextmanager
-def _on_stream(stream, device):
-    """Run a call's own allocations and fills on the stream its kernels run on, and yield
+class _on_stream:
+    """Run a call's own allocations and fills on the stream its kernels run on; `with` gives
     that stream's handle. Tensors a call creates (outputs, workspaces, zeroed counters)
     then belong to that stream: a fill is ordered before the kernels that use the memory,
     and the caching allocator does not hand the memory out again before the stream is
-    done with it, whichever stream is torch's current one."""
-    s = _torch_stream(stream, device)
-    with torch.cuda.stream(s):
-        yield _stream(s)
+    done with it, whichever stream is torch's current one.
+
+    A call with no stream of its own on the current device is on that stream already: only
+    its handle is asked for (torch's stream objects and their context cost 7 us a call, and
+    short calls are bound by the host: the lookup, insert, touch and erase of a 12,917-block
+    model took the host 97 us, 60 without them, and one first_writes call 24 us, 12 without)."""
+
+    __slots__ = ("stream", "device", "inner")
+
+    def __init__(self, stream, device):
+        self.stream, self.device, self.inner = stream, device, None
+
+    def __enter__(self):
+        stream, device = self.stream, self.device
+        if stream is None and isinstance(device, torch.device) and device.type == "cuda":
+            current = torch.cuda.current_device()
+            if device.index is None or device.index == current:
+                return torch._C._cuda_getCurrentRawStream(current)
+        s = _torch_stream(stream, device)
+        self.inner = torch.cuda.stream(s)
+        self.inner.__enter__()
+        return _stream(s)
+
+    def __exit__(self, *exc):
+        if self.inner is not None:
+            self.inner.__exit__(*exc)
+        return False
 
 
 def _u64_device(a: np.ndarray, device) -> torch.Tensor:
