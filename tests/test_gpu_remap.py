@@ -370,3 +370,18 @@ def test_small_update_of_a_large_map(cap):
         st, counts, est, ecounts = update_both(m, om, rem, add)
         assert np.array_equal(st, est) and counts == ecounts
         assert_map(m, om, "large")
+
+
+@pytest.mark.parametrize("count", [131_072, 131_073, 262_144, 262_145, 400_003])
+def test_runs_of_whole_lines(count):
+    """Past 8,192 intervals a fence entry covers a multiple of 16 starts, which 16 lanes read
+    as one or two lines, after narrowing longer runs to 32: counts on both sides of a run of
+    16, 32 and 48, every interval edge probed, in a map with no room to spare."""
+    rng = np.random.default_rng(count)
+    start = np.sort(rng.choice(1 << 30, count, replace=False).astype(np.uint64)) * np.uint64(4)
+    length = rng.integers(1, 5, count, dtype=np.uint64)
+    m, om = g.Remap(count), oremap.RemapMap(count)
+    say("remap runs: count", count)
+    st, counts, est, ecounts = update_both(m, om, add=(start, length, rng.integers(0, 1 << 62, count, dtype=np.uint64)))
+    assert counts == ecounts and counts[0] == count
+    assert_translate(m, om, probes(om, rng, 10_001, 1 << 33), f"runs {count}")
