@@ -22,7 +22,8 @@
 // at the first free slot from its home, which is never past its old slot, so the cluster
 // stays a valid probe sequence and other clusters are not touched. Clusters are found
 // before any is repaired (a kernel boundary apart), and each is repaired by exactly one
-// wave.
+// wave. Evict does not leave a long cluster to one wave: its entries are taken out and put
+// back in parallel (see kLongFew).
 //
 // The table header keeps the live-entry count (word 3): inserts add their new keys, erase
 // subtracts what it removed, evict sets it, so erase can report the count without a scan.
@@ -50,6 +51,11 @@ enum : int {
   kWWidthHi = 10,   // and their range
   kWWidthLo = 11,
   kWLimit = 12,     // evict: the last bin collected first
+  kWLastHi = 13,    // evict: (stamp, key) of the last victim
+  kWLastLo = 14,
+  kWLong = 15,      // evict: a victim's cluster is long
+  kWMoved = 16,     // evict: entries were taken out, to be put back
+  kWFull = 17,      // evict: some kCollectTile slots in a row are all occupied
 };
 constexpr size_t kCounterBytes = 256;
 
@@ -355,6 +361,9 @@ __global__ __launch_bounds__(kInitThreads) void maint_init_kernel(TableRef t, ui
     counters[kWWidthHi] = (uint64_t)((end - base) >> 64);
     counters[kWWidthLo] = (uint64_t)(end - base);
     counters[kWLimit] = kPickBins - 1;
+    counters[kWLong] = 0;
+    counters[kWMoved] = 0;
+    counters[kWFull] = 0;
   }
   if (!kByStamp) return;
   __syncthreads();  // the range, read back by every thread of this workgroup
@@ -437,7 +446,7 @@ __global__ __launch_bounds__(kPickThreads) void evict_pick_kernel(TableRef t, co
 // (the claims queue on one word: by 64, 20 M entries took 3 ms); it has no barrier on its
 // way through the table. It also folds the AND and
 // OR of what it collects, from which the sort skips the digits every entry shares, and
-// notes which slots are occupied (a bit each).
+// notes which slots are occupied (a bit each), and whether a whole step of them is.
 constexpr uint32_t kCollectItems = 8;
 constexpr uint64_t kCollectTile = 64 * kCollectItems;  // slots per step of a wave
 constexpr uint32_t kCollectGrid = 512;  // 2^25 slots: 512 workgroups 175 us, 1,024 190, 2,048 228
@@ -519,18 +528,21 @@ __global__ __launch_bounds__(kThreads) void evict_collect_kernel(TableRef t, con
       stamp[r] = t.stamps[at];
     }
     uint64_t held_word = 0;
+    bool full = true;
 #pragma unroll
     for (uint32_t r = 0; r < kCollectItems; ++r) {
       const uint64_t i = i0 + 64 * r + lane;
       const bool held = i < capacity && key[r] != kEmpty;
       const uint64_t word = __ballot(held);
       if (lane == (int)r) held_word = word;
+      full = full && word == ~0ull;
       const bool mine = held && in_range(key[r], stamp[r]);
       const uint64_t who = __ballot(mine);
       if (mine) list[wave][listed + (uint32_t)__popcll(who & lt)] = (uint32_t)i;
       listed += (uint32_t)__popcll(who);
     }
     if (!kAgain && lane < (int)kCollectItems && i0 + 64 * lane < capacity) occupied[i0 / 64 + lane] = held_word;
+    if (!kAgain && full && lane == 0) counters[kWFull] = 1;
     wave_lds_sync();
     if (listed >= kListFlush) {  // all but a remainder, from the end of the list
       const uint32_t keep = listed % 64;
@@ -611,11 +623,25 @@ __device__ __forceinline__ uint32_t span_ballot(bool x, int lane) {
 // are repaired in a pass over the whole table instead, which needs no starts.
 constexpr uint32_t kNoStart = ~0u;
 
+// A long cluster is a long chain for one wave, and the longest ones grow without bound as the
+// load nears 1 (random keys in 2^20 slots: some of 4,096 slots from load 0.95 on, where one
+// lane repaired them slot by slot: 1,000 victims 29 ms, 106 at load 0.97). So, where slots of
+// a whole collecting step in a row are occupied (else no cluster has 1,024), the pass over the
+// table takes the entries of long clusters out, each wave those of its 64 slots, and
+// evict_put_back_kernel inserts them again, each by its own lane (1.0 and 1.8 ms). With few
+// victims one in a cluster of kLongFew slots or more sends the call through that pass, and
+// only such clusters are taken out (a wave repairs up to kLongFew slots, and there may be many
+// clusters and no victim in most of them: 20 victims in 2^25 slots at load 0.95 took 0.48 ms
+// so, 4.2 with 512 in the place of 4,096). With many victims nearly every cluster has some:
+// from kLongMany slots on (half of 2^20 slots at load 0.95: 0.36 ms; 0.39 with 512).
+constexpr uint32_t kLongFew = 4096, kLongMany = 256;
+
 // From one victim in 64 slots on: in 2^25 slots a pass over the table takes about as long
 // as finding and repairing the clusters of half a million victims one by one.
 __device__ __forceinline__ bool many_victims(const TableRef& t, uint64_t drop) { return drop > (t.mask + 1) / 64; }
 __global__ __launch_bounds__(kThreads) void evict_mark_kernel(TableRef t, SortBuf a, SortBuf b, uint64_t* counters,
-                                                              uint32_t* starts, uint64_t* evicted, uint64_t* counts) {
+                                                              const uint64_t* occupied, uint32_t* starts,
+                                                              uint64_t* evicted, uint64_t* counts) {
   const uint64_t drop = counters[kWDrop], live = counters[kWLive];
   const uint64_t t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t0 == 0) {
@@ -626,7 +652,12 @@ __global__ __launch_bounds__(kThreads) void evict_mark_kernel(TableRef t, SortBu
   if (drop == 0) return;
   const SortBuf sorted = sort_result(a, b, counters + kWBits, 2);
   const UpTo gone = last_victim(sorted, drop);
+  if (t0 == 0) {
+    counters[kWLastHi] = (uint64_t)(gone.last >> 64);
+    counters[kWLastLo] = (uint64_t)gone.last;
+  }
   const int lane = threadIdx.x & 63, l = lane & (kSpan - 1);
+  const bool full = counters[kWFull] != 0;
   if (many_victims(t, drop)) {
     for (uint64_t i = t0; i < drop; i += (uint64_t)gridDim.x * blockDim.x) {
       if (evicted) evicted[i] = sorted.lo[i];
@@ -649,7 +680,15 @@ __global__ __launch_bounds__(kThreads) void evict_mark_kernel(TableRef t, SortBu
       }
     }
     bool first = walking;
-    for (uint64_t step = 0; __any(walking) && step <= t.mask; step += kSpan) {
+    // whole words of the cluster after the victim's, up to kLongFew slots
+    const uint64_t v = walking ? c0 : 0, last_word = t.mask / 64;
+    uint32_t after = 0;
+    for (uint32_t at = 0; full && __any(walking && after == at) && at < kLongFew / 64 && at <= last_word; at += kSpan) {
+      const uint32_t open = span_ballot(occupied[(v / 64 + 1 + at + l) & last_word] != ~0ull, lane);
+      if (after == at) after += open ? __builtin_ctz(open) : kSpan;
+    }
+    uint32_t steps = 0;
+    for (; __any(walking) && steps < kLongFew && steps <= t.mask; steps += kSpan) {
       const uint64_t p = (c0 - 1 - l) & t.mask;
       const uint64_t k = t.slots[2 * p], stamp = t.stamps[p];
       const uint32_t open = span_ballot(k == kEmpty, lane), hit = span_ballot(gone(k, stamp), lane);
@@ -663,6 +702,7 @@ __global__ __launch_bounds__(kThreads) void evict_mark_kernel(TableRef t, SortBu
         }
       }
     }
+    if (first && l == 0 && (walking || ((v - c0) & t.mask) + 64 * (uint64_t)after >= kLongFew)) counters[kWLong] = 1;
     if (i < drop && l == 0) starts[i] = first ? (uint32_t)c0 : kNoStart;
   }
 }
@@ -697,7 +737,7 @@ __device__ uint32_t wave_repair(const TableRef& t, uint64_t c0, const Erased& er
     }
   }
   uint32_t removed = 0;
-  if (len >= 64 * kRepairWords) {  // a longer cluster: one lane, slot by slot
+  if (len >= 64 * kRepairWords) {  // a longer cluster (of an erased key): one lane, slot by slot
     if (lane == 0) {
       uint64_t n = 0;
       for (uint64_t p = c0; n <= t.mask; p = (p + 1) & t.mask, ++n) {
@@ -947,23 +987,74 @@ EraseWs erase_ws(void* ws, const EraseLayout& L) {
   return w;
 }
 
+// Entries of long clusters on their way out of the table and back: key, value and stamp by
+// the slot that they come from, and a bit for each.
+struct Moved {
+  uint64_t *key, *val, *stamp, *bits;
+};
+
+// The slots of word w (occupied bits occ) that lie in clusters of `from` slots or more. A
+// cluster gets that long only through a whole word, so most words need only their
+// neighbours; else the wave reads the 64 words on either side. Every word of a cluster
+// finds the same: its length, or that it reaches past those words. Every lane calls it.
+__device__ __forceinline__ uint64_t long_slots(const uint64_t* occupied, uint64_t last_word, uint64_t w, uint64_t occ,
+                                               uint32_t from, int lane) {
+  static_assert(kLongMany >= 256 && kLongFew <= 4096, "seen from any of its words");
+  const uint64_t prev = occupied[(w - 1) & last_word], next = occupied[(w + 1) & last_word];
+  if (occ != ~0ull && prev != ~0ull && next != ~0ull) return 0;
+  const uint64_t down = occupied[(w - 1 - lane) & last_word], up = occupied[(w + 1 + lane) & last_word];
+  const uint64_t down_open = __ballot(down != ~0ull), up_open = __ballot(up != ~0ull);
+  uint32_t before = 4096, after = 4096;  // occupied slots next to the word
+  if (down_open) {
+    const int j = __builtin_ctzll(down_open);
+    before = 64 * j + (uint32_t)__builtin_clzll(~shfl64(down, j));
+  }
+  if (up_open) {
+    const int j = __builtin_ctzll(up_open);
+    after = 64 * j + (uint32_t)__builtin_ctzll(~shfl64(up, j));
+  }
+  if (occ == ~0ull) return before + 64 + after >= from ? ~0ull : 0;
+  const uint32_t head = (uint32_t)__builtin_ctzll(~occ), tail = (uint32_t)__builtin_clzll(~occ);
+  uint64_t slots = 0;
+  if (head && before + head >= from) slots |= (1ull << head) - 1;
+  if (tail && tail + after >= from) slots |= ~0ull << (64 - tail);
+  return slots;
+}
+
 // The clusters that start in the 64 slots of word w, by one wave; `occupied` tells the
 // clusters as they were before any repair (a neighbouring wave may already have emptied the
 // slot before these). Those that end here too are done together: their entries are in the
 // lanes, and empty slots, which stay empty, keep them apart. One that goes on past the word
-// takes wave_repair.
+// takes wave_repair. Of a long cluster the wave takes out the slots of this word only.
 template <class Erased>
 __device__ void wave_repair_word(const TableRef& t, const uint64_t* occupied, uint64_t w, const Erased& erased,
-                                 uint64_t* used, int lane) {
+                                 uint64_t* used, const Moved& moved, uint64_t* any_moved, uint32_t long_from,
+                                 int lane) {
   const uint64_t occ = occupied[w], before = (64 * w - 1) & t.mask;
   const uint32_t size = t.mask < 63 ? (uint32_t)t.mask + 1 : 64u;
   const uint64_t p = 64 * w + (uint64_t)lane < t.mask ? 64 * w + (uint64_t)lane : t.mask;
   const uint4 e = *reinterpret_cast<const uint4*>(t.slots + 2 * p);
   const uint64_t stamp = t.stamps[p], k = lo64(e);
-  const uint64_t starts = occ & ~(occ << 1 | ((occupied[before / 64] >> (before & 63)) & 1));
-  if (starts == 0) return;  // uniform, as all the masks are
+  const uint64_t out = long_from ? long_slots(occupied, t.mask / 64, w, occ, long_from, lane) : 0;
+  const uint64_t starts = occ & ~(occ << 1 | ((occupied[before / 64] >> (before & 63)) & 1)) & ~out;
+  const bool mine_out = (out >> lane) & 1, back = mine_out && !erased(k, stamp);
+  const uint64_t back_bits = __ballot(back);
+  if (long_from && lane == 0) moved.bits[w] = back_bits;
+  if (out) {  // uniform, as all the masks are
+    if (lane == 0) *any_moved = 1;
+    if (back) {
+      moved.key[p] = k;
+      moved.val[p] = hi64(e);
+      moved.stamp[p] = stamp;
+    }
+    if (mine_out) {
+      t.slots[2 * p] = kEmpty;
+      t.stamps[p] = 0;
+    }
+  }
+  if (starts == 0) return;
   // the slots of this word's own clusters: from the first start on
-  uint64_t own = occ & (~0ull << __builtin_ctzll(starts));
+  uint64_t own = occ & ~out & (~0ull << __builtin_ctzll(starts));
   if ((own >> (size - 1)) & 1) {  // the last cluster reaches the word's end
     const int c = 63 - __builtin_clzll(starts);
     own &= (1ull << c) - 1;
@@ -997,11 +1088,10 @@ __device__ void wave_repair_word(const TableRef& t, const uint64_t* occupied, ui
   }
 }
 
-// One wave per cluster with victims, or, with many, one per 64 slots of the table; with
-// nothing but victims, a clear.
-__global__ __launch_bounds__(kThreads) void evict_repair_kernel(TableRef t, SortBuf a, SortBuf b,
-                                                                const uint64_t* counters, const uint32_t* starts,
-                                                                const uint64_t* occupied) {
+// One wave per cluster with victims, or, with many or in long clusters, one per 64 slots of
+// the table; with nothing but victims, a clear. (`moved` lies where the sorted victims were.)
+__global__ __launch_bounds__(kThreads) void evict_repair_kernel(TableRef t, uint64_t* counters, const uint32_t* starts,
+                                                                const uint64_t* occupied, Moved moved) {
   __shared__ uint64_t used[kWaves][kRepairWords];
   const uint64_t drop = counters[kWDrop];
   if (drop == 0) return;
@@ -1013,15 +1103,51 @@ __global__ __launch_bounds__(kThreads) void evict_repair_kernel(TableRef t, Sort
     }
     return;
   }
-  const UpTo gone = last_victim(sort_result(a, b, counters + kWBits, 2), drop);
+  const UpTo gone{order_of(counters[kWLastHi], counters[kWLastLo])};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t first = (uint64_t)blockIdx.x * kWaves + wave, stride = (uint64_t)gridDim.x * kWaves;
-  if (many_victims(t, drop)) {
+  const bool many = many_victims(t, drop);
+  if (many || counters[kWLong]) {
+    const uint32_t long_from = counters[kWFull] == 0 ? 0 : many ? kLongMany : kLongFew;
     const uint64_t words = (t.mask + 64) / 64;
-    for (uint64_t w = first; w < words; w += stride) wave_repair_word(t, occupied, w, gone, used[wave], lane);
+    for (uint64_t w = first; w < words; w += stride)
+      wave_repair_word(t, occupied, w, gone, used[wave], moved, &counters[kWMoved], long_from, lane);
   } else {
     for (uint64_t c = first; c < drop; c += stride)
       if (starts[c] != kNoStart) wave_repair(t, starts[c], gone, used[wave], lane);
+  }
+}
+
+// Puts the entries of long clusters back: one lane each, at the first free slot from its
+// home (the slots read kPutAhead at a time; only one that reads free costs a
+// compare-and-swap). Any order of insertions leaves valid probe sequences.
+constexpr int kPutAhead = 8;
+__global__ __launch_bounds__(kThreads) void evict_put_back_kernel(TableRef t, const uint64_t* counters, Moved moved) {
+  if (counters[kWMoved] == 0) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t words = (t.mask + 64) / 64;
+  for (uint64_t w = (uint64_t)blockIdx.x * kWaves + wave; w < words; w += (uint64_t)gridDim.x * kWaves) {
+    const uint64_t bits = moved.bits[w];
+    if (!((bits >> lane) & 1)) continue;
+    const uint64_t from = 64 * w + (uint64_t)lane;
+    const uint64_t k = moved.key[from], val = moved.val[from], stamp = moved.stamp[from];
+    uint64_t pos = slot_hash(k, t.shift);
+    bool placed = false;
+    for (uint64_t probe = 0; !placed && probe <= t.mask; probe += kPutAhead) {
+      uint64_t seen[kPutAhead];
+#pragma unroll
+      for (int j = 0; j < kPutAhead; ++j) seen[j] = t.slots[2 * ((pos + j) & t.mask)];
+#pragma unroll
+      for (int j = 0; j < kPutAhead; ++j) {
+        if (placed || seen[j] != kEmpty) continue;
+        const uint64_t q = (pos + j) & t.mask;
+        if (atomicCAS(ull(&t.slots[2 * q]), (unsigned long long)kEmpty, (unsigned long long)k) != kEmpty) continue;
+        t.slots[2 * q + 1] = val;
+        t.stamps[q] = stamp;
+        placed = true;
+      }
+      pos = (pos + kPutAhead) & t.mask;
+    }
   }
 }
 
@@ -1639,12 +1765,16 @@ extern "C" gleam_status gleam_cache_evict(gleam_cache* c, uint64_t keep, uint64_
   st = radix_sort_pairs(sa, counters + kWCollected, counters + kWBits, L.m, 2, ws_at<uint8_t>(d_ws, L.sort2), s);
   if (st != GLEAM_OK) return st;
   const uint32_t grid = grid_for(L.m) < 2048 ? grid_for(L.m) : 2048;
-  hipLaunchKernelGGL(evict_mark_kernel, dim3(grid), dim3(kThreads), 0, s, t, sa, sb, counters, leaders, d_evicted,
-                     d_counts);
+  hipLaunchKernelGGL(evict_mark_kernel, dim3(grid), dim3(kThreads), 0, s, t, sa, sb, counters, occupied, leaders,
+                     d_evicted, d_counts);
   if ((st = launch_status("evict_mark_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(evict_repair_kernel, dim3(grid), dim3(kThreads), 0, s, t, sa, sb, counters, leaders,
-                     occupied);
+  const Moved moved{sa.hi, sa.lo, sb.hi, reinterpret_cast<uint64_t*>(sa.idx)};
+  hipLaunchKernelGGL(evict_repair_kernel, dim3(grid), dim3(kThreads), 0, s, t, counters, leaders, occupied, moved);
   if ((st = launch_status("evict_repair_kernel")) != GLEAM_OK) return st;
+  if (c->capacity > kCollectTile) {  // else no step of slots is full
+    hipLaunchKernelGGL(evict_put_back_kernel, dim3(grid), dim3(kThreads), 0, s, t, counters, moved);
+    if ((st = launch_status("evict_put_back_kernel")) != GLEAM_OK) return st;
+  }
   if (keep < c->key_bound) c->key_bound = keep;
   return GLEAM_OK;
 }

@@ -398,3 +398,87 @@ def test_many_sort_tiles():
         assert u64(counts).tolist() == [want.size, len(ot)]
         assert np.array_equal(u64(ev)[:want.size], want)
         assert_table(table, ot, f"keep {keep}")
+
+
+def filled(log2_cap, keys, rng, stamps=100_000):
+    """A table (and the oracle's) that holds the keys, with random values and stamps."""
+    vals = rng.integers(0, 2**64, keys.size, dtype=np.uint64, endpoint=False)
+    table, ot = g.Cache(1 << log2_cap, max_load=0.9999), oracle.Table()
+    table.insert(keys_to_device(keys), keys_to_device(vals))
+    ot.insert(keys, vals)
+    ep = rng.integers(1, stamps, keys.size, dtype=np.uint64)
+    table.touch(keys_to_device(keys), epochs=keys_to_device(ep))
+    ot.touch(keys, ep)
+    return table, ot
+
+
+def evict_and_compare(table, ot, keys, keep):
+    ev, counts = table.evict(keep)
+    want = ot.evict(keep)
+    assert u64(counts).tolist() == [want.size, len(ot)], keep
+    assert np.array_equal(u64(ev)[:want.size], want), keep
+    assert_table(table, ot, f"keep {keep}")
+    st, ref = table.lookup(keys_to_device(keys))
+    est, eref = oracle.lookup(keys, ot)
+    assert np.array_equal(st.cpu().numpy(), est) and np.array_equal(u64(ref), eref), keep
+
+
+@pytest.mark.parametrize("log2_cap,load", [(9, 0.998), (10, 0.998), (11, 0.99), (13, 0.999), (14, 0.97), (17, 0.97),
+                                           (17, 0.99)])
+def test_evict_in_long_clusters(log2_cap, load):
+    """Eviction from tables so full that their clusters are hundreds to tens of thousands of
+    slots long (entries taken out and put back), down to single victims, and of few and of
+    many victims from one step to the next."""
+    rng = np.random.default_rng([1013, log2_cap, int(1000 * load)])
+    n = int(load * (1 << log2_cap))
+    keys = np.unique(rng.integers(0, 2**64, n, dtype=np.uint64, endpoint=False))
+    keys[:2] = [0, 2**64 - 1]
+    table, ot = filled(log2_cap, keys, rng)
+    for keep in (n - 1, n - 4, n - n // 200, n - n // 30, n // 2, 1):
+        say("evict in long clusters", log2_cap, load, keep)
+        evict_and_compare(table, ot, keys, keep)
+
+
+@pytest.mark.parametrize("length,each", [(1100, 3), (4090, 2), (4100, 2), (9000, 6), (9000, 40)])
+def test_evict_few_from_one_long_cluster(length, each):
+    """One cluster that wraps past the table's end, `each` keys per home slot, in a table
+    otherwise at load 1/4: one victim in it, none, a few, a third."""
+    rng = np.random.default_rng([1014, length, each])
+    log2_cap = 17
+    homes = (np.arange(length) // each * each + (1 << log2_cap) - length // 3) % (1 << log2_cap)
+    crowd = keys_at_homes(rng, homes, log2_cap)
+    keys = np.unique(np.concatenate([crowd, rng.integers(0, 2**64, 1 << 15, dtype=np.uint64, endpoint=False)]))
+    rng.shuffle(keys)
+    table, ot = filled(log2_cap, keys, rng)
+    n = len(ot)
+    old = crowd[rng.random(length) < 0.001]
+    for keep in (n - 1, n - 1 - old.size - 40, n - 3000, n * 2 // 3):
+        say("evict few from a long cluster", length, each, keep)
+        evict_and_compare(table, ot, keys, keep)
+
+
+def test_evict_cost_follows_no_cluster():
+    """A full table has clusters of any length (random keys in 2^20 slots at load 0.97: some
+    of tens of thousands of slots), and no one wave or lane may be left with one: evicting
+    1,000 entries there takes 10 times as long as at load 0.65, and took 290 times where a
+    lane repaired such a cluster by itself; the bound of 60 has room on both sides."""
+    rng = np.random.default_rng(1015)
+
+    def cost(load):
+        n = int(load * (1 << 20))
+        keys = np.unique(rng.integers(0, 2**64, n, dtype=np.uint64, endpoint=False))
+        table, _ = filled(20, keys, rng)
+        ws = table.maint_workspace()
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        best = float("inf")
+        for k in range(1, 4):
+            a.record()
+            table.evict(keys.size - 1000 * k, ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    say("evict cost at high load")
+    plain, full = cost(0.65), cost(0.97)
+    assert full < 60 * plain, (plain, full)
