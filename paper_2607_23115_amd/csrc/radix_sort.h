@@ -199,9 +199,13 @@ struct SortLds {
 
 // Up to kSortFineMax elements the tiles are a quarter (kSortItems 2 instead of 8): a pass of a
 // few tiles takes as long as one workgroup does, which is mostly the chain of its ranking
-// rounds.
+// rounds. Two-word keys take half tiles up to kSortMidMax, as whole ones would leave half of
+// the CUs idle (341,000 of 681,000 entries evicted: 322 to 275 us a call, all of 996,000 387 to
+// 373; sorting the million keys of an export, one word each, 308 to 342, so those do not).
 constexpr uint64_t kSortFineMax = 1u << 18;
 constexpr uint32_t kSortFineTile = kSortTile / 4;
+constexpr uint64_t kSortMidMax = 1u << 20;
+constexpr uint32_t kSortMidTile = kSortTile / 2;
 constexpr uint64_t kSortChunks = 512;  // two workgroups on each CU
 
 template <int kWords, int kSortItems>
@@ -394,6 +398,8 @@ __global__ __launch_bounds__(kPassThreads, 4) void sort_pass_kernel(SortBuf a, S
   const uint64_t n = *n_dev;
   if (n <= kSortFineMax)
     sort_pass<kWords, kPassItems / 4>(lds, a, b, n, bits, pass, totals, state, ticket);
+  else if (kWords == 2 && n <= kSortMidMax)
+    sort_pass<kWords, kPassItems / 2>(lds, a, b, n, bits, pass, totals, state, ticket);
   else
     sort_pass<kWords, kPassItems>(lds, a, b, n, bits, pass, totals, state, ticket);
 }
@@ -575,7 +581,9 @@ inline SortLayout sort_layout(uint64_t n_max, int words) {
   const uint64_t n = sort_capacity(n_max);
   L.tiles = (n_max + kSortTile - 1) / kSortTile;
   const uint64_t fine = ((n_max < kSortFineMax ? n_max : kSortFineMax) + kSortFineTile - 1) / kSortFineTile;
-  const uint64_t most = fine > L.tiles ? fine : L.tiles;  // (a sort for n_max may sort fewer)
+  const uint64_t mid = ((n_max < kSortMidMax ? n_max : kSortMidMax) + kSortMidTile - 1) / kSortMidTile;
+  uint64_t most = fine > L.tiles ? fine : L.tiles;  // (a sort for n_max may sort fewer)
+  if (words == 2 && n_max > kSortFineMax && mid > most) most = mid;
   L.chunks = most < kSortChunks ? most : kSortChunks;
   size_t off = 0;
   auto take = [&](size_t bytes) {

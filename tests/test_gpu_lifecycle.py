@@ -482,3 +482,19 @@ def test_evict_cost_follows_no_cluster():
     say("evict cost at high load")
     plain, full = cost(0.65), cost(0.97)
     assert full < 60 * plain, (plain, full)
+
+
+@pytest.mark.parametrize("n", [1 << 14, (1 << 18) - 1, (1 << 18) + 1, 333_333, (1 << 20) - 2047, 1 << 20, (1 << 20) + 1])
+def test_sort_tile_sizes(n):
+    """Every entry evicted, in order, for counts on either side of where the sort's tiles
+    change size, and of a last tile that is full, nearly empty or ragged."""
+    rng = np.random.default_rng(1016)
+    keys = rng.permutation(np.unique(rng.integers(0, 2**64, n + n // 64 + 8, dtype=np.uint64, endpoint=False)))[:n]
+    ep = rng.integers(1, 1 << 20, n, dtype=np.uint64)
+    say("sort tiles", n)
+    table = g.Cache(1 << 21, max_load=0.7)
+    table.insert(keys_to_device(keys), keys_to_device(keys))
+    table.touch(keys_to_device(keys), epochs=keys_to_device(ep))
+    ev, counts = table.evict(0)
+    assert u64(counts).tolist() == [n, 0]
+    assert np.array_equal(u64(ev)[:n], keys[np.lexsort((keys, ep))])
