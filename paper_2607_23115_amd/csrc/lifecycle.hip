@@ -63,20 +63,25 @@ constexpr uint32_t kPickBins = 1024;        // evict's histogram
 
 // Export: bins of the key range, each of `parts` parts of kCuts cuts. A part covers
 // kPartSlots table slots' share of the range, so a part of a digest table at load 0.7 has
-// 5,734 entries, of the kPartMax that a workgroup sorts in LDS. The entries are written to
-// their bins only, so that a tile of 8,192 slots has several entries for each bin.
+// 5,734 entries, of the kPartMax that a workgroup sorts in LDS. Where the table may hold more
+// than kPartFine entries a part (load 0.75, by the host's bound on its keys), there are twice
+// as many bins: digests then fit at any load up to 2^27 slots, and up to load 0.75 in 2^28
+// (kMaxAllParts). 2^20 slots at load 0.95: 109 us, against 304 when the parts overflow and
+// the radix sort takes over, and 260 for gathering and sorting from the start. The entries are
+// written to their bins only, so that a tile of 8,192 slots has several entries for each bin.
 constexpr uint32_t kPartSlots = 8192;
 constexpr uint32_t kPartMax = 7168;
+constexpr uint32_t kPartFine = 6144;
 constexpr uint32_t kCuts = 2048;
 constexpr uint32_t kMaxParts = 8;
 constexpr uint32_t kBinMax = 65535;         // entries of a bin (numbered in 16 bits)
-constexpr uint32_t kMaxAllParts = 16384;
-constexpr uint32_t kMaxBins = kMaxAllParts / kMaxParts;
+constexpr uint32_t kMaxAllParts = 32768;
+constexpr uint32_t kFewParts = 16384;       // up to these the kernels take half the LDS and registers
 constexpr uint32_t kSpreadGrid = 256;       // workgroups that spread the entries over the bins
 
 struct MaintLayout {
   uint64_t m;     // capacity + 1 (the last is the key kEmpty's header side slot)
-  uint32_t bins, parts, spread;
+  uint32_t bins, parts, spread;  // (bins: the fewer ones)
   size_t counters;
   size_t pick, occupied, leaders, hi, lo, idx, sort2;          // evict
   size_t share, starts, xkey, xpay, xidx, sort1;               // export
@@ -103,13 +108,13 @@ MaintLayout maint_layout(uint64_t capacity) {
   const size_t evict_total = off;
   off = kCounterBytes;
   const uint64_t want = capacity / kPartSlots;
-  const uint32_t all = (uint32_t)(want < 1 ? 1 : want < kMaxAllParts ? want : kMaxAllParts);
+  const uint32_t all = (uint32_t)(want < 1 ? 1 : want < kMaxAllParts / 2 ? want : kMaxAllParts / 2);
   L.parts = all < kMaxParts ? all : kMaxParts;
   L.bins = all / L.parts;
   const uint64_t spread = (capacity + 4095) / 4096;
   L.spread = (uint32_t)(spread < kSpreadGrid ? spread : kSpreadGrid);
-  L.share = take(4 * (size_t)all * L.spread);
-  L.starts = take(4 * ((size_t)all + 1));
+  L.share = take(4 * 2 * (size_t)all * L.spread);
+  L.starts = take(4 * (2 * (size_t)all + 1));
   L.xkey = take(8 * sort_capacity(L.m));  // every entry's key by bin (the radix sort's buffer a)
   L.xpay = take(16 * L.m);                // and {value, stamp}
   L.xidx = take(4 * sort_capacity(L.m));
@@ -1164,10 +1169,11 @@ constexpr uint32_t kSpreadThreads = 1024;
 constexpr uint32_t kSpreadItems = 4;  // slots per thread and step when counting
 constexpr uint32_t kSpreadEach = 8;   // slots per thread and tile when spreading
 
-// Counts the entries of the parts in this workgroup's share of the slots.
-__global__ __launch_bounds__(kSpreadThreads) void export_count_kernel(TableRef t, const uint64_t* counters, uint32_t all,
-                                                                      uint32_t* share) {
-  __shared__ uint32_t h[kMaxAllParts];
+// Counts the entries of the (at most kMost) parts in this workgroup's share of the slots.
+template <uint32_t kMost>
+__global__ __launch_bounds__(kSpreadThreads) void export_count_kernel(TableRef t, const uint64_t* counters,
+                                                                      uint32_t all, uint32_t* share) {
+  __shared__ uint32_t h[kMost];
   for (uint32_t i = threadIdx.x; i < all; i += kSpreadThreads) h[i] = 0;
   __syncthreads();
   const KeyCells cells(counters, all * kCuts);
@@ -1217,11 +1223,12 @@ __global__ __launch_bounds__(64) void export_share_kernel(uint32_t all, uint32_t
 
 // One workgroup: starts[] from totals to positions, starts[all] = the entries; the count;
 // and whether the radix sort takes over (counters[kWCollected]: its count, else 0).
+template <uint32_t kMost>
 __global__ __launch_bounds__(kInitThreads) void export_starts_kernel(uint32_t bins, uint32_t parts, uint32_t* starts,
                                                                      uint64_t* counters, uint64_t* count) {
   __shared__ uint32_t wave_sum[kInitThreads / 64];
   __shared__ uint32_t skewed;
-  constexpr uint32_t kEach = kMaxAllParts / kInitThreads;
+  constexpr uint32_t kEach = kMost / kInitThreads;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t all = bins * parts;
   const uint32_t each = (all + kInitThreads - 1) / kInitThreads;  // at most kEach
@@ -1271,10 +1278,12 @@ __global__ __launch_bounds__(kInitThreads) void export_starts_kernel(uint32_t bi
 // bin order in LDS first, so that consecutive lanes write a bin's entries to consecutive
 // addresses: written one by one, 20 M entries are 40 M small requests to the L2s (580 us).
 constexpr uint32_t kTileSlots = kSpreadThreads * kSpreadEach;
+template <uint32_t kMost>
 __global__ __launch_bounds__(kSpreadThreads) void export_spread_kernel(TableRef t, const uint64_t* counters,
                                                                        uint32_t bins, uint32_t parts,
                                                                        const uint32_t* share, const uint32_t* starts,
                                                                        uint64_t* xkey, uint4* xpay) {
+  constexpr uint32_t kMaxBins = kMost / kMaxParts;
   __shared__ uint32_t at[kMaxBins];     // the workgroup's next place in each bin
   __shared__ uint32_t count[kMaxBins];  // the tile's entries by bin, then their first places in the tile
   __shared__ uint16_t sbin[kTileSlots];
@@ -1857,23 +1866,27 @@ extern "C" gleam_status gleam_cache_export(const gleam_cache* c, uint64_t* d_key
   uint32_t* starts = ws_at<uint32_t>(d_ws, L.starts);
   uint64_t* xkey = ws_at<uint64_t>(d_ws, L.xkey);
   uint4* xpay = ws_at<uint4>(d_ws, L.xpay);
-  const uint32_t all = L.bins * L.parts;
+  const uint32_t fewer = L.bins * L.parts;
+  const uint32_t bins = c->key_bound > (uint64_t)fewer * kPartFine ? 2 * L.bins : L.bins, all = bins * L.parts;
+  const bool few = all <= kFewParts;
   hipLaunchKernelGGL(maint_init_kernel<false>, dim3(1), dim3(kInitThreads), 0, s, t, 0, counters, (uint32_t*)nullptr);
   if ((st = launch_status("maint_init_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_count_kernel, dim3(L.spread), dim3(kSpreadThreads), 0, s, t, counters, all, share);
+  hipLaunchKernelGGL(few ? export_count_kernel<kFewParts> : export_count_kernel<kMaxAllParts>, dim3(L.spread),
+                     dim3(kSpreadThreads), 0, s, t, counters, all, share);
   if ((st = launch_status("export_count_kernel")) != GLEAM_OK) return st;
   hipLaunchKernelGGL(export_share_kernel, dim3((all + 63) / 64), dim3(64), 0, s, all, L.spread, share, starts);
   if ((st = launch_status("export_share_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_starts_kernel, dim3(1), dim3(kInitThreads), 0, s, L.bins, L.parts, starts, counters, d_count);
+  hipLaunchKernelGGL(few ? export_starts_kernel<kFewParts> : export_starts_kernel<kMaxAllParts>, dim3(1),
+                     dim3(kInitThreads), 0, s, bins, L.parts, starts, counters, d_count);
   if ((st = launch_status("export_starts_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_spread_kernel, dim3(L.spread), dim3(kSpreadThreads), 0, s, t, counters, L.bins, L.parts,
-                     share, starts, xkey, xpay);
+  hipLaunchKernelGGL(few ? export_spread_kernel<kFewParts> : export_spread_kernel<kMaxAllParts>, dim3(L.spread),
+                     dim3(kSpreadThreads), 0, s, t, counters, bins, L.parts, share, starts, xkey, xpay);
   if ((st = launch_status("export_spread_kernel")) != GLEAM_OK) return st;
   // (the shares are done with: their first words tell the parts left to the second launch)
-  hipLaunchKernelGGL(export_part_kernel<false>, dim3(all), dim3(kPartThreads), 0, s, counters, L.bins, L.parts, starts,
+  hipLaunchKernelGGL(export_part_kernel<false>, dim3(all), dim3(kPartThreads), 0, s, counters, bins, L.parts, starts,
                      xkey, xpay, share, d_keys, d_vals, d_stamps);
   if ((st = launch_status("export_part_kernel")) != GLEAM_OK) return st;
-  hipLaunchKernelGGL(export_part_kernel<true>, dim3(all), dim3(kPartThreads), 0, s, counters, L.bins, L.parts, starts,
+  hipLaunchKernelGGL(export_part_kernel<true>, dim3(all), dim3(kPartThreads), 0, s, counters, bins, L.parts, starts,
                      xkey, xpay, share, d_keys, d_vals, d_stamps);
   if ((st = launch_status("export_part_kernel")) != GLEAM_OK) return st;
   if (c->capacity <= kPartMax) return GLEAM_OK;  // no part can hold more

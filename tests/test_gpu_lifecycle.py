@@ -484,7 +484,8 @@ def test_evict_cost_follows_no_cluster():
     assert full < 60 * plain, (plain, full)
 
 
-@pytest.mark.parametrize("n", [1 << 14, (1 << 18) - 1, (1 << 18) + 1, 333_333, (1 << 20) - 2047, 1 << 20, (1 << 20) + 1])
+@pytest.mark.parametrize("n", [1 << 14, (1 << 18) - 1, (1 << 18) + 1, 333_333, (1 << 20) - 2047, 1 << 20,
+                               (1 << 20) + 1])
 def test_sort_tile_sizes(n):
     """Every entry evicted, in order, for counts on either side of where the sort's tiles
     change size, and of a last tile that is full, nearly empty or ragged."""
@@ -498,3 +499,69 @@ def test_sort_tile_sizes(n):
     ev, counts = table.evict(0)
     assert u64(counts).tolist() == [n, 0]
     assert np.array_equal(u64(ev)[:n], keys[np.lexsort((keys, ep))])
+
+
+@pytest.mark.parametrize("log2_cap,load", [(13, 0.74), (13, 0.76), (13, 0.999), (15, 0.74), (15, 0.9), (16, 0.99),
+                                           (20, 0.95)])
+def test_export_of_full_tables(log2_cap, load):
+    """Digests on either side of the load from which the export has twice as many bins; the
+    table's bound on its keys too high (keys inserted again) and too low (a smaller one set)
+    for its live count."""
+    rng = np.random.default_rng([1017, log2_cap, int(1000 * load)])
+    n = int(load * (1 << log2_cap))
+    keys = rng.permutation(np.unique(rng.integers(0, 2**64, n, dtype=np.uint64, endpoint=False)))
+    say("export of full tables", log2_cap, load)
+    table, ot = filled(log2_cap, keys, rng)
+    assert_table(table, ot, "full")
+    table.set_key_bound(1)
+    assert_table(table, ot, "low bound")
+    few, ofew = filled(log2_cap, keys[: n // 4], rng)
+    again = keys_to_device(keys[: n // 4])
+    for _ in range(3):  # the bound comes to n
+        few.insert(again, again)
+    assert_table(few, ofew, "high bound")
+
+
+def test_export_cost_at_high_load():
+    """An export's parts fit their workgroups at any load, so that a fuller table takes little
+    longer: at load 0.95 as long as at 0.65 (1.0 times; 2.8 where its parts overflowed and all
+    entries went through a sort by digits instead)."""
+    rng = np.random.default_rng(1018)
+
+    def cost(load):
+        n = int(load * (1 << 20))
+        table, _ = filled(20, np.unique(rng.integers(0, 2**64, n, dtype=np.uint64, endpoint=False)), rng)
+        ws = table.maint_workspace()
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        best = float("inf")
+        for _ in range(8):
+            a.record()
+            table.export(ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    say("export cost at high load")
+    plain, full = cost(0.65), cost(0.95)
+    assert full < 1.8 * plain, (plain, full)
+
+
+def test_export_of_most_parts():
+    """110 M digests in 2^27 slots: twice the bins of the largest number (32,768 parts). The
+    oracle's table would take minutes, so the order, count and payloads are checked directly:
+    value and stamp are functions of the key."""
+    n, step = 110_000_000, 1 << 25
+    say("export of most parts")
+    gen = torch.Generator(device="cuda").manual_seed(1019)
+    table = g.Cache(1 << 27, max_load=0.9)
+    for i in range(0, n, step):
+        k = torch.empty(min(step, n - i), dtype=torch.int64, device="cuda").random_(generator=gen)
+        table.insert(k, k ^ 12345)
+        table.touch(k, epochs=(k >> 20) + 1)
+    keys, vals, stamps, count = table.export()
+    c = int(count.item())
+    assert n - 1000 < c <= n  # a few repeats among random keys
+    k = keys[:c]
+    assert bool((k[1:] > k[:-1]).all())  # (63-bit keys: signed order is theirs)
+    assert torch.equal(vals[:c], k ^ 12345) and torch.equal(stamps[:c], (k >> 20) + 1)
