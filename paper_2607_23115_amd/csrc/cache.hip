@@ -237,11 +237,14 @@ __global__ __launch_bounds__(kThreads) void lookup_probe_kernel(TableRef t, Scra
 // LDS (kSmallSlots slots of index + 1, 0 = free; the key is read back from `keys`), so
 // no clear pass and no device-scope atomics. Pass 1 probes the resident table (each
 // thread first issues the reads of all its keys' home slots) and marks non-hits in LDS;
-// pass 2 resolves them. At these sizes the cost is launches, not bytes. Measured per
-// call on MI355X, the three launches about 19 us throughout: 1,000 keys 7.2 us in a table
-// of 2^21 slots at load 0.05, 11.8 at load 0.5, 14.3 in one of 2^25 at load 0.6; 2,000 keys
-// 9.8, 14.8 and 27.2; 4,000 keys 17.2, 34.4 and 42.0: one CU cannot issue the table's
-// scattered reads any faster. So 2,048 keys, 1,024 in a table of more than 2^22 slots.
+// pass 2 resolves them. At these sizes the cost is launches, not bytes, and how far it
+// carries follows the table's load (the reads that one CU has to issue, not their distance:
+// tables of 2^12 to 2^25 slots differ little). Measured per call on MI355X, this / the three
+// launches, keys of which none, half and all are held: load 0.05, 2,500 keys 12 / 14, 9 / 12
+// and 5 / 12 us, 3,000 15 / 14, 11 / 12 and 6 / 12, 4,000 28 / 14, 16 / 13 and 7 / 12; load
+// 0.3, 2,500 keys 14 / 13, 12 / 11 and 7 / 9, 3,000 19 / 13, 15 / 11 and 8 / 9; load 0.6,
+// 2,000 keys 23 / 20, 20 / 17 and 12 / 12, 2,500 30 / 19, 26 / 17 and 14 / 12. So 3,072 keys
+// below load 1/4, 2,560 below 1/2, 2,048 above, by the host's bound on the table's keys.
 // (Lookups without a caller's workspace stay here up to kSmallKeys: the others share the
 // GPU's one scratch table.)
 constexpr int kSmallThreads = 1024;
@@ -250,7 +253,9 @@ constexpr uint64_t kSmallKeys = (uint64_t)kSmallThreads * kSmallPerThread;  // 4
 constexpr uint32_t kSmallSlots = 2 * kSmallKeys;                              // 32 KiB of LDS
 constexpr int kSmallShift = 64 - 13;                                           // log2(kSmallSlots) = 13
 
-uint64_t small_lookup_keys(const gleam_cache* c) { return c->capacity > (1ull << 22) ? 1024 : 2048; }
+uint64_t small_lookup_keys(const gleam_cache* c) {
+  return c->key_bound < c->capacity / 4 ? 3072 : c->key_bound < c->capacity / 2 ? 2560 : 2048;
+}
 
 __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableRef t, const uint64_t* keys, uint64_t n,
                                                                      uint8_t* status, uint64_t* ref) {

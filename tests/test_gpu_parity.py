@@ -540,6 +540,55 @@ def test_lookup_at_single_workgroup_limit(n):
     assert {0, 1, 2} <= set(est.tolist())
 
 
+@pytest.mark.parametrize("bound", [0.2, 0.25, 0.4, 0.5, 0.6])
+@pytest.mark.parametrize("n", [2_048, 2_049, 2_560, 2_561, 3_072, 3_073])
+def test_lookup_limits_by_load(n, bound):
+    """Batches on either side of the three sizes up to which one workgroup looks keys up, in
+    tables on either side of the bounds that choose among them; repeats and both special keys."""
+    rng = np.random.default_rng([851, n, int(100 * bound)])
+    cached = rng.permutation(np.arange(int(bound * (1 << 13)), dtype=np.uint64) * np.uint64(0x9E3779B97F4A7C15))
+    pool = np.concatenate([cached[: n // 4], rng.integers(0, 2**64, n // 2, dtype=np.uint64, endpoint=False),
+                           np.array([0, 2**64 - 1], np.uint64)])
+    keys = pool[rng.integers(0, pool.size, n)]
+    say("lookup limits by load", n, bound)
+    table, ot = g.Cache(1 << 13), oracle.Table()
+    table.insert(keys_to_device(cached), keys_to_device(cached))
+    ot.insert(cached, cached)
+    status, ref = table.lookup(keys_to_device(keys))
+    est, eref = oracle.lookup(keys, ot)
+    assert np.array_equal(status.cpu().numpy(), est) and np.array_equal(u64(ref), eref)
+
+
+def test_lookup_cost_follows_load_not_capacity():
+    """2,000 held keys of a table at load 0.05 cost one launch whatever its capacity: 4.5 us
+    in 2^21 and in 2^23 slots, where a limit by capacity made three launches of the latter
+    (12 us)."""
+    rng = np.random.default_rng(852)
+
+    def cost(log2_cap):
+        keys = keys_to_device(rng.integers(0, 2**64, (1 << log2_cap) // 20, dtype=np.uint64, endpoint=False))
+        table = g.Cache(1 << log2_cap)
+        table.insert(keys, keys)
+        q = keys[:2000].contiguous()
+        status, ref = torch.empty(2000, dtype=torch.uint8, device="cuda"), torch.empty_like(q)
+        ws, stream = g.workspace(2000), torch.cuda.current_stream().cuda_stream
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        best = float("inf")
+        for _ in range(6):
+            a.record()
+            for _ in range(100):  # the C call: the binding's own time would hide the launches
+                g._check(g.lib.gleam_cache_lookup(table.handle, q.data_ptr(), 2000, status.data_ptr(),
+                                                  ref.data_ptr(), ws.data_ptr(), ws.numel(), stream))
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    say("lookup cost by load")
+    small, large = cost(21), cost(23)
+    assert large < 1.8 * small, (small, large)
+
+
 def test_capacity_is_enforced():
     table = g.Cache(16, max_load=0.5)  # at most 8 keys
     k = keys_to_device(np.arange(9, dtype=np.uint64))
