@@ -14,12 +14,14 @@
 
 #include "gleam_device.h"
 #include "gleam_internal.h"
+#include "launch_shape.h"
 
 namespace gleam {
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
+static_assert(kThreads == (int)kCopyThreads, "copy_shape's workgroups");
 constexpr int kScanThreads = 1024;
 // The plan's tiles: kThreads consecutive blocks times `rounds` (1, 2, 4 or 8), the
 // fewest rounds that keep the tiles within kPlanTiles, so that a small batch spreads over
@@ -28,23 +30,6 @@ constexpr int kScanThreads = 1024;
 // workgroup scan over tiles of 2,048 blocks and a thread walking 8 blocks at a time.
 constexpr uint64_t kPlanTiles = 2048;
 constexpr uint32_t kPlanRounds = (uint32_t)(kTileItems / kThreads);  // at most 8
-// Copy pieces: one wave copies one piece of a block, a whole piece loaded before its first
-// word is stored. Copying is bound by HBM (one read and one write per byte). Measured on
-// 4 GiB (read + write traffic), four waves per workgroup: 4 KiB per wave (four 16-byte
-// words per lane) 6.0-6.1 TB/s, 16 KiB 5.9-6.0; 8 KiB 5.1, 16 KiB in four rounds 5.5; a
-// 256-thread workgroup striding over 64 KiB with four words per thread 5.4; persistent
-// grids 5.2-5.8. A block of 4 KiB, the small copies' block size, is one piece, so its wave
-// waits for the record once and keeps no other wave waiting.
-// The larger piece is for grids in which most waves find nothing to copy, in blocks of
-// kLargePieceBlock and up: the GPU starts about 1.2 workgroups per ns, so such a grid costs
-// by its size. Packing takes it (held blocks have nothing to pack: a 3.8 GB decoder shard
-// with about a tenth missing 98-148 us against 133-185), and restoring batches of mostly
-// short payloads (20,000 of 12 KB in 64 KiB blocks 92 us against 133); restoring mostly
-// full blocks does not (the shard 1,327 us against 1,262).
-constexpr uint32_t kSmallPiece = 4096, kLargePiece = 16384;
-constexpr uint32_t kLargePieceBlock = 65536;
-constexpr uint64_t kMaxCopyGrid = 1u << 26;  // workgroups of kWaves pieces; a grid-stride loop beyond
-
 __device__ __forceinline__ uint64_t round16(uint64_t n) { return (n + 15) & ~15ull; }
 
 __device__ __forceinline__ uint64_t wave_inclusive_scan64(uint64_t x, int lane) {
@@ -346,22 +331,6 @@ __global__ __launch_bounds__(kThreads) void restore_kernel(const uint64_t* __res
   }
 }
 
-struct CopyGrid {
-  bool large;         // kLargePiece
-  uint32_t per_log2;  // log2 of the pieces per block
-  dim3 grid;
-};
-// `sparse`: many of the blocks may have nothing to copy.
-CopyGrid copy_grid(const gleam_batch* b, bool sparse) {
-  CopyGrid c;
-  c.large = sparse && b->block_bytes >= kLargePieceBlock;
-  c.per_log2 = (uint32_t)log2_exact(b->block_bytes / (c.large ? kLargePiece : kSmallPiece));
-  const uint64_t pieces = b->n_blocks << c.per_log2;  // n_blocks < 2^51 (validate_batch)
-  const uint64_t want = (pieces + kWaves - 1) / kWaves;
-  c.grid = dim3((uint32_t)(want < kMaxCopyGrid ? want : kMaxCopyGrid));
-  return c;
-}
-
 }  // namespace
 // Loads this file's GPU code object on the current device (gleam_preload).
 hipError_t preload_transfer() {
@@ -424,8 +393,8 @@ extern "C" gleam_status gleam_pack_misses(const gleam_batch* b, const gleam_send
     set_error("gleam_pack_misses: null records or output");
     return GLEAM_E_INVALID;
   }
-  const CopyGrid c = copy_grid(b, true);
-  hipLaunchKernelGGL(c.large ? pack_kernel<kLargePiece> : pack_kernel<kSmallPiece>, c.grid, dim3(kThreads), 0,
+  const CopyShape c = copy_shape(b->n_blocks, b->block_bytes, true);
+  hipLaunchKernelGGL(c.large ? pack_kernel<kLargePiece> : pack_kernel<kSmallPiece>, dim3(c.groups), dim3(kThreads), 0,
                      (hipStream_t)stream, b->seg_addr, b->seg_len, b->n_seg, d_records, b->n_blocks, c.per_log2, d_out,
                      out_bytes);
   return launch_status("pack_kernel");
@@ -445,9 +414,9 @@ extern "C" gleam_status gleam_restore_blocks(const gleam_batch* dst, const gleam
   }
   // at most one block of each payload is short: with four blocks per payload or more, at
   // least three in four are full
-  const CopyGrid c = copy_grid(dst, dst->n_blocks / 4 < dst->n_seg);
-  hipLaunchKernelGGL(c.large ? restore_kernel<kLargePiece> : restore_kernel<kSmallPiece>, c.grid, dim3(kThreads), 0,
-                     (hipStream_t)stream, dst->seg_addr, dst->seg_len, dst->n_seg, d_records, dst->n_blocks,
-                     c.per_log2, d_packed, packed_bytes, d_held);
+  const CopyShape c = copy_shape(dst->n_blocks, dst->block_bytes, dst->n_blocks / 4 < dst->n_seg);
+  hipLaunchKernelGGL(c.large ? restore_kernel<kLargePiece> : restore_kernel<kSmallPiece>, dim3(c.groups),
+                     dim3(kThreads), 0, (hipStream_t)stream, dst->seg_addr, dst->seg_len, dst->n_seg, d_records,
+                     dst->n_blocks, c.per_log2, d_packed, packed_bytes, d_held);
   return launch_status("restore_kernel");
 }

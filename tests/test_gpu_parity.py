@@ -586,7 +586,7 @@ def test_lookup_cost_follows_load_not_capacity():
 
     say("lookup cost by load")
     small, large = cost(21), cost(23)
-    assert large < 1.8 * small, (small, large)
+    assert large < 1.5 * small, (small, large)
 
 
 def test_capacity_is_enforced():

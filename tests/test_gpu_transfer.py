@@ -246,6 +246,15 @@ def test_copy_piece_edges(block, reps):
     check_round_trip(payloads, block, held, skew=reps % 3)
 
 
+def test_copies_beyond_one_launch():
+    """66,000 payloads of a few bytes in 16 MiB blocks: 2^24 workgroups' worth of pieces and
+    more, so that the largest launch (2^24 - 1 of them) strides on to the rest."""
+    g0 = np.random.default_rng(18)
+    payloads = [g0.integers(0, 256, int(n), dtype=np.uint8) for n in g0.integers(1, 40, 66_000)]
+    say("copies beyond one launch")
+    check_round_trip(payloads, 16 << 20, [])
+
+
 @pytest.mark.parametrize("n_seg,hi", [(3, 5), (70_000, 3), (300_000, 5), (2000, 6000)])
 def test_plan_tiles(n_seg, hi):
     """The plan's tile sizes (256 to 2,048 blocks) and its three-launch path, on statuses
