@@ -39,6 +39,7 @@
 // computation as the plain bottom-up definition.
 
 #include "fp_core.h"
+#include "launch_shape.h"
 
 namespace gleam {
 namespace {
@@ -227,17 +228,19 @@ __device__ __forceinline__ void leaf_pass_quad(const FpArgs& a, uint64_t slot0, 
 }
 
 // Two lanes per leaf in the first a.items workgroups, four in those after them (as fp_kernel).
+// `first`: the workgroups launched before these.
 template <typename Out>
-__global__ __launch_bounds__(kThreads) void fp_leaf_kernel(FpArgs a, Out out) {
+__global__ __launch_bounds__(kThreads) void fp_leaf_kernel(FpArgs a, uint64_t first, Out out) {
   constexpr int W = kThreads / 64;
   __shared__ __attribute__((aligned(16))) uint8_t lds[W * kWaveLds];
   static_assert(kQuadWaveLds <= kWaveLds, "one tile per wave");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint8_t* tile = lds + wave * kWaveLds;
-  if (blockIdx.x < a.items) {
-    leaf_pass(a, uniform64(((uint64_t)blockIdx.x * W + wave) * kLeavesPerWave), tile, lane, out);
+  const uint64_t group = first + blockIdx.x;
+  if (group < a.items) {
+    leaf_pass(a, uniform64((group * W + wave) * kLeavesPerWave), tile, lane, out);
   } else {
-    const uint64_t slot0 = a.items * W * kLeavesPerWave + ((blockIdx.x - a.items) * W + wave) * kQuadLeaves;
+    const uint64_t slot0 = a.items * W * kLeavesPerWave + ((group - a.items) * W + wave) * kQuadLeaves;
     leaf_pass_quad<false>(a, uniform64(slot0), tile, lane, out);
   }
 }
@@ -371,8 +374,10 @@ gleam_status launch_leaf_compare(const gleam_batch* b, const uint64_t* recorded,
     set_error("fingerprint: batch needs more than 2^31 workgroups");
     return GLEAM_E_UNSUPPORTED;
   }
-  hipLaunchKernelGGL(fp_leaf_kernel<CompareLeaves>, dim3((uint32_t)grid), dim3(kThreads), 0, stream, a, out);
-  return launch_status("fp_leaf_kernel");
+  return launch_in_parts(grid, max_workgroups(kThreads), [&](uint64_t first, uint32_t groups) {
+    hipLaunchKernelGGL(fp_leaf_kernel<CompareLeaves>, dim3(groups), dim3(kThreads), 0, stream, a, first, out);
+    return launch_status("fp_leaf_kernel");
+  });
 }
 
 // Loads this file's GPU code object on the current device (gleam_preload).

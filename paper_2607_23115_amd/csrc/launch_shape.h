@@ -10,6 +10,18 @@ namespace gleam {
 // 256. (Larger ones ran with ROCm 7.2, but nothing says that they have to.)
 constexpr uint64_t max_workgroups(uint32_t threads) { return UINT32_MAX / threads; }
 
+// Calls launch(first, count) for workgroups [first, first + count) of `groups`, at most `most`
+// at once, in order; stops at the first status that is not 0 and returns it.
+template <class Launch>
+int32_t launch_in_parts(uint64_t groups, uint64_t most, const Launch& launch) {
+  for (uint64_t first = 0; first < groups; first += most) {
+    const uint64_t left = groups - first;
+    const int32_t status = launch(first, (uint32_t)(left < most ? left : most));
+    if (status != 0) return status;
+  }
+  return 0;
+}
+
 // Copy pieces: one wave copies one piece of a block, a whole piece loaded before its first
 // word is stored. Copying is bound by HBM (one read and one write per byte). Measured on
 // 4 GiB (read + write traffic), four waves per workgroup: 4 KiB per wave (four 16-byte

@@ -182,3 +182,28 @@ def test_identify_matches_the_digests_of_both_states(shape, block):
         assert np.array_equal(u64(got[1]), want)
         assert got[2].cpu().numpy().tolist() == verdict
     assert np.array_equal(np.flatnonzero(want != oracle.NO_DIFF), change)
+
+
+def test_identify_leaves_beyond_one_launch():
+    """262,145 payloads of a few bytes in 16 MiB blocks, 2^30 leaf slots and 4,096 more: one
+    workgroup for every 64 of them is more than one launch holds. The largest and the last
+    payloads differ, and one in the part of the second launch."""
+    rng = np.random.default_rng(9200)
+    n, block, per = (1 << 18) + 1, 16 << 20, 4096
+    lens = rng.integers(1, 60, n).astype(np.uint64)
+    offs = np.arange(n, dtype=np.uint64) * np.uint64(64)
+    arena = torch.randint(0, 256, (64 * n,), dtype=torch.uint8, device="cuda")
+    batch = g.Batch.from_arena(arena, offs, lens, block)
+    say("identify leaves beyond one launch", batch.n_blocks * per)
+    _, recorded = g.fp_chunks(batch, with_leaves=True)
+    change = np.array([0, int(lens.argmax()), 131_073, n - 2, n - 1])
+    arena[torch.from_numpy(64 * change).cuda()] ^= 1
+    regions = np.append(np.arange(0, n, 1000), n).astype(np.uint64)
+    match, first_diff, weight = g.identify_leaves(batch, recorded, regions)
+    want = np.full(n, oracle.NO_DIFF, np.uint64)
+    want[change] = 0
+    assert np.array_equal(u64(first_diff), want)
+    match = match.reshape(n, per)
+    assert np.array_equal(match[:, 0].cpu().numpy() == 0, want == 0) and bool((match[:, 1:] == 1).all())
+    assert weight.cpu().numpy().tolist() == [int((want[a:b] != 0).all()) for a, b in
+                                             zip(regions[:-1].astype(int), regions[1:].astype(int))]

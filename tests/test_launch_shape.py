@@ -48,3 +48,22 @@ def test_copy_shape(copy_shape, block, sparse):
         assert got_large == (1 if large else 0) and 1 << per_log2 == per, (n, block)
         assert groups == min(-(-n * per // WAVES), MOST), (n, block)
         assert 0 < groups * THREADS < 2**32
+
+
+def test_launch_in_parts(tmp_path):
+    """Parts in order, none larger than the limit, that make up every workgroup once; a failed
+    one is the last."""
+    run = compiled(tmp_path,
+                   "const uint64_t fail = argc > 3 ? arg(3) : ~0ull;\n"
+                   "const int32_t st = launch_in_parts(arg(1), arg(2), [&](uint64_t first, uint32_t count) -> int32_t {\n"
+                   '  printf("%llu %u\\n", (unsigned long long)first, count);\n'
+                   "  return first >= fail ? -4 : 0;\n});\n"
+                   'printf("%d\\n", st);\n')
+    for groups in (0, 1, MOST - 1, MOST, MOST + 1, 2 * MOST, 2**24, 2**31 - 1):
+        *parts, status = run(groups, MOST)
+        at = 0
+        for first, count in zip(parts[::2], parts[1::2]):
+            assert first == at and 0 < count <= MOST
+            at += count
+        assert at == groups and status == 0 and len(parts) // 2 == -(-groups // MOST)
+    assert run(50, 20, 20) == [0, 20, 20, 20, -4]
