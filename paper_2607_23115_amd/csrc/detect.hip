@@ -74,11 +74,13 @@ __device__ __forceinline__ uint32_t wg_exclusive_scan(uint32_t x, uint32_t* wave
 }
 
 // Stores a block's digest and probes the table for it (in the lane that computed it).
-struct TableProbe {
+struct TableProbe : NothingBefore {
   TableRef t;
   uint8_t* status;
   uint64_t* ref;
-  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t key, uint64_t) const {
+  __device__ TableProbe(const TableRef& table, uint8_t* st, uint64_t* rf) : t(table), status(st), ref(rf) {}
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t key, uint64_t,
+                                             Before, bool = false) const {
     if (!valid) return;
     a.block_out[g] = key;
     uint64_t val = 0;
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(64 * W) void detect_small_kernel(DetectArgs a) {
   __shared__ uint64_t wave_bytes[W];
 
   // digests, block lengths, and each block's table probe
-  quad_pass<W, true, W == 1>(a.fp, blockIdx.x, lds, a.blen, TableProbe{a.t, a.status, a.ref});
+  quad_pass<W, true, W == 1>(a.fp, blockIdx.x, lds, a.blen, TableProbe(a.t, a.status, a.ref));
   // Arrive. Each thread waits for its own stores (digests, lengths, statuses) to
   // complete; after the barrier one release at device scope per workgroup writes them
   // back from this XCD's L2, and the arrival counts. (A device-scope fence in every wave

@@ -79,6 +79,8 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       const uint64_t g = slot >> L2;
       const uint32_t k = (uint32_t)(slot & (lpb - 1));
       const Leaf lf = locate_wave(a, wave_slot0 >> L2, g, k, lane);
+      const bool valid = lpb <= kLeavesPerWave && even && k == 0 && g < a.n_blocks;
+      const typename Out::Before before_hash = out.before(valid, g);
       const uint64_t d = hash_slot(lf, tile, lane);
       if (a.leaf_out && even && g < a.n_blocks) a.leaf_out[slot] = lf.len ? d : 0;
       const uint32_t G = lpb <= kLeavesPerWave ? lpb : (uint32_t)kLeavesPerWave;
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       }
       const uint64_t v = tree_reduce_lanes(d, p, n, G, 2);
       if (lpb <= kLeavesPerWave) {
-        out(a, even && p == 0 && g < a.n_blocks, g, v, lf.seg);
+        out(a, valid, g, v, lf.seg, before_hash);
       } else {
         if (lane == 0) roots[0][wave] = v;
         __syncthreads();
@@ -101,12 +103,14 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
           uint32_t n2 = 0;
           uint64_t v2 = 0;
           const Leaf head = locate_wave(a, (item * GROUP) >> L2, g2, 0, lane);
+          const bool valid2 = lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks;
+          const typename Out::Before before2 = out.before(valid2, g2);
           if (lane < W && g2 < a.n_blocks) {
             n2 = (head.blk_leaves + kLeavesPerWave - 1) / kLeavesPerWave;
             v2 = roots[0][lane];
           }
           v2 = tree_reduce_lanes(v2, lane & (G2 - 1), n2, G2);
-          out(a, lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks, g2, v2, head.seg);
+          out(a, valid2, g2, v2, head.seg, before2);
         }
       }
     } else {
@@ -115,6 +119,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       const uint64_t s0 = uniform64(find_segment(a.blk_first, a.n_seg, g));
       const Leaf head = locate(a, g, 0, s0);
       const uint32_t nleaf = head.blk_leaves;
+      const typename Out::Before before_hash = out.before(threadIdx.x == 0, g);
       const uint32_t groups = a.leaf_out ? lpb / GROUP : (nleaf + GROUP - 1) / GROUP;
       for (uint32_t grp = 0; grp < groups; ++grp) {
         const uint32_t k = grp * GROUP + (uint32_t)wave * kLeavesPerWave + (lane >> 1);
@@ -130,7 +135,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       if (wave == 0) {
         const uint32_t n2 = (nleaf + kLeavesPerWave - 1) / kLeavesPerWave;  // <= kMaxRoots
         const uint64_t r = tree_reduce_lds(roots[0], roots[1], n2, lane);
-        out(a, lane == 0, g, r, head.seg);
+        out(a, lane == 0, g, r, head.seg, before_hash, true);
       }
     }
   }
@@ -151,17 +156,28 @@ __global__ __launch_bounds__(64 * W) void fp_quad_kernel(FpArgs a, Out out) {
 // memory, and no second pass reads them (30,000 small copies: 80.6 to 76.4 us a call; 2.9 GB
 // of a decoder in 1 MiB blocks, located to the leaf: 474 to 428 us, most of it from
 // leaf_pass). A lane keeps the payload it found when it located its leaf: searching for it
-// again where digests differ cost the small copies 6 us.
-//
-// first_diff[s] = min(first_diff[s], x) for the lanes with `differs`. When every such lane
-// of the wave lies in one payload (all but the waves at payload boundaries), the wave
-// takes the minimum itself and one lane issues the atomic, unless the word is already as
-// low: a payload whose blocks all changed (a layer updated in place) would otherwise queue
-// one atomic per block on its word (262,144 leaves of one payload: 3.2 ms). Every lane of
-// the wave calls it.
-__device__ __forceinline__ void lower_first_diff(uint64_t* first_diff, uint64_t s, bool differs, uint64_t x) {
+// again where digests differ cost the small copies 6 us. The recorded digest is read before
+// the leaves are hashed: a wave that reads it at its end keeps its LDS, and with it the next
+// workgroup, waiting for a round trip of memory.
+struct FirstDiff {
+  uint64_t s, at;
+};
+
+// first_diff[s] = min(first_diff[s], x) for the lanes with `differs`. When every such lane of
+// the wave lies in one payload (all but the waves at payload boundaries), the wave takes the
+// minimum itself and one lane issues the atomic, unless the word is already as low: a payload
+// whose blocks all changed (a layer updated in place) would otherwise queue one atomic per
+// block on its word (262,144 leaves of one payload: 3.2 ms). That word is read at the end
+// (read before hashing, the waves that start together all find it high and queue: 425 us for
+// 1 GB changed throughout in 4 KiB blocks), and those reads queue too: 203 us with one for
+// each wave, 175 where the four waves of a workgroup leave their differences in `late` for one
+// (Compare::finish), 182 with the comparison in a pass of its own. Where the calls are `rare`,
+// one for a whole block of 1 MiB or more, the word is not read. Every lane of the wave calls it.
+__device__ __forceinline__ void lower_first_diff(uint64_t* first_diff, uint64_t s, bool differs, uint64_t x,
+                                                 bool rare, FirstDiff* late) {
   const int lane = threadIdx.x & 63;
   const uint64_t active = __ballot(differs);
+  if (late && lane == 0) late->at = ~0ull;
   if (active == 0) return;  // the wave
   const int leader = __ffsll((unsigned long long)active) - 1;
   const uint64_t s0 = shfl64(s, leader);
@@ -174,34 +190,61 @@ __device__ __forceinline__ void lower_first_diff(uint64_t* first_diff, uint64_t 
       m = y < m ? y : m;
     }
     issue = lane == leader;
+    if (late) {
+      if (issue) *late = FirstDiff{s, m};
+      return;
+    }
+  } else {
+    rare = true;
   }
-  if (issue && m < __hip_atomic_load(&first_diff[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+  if (issue && (rare || m < __hip_atomic_load(&first_diff[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
     atomicMin(reinterpret_cast<unsigned long long*>(&first_diff[s]), (unsigned long long)m);
 }
 
-// Block g: equal digests? The first differing block of each payload.
-struct CompareBlocks {
+struct Compare {
   const uint64_t* recorded;
   uint8_t* match;  // nullable
   uint64_t* first_diff;
-  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t v, uint64_t s) const {
-    const bool same = !valid || recorded[g] == v;
+  typedef uint64_t Before;  // the recorded digest
+  // The waves' differences, for one read of the payload's word instead of one per wave.
+  static constexpr bool kFinishes = true;
+  template <int W>
+  struct Late {
+    FirstDiff wave[W];
+  };
+  // Every thread of the workgroup calls it. Later waves hold later slots.
+  template <int W>
+  __device__ __forceinline__ void finish(const Late<W>& late) const {
+    __syncthreads();
+    if (threadIdx.x >= W) return;
+    const FirstDiff mine = late.wave[threadIdx.x];
+    bool issue = mine.at != ~0ull;
+    for (uint32_t w = 0; w < threadIdx.x; ++w) issue = issue && !(late.wave[w].s == mine.s && late.wave[w].at != ~0ull);
+    if (issue && mine.at < __hip_atomic_load(&first_diff[mine.s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMin(reinterpret_cast<unsigned long long*>(&first_diff[mine.s]), (unsigned long long)mine.at);
+  }
+  __device__ __forceinline__ uint64_t before(bool valid, uint64_t at) const { return valid ? recorded[at] : 0; }
+};
+
+// Block g: equal digests? The first differing block of each payload.
+struct CompareBlocks : Compare {
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t v, uint64_t s,
+                                             uint64_t was, bool rare = false, FirstDiff* late = nullptr) const {
+    const bool same = !valid || was == v;
     if (valid && match) match[g] = same ? 1 : 0;
-    lower_first_diff(first_diff, s, !same, same ? 0 : g - a.blk_first[s]);
+    lower_first_diff(first_diff, s, !same, same ? 0 : g - a.blk_first[s], rare, late);
   }
 };
 
 // Leaf slot (slot = g * LPB + k): equal digests? Slots past a short block's last leaf hold 0
 // on both sides, so they always agree. The first differing leaf of each payload by its index
 // within the payload, (g - blk_first[s]) * LPB + k.
-struct CompareLeaves {
-  const uint64_t* recorded;
-  uint8_t* match;  // nullable
-  uint64_t* first_diff;
-  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t slot, uint64_t v, uint64_t s) const {
-    const bool same = !valid || recorded[slot] == v;
+struct CompareLeaves : Compare {
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t slot, uint64_t v, uint64_t s,
+                                             uint64_t was, bool rare = false, FirstDiff* late = nullptr) const {
+    const bool same = !valid || was == v;
     if (valid && match) match[slot] = same ? 1 : 0;
-    lower_first_diff(first_diff, s, !same, same ? 0 : slot - (a.blk_first[s] << a.lpb_log2));
+    lower_first_diff(first_diff, s, !same, same ? 0 : slot - (a.blk_first[s] << a.lpb_log2), rare, late);
   }
 };
 
@@ -209,22 +252,27 @@ struct CompareLeaves {
 // same few slots in blocks of any size (1 MiB blocks by whole blocks end unevenly: 2,829 of
 // them are 11.05 rounds of the 256 CUs). `slot0` in slots.
 template <typename Out>
-__device__ __forceinline__ void leaf_pass(const FpArgs& a, uint64_t slot0, uint8_t* tile, int lane, const Out& out) {
+__device__ __forceinline__ void leaf_pass(const FpArgs& a, uint64_t slot0, uint8_t* tile, int lane, const Out& out,
+                                          FirstDiff* late) {
   const uint64_t slot = slot0 + (lane >> 1), g = slot >> a.lpb_log2;
   const uint32_t k = (uint32_t)(slot & ((1u << a.lpb_log2) - 1));
   const Leaf lf = locate_wave(a, slot0 >> a.lpb_log2, g, k, lane);
+  const bool valid = (lane & 1) == 0 && g < a.n_blocks;
+  const typename Out::Before before = out.before(valid, slot);
   const uint64_t d = hash_slot(lf, tile, lane);
-  out(a, (lane & 1) == 0 && g < a.n_blocks, slot, lf.len ? d : 0, lf.seg);
+  out(a, valid, slot, lf.len ? d : 0, lf.seg, before, false, late);
 }
 
 template <bool kDirect, typename Out>
 __device__ __forceinline__ void leaf_pass_quad(const FpArgs& a, uint64_t slot0, uint8_t* tile, int lane,
-                                               const Out& out) {
+                                               const Out& out, FirstDiff* late = nullptr) {
   const uint64_t slot = slot0 + (lane >> 2), g = slot >> a.lpb_log2;
   const uint32_t k = (uint32_t)(slot & ((1u << a.lpb_log2) - 1));
   const Leaf lf = locate_wave(a, slot0 >> a.lpb_log2, g, k, lane);
+  const bool valid = (lane & 3) == 0 && g < a.n_blocks;
+  const typename Out::Before before = out.before(valid, slot);
   const uint64_t d = kDirect ? hash_slot_quad_direct(lf, tile, lane) : hash_slot_quad(lf, tile, lane);
-  out(a, (lane & 3) == 0 && g < a.n_blocks, slot, lf.len ? d : 0, lf.seg);
+  out(a, valid, slot, lf.len ? d : 0, lf.seg, before, false, late);
 }
 
 // Two lanes per leaf in the first a.items workgroups, four in those after them (as fp_kernel).
@@ -236,13 +284,15 @@ __global__ __launch_bounds__(kThreads) void fp_leaf_kernel(FpArgs a, uint64_t fi
   static_assert(kQuadWaveLds <= kWaveLds, "one tile per wave");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint8_t* tile = lds + wave * kWaveLds;
+  __shared__ typename Out::template Late<W> late;
   const uint64_t group = first + blockIdx.x;
   if (group < a.items) {
-    leaf_pass(a, uniform64((group * W + wave) * kLeavesPerWave), tile, lane, out);
+    leaf_pass(a, uniform64((group * W + wave) * kLeavesPerWave), tile, lane, out, &late.wave[wave]);
   } else {
     const uint64_t slot0 = a.items * W * kLeavesPerWave + ((group - a.items) * W + wave) * kQuadLeaves;
-    leaf_pass_quad<false>(a, uniform64(slot0), tile, lane, out);
+    leaf_pass_quad<false>(a, uniform64(slot0), tile, lane, out, &late.wave[wave]);
   }
+  out.finish(late);
 }
 
 // One-wave workgroups, every stage at once into LDS.
@@ -345,7 +395,7 @@ gleam_status launch_fp(const gleam_batch* b, uint64_t* d_block_digest, uint64_t*
 
 gleam_status launch_fp_compare(const gleam_batch* b, const uint64_t* recorded, uint8_t* match, uint64_t* first_diff,
                                hipStream_t stream) {
-  return launch_fp_out(b, nullptr, nullptr, CompareBlocks{recorded, match, first_diff}, stream);
+  return launch_fp_out(b, nullptr, nullptr, CompareBlocks{{recorded, match, first_diff}}, stream);
 }
 
 // The launch rules of launch_fp for blocks of up to 64 KiB, here for blocks of any size.
@@ -354,7 +404,7 @@ gleam_status launch_leaf_compare(const gleam_batch* b, const uint64_t* recorded,
   if (b->n_blocks == 0) return GLEAM_OK;
   const int lpb_log2 = log2_exact(b->block_bytes) - 12;
   const uint64_t slots = b->n_blocks << lpb_log2;
-  const CompareLeaves out{recorded, match, first_diff};
+  const CompareLeaves out{{recorded, match, first_diff}};
   FpArgs a{b->seg_addr, b->seg_len, b->blk_first, b->n_seg, b->n_blocks, nullptr, nullptr, (uint32_t)lpb_log2, 0};
   if (slots <= kQuadMaxSlots) {
     int cus = 0;

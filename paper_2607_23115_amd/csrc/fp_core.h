@@ -533,13 +533,22 @@ __device__ __forceinline__ uint64_t hash_slot_quad_direct(const Leaf& lf, uint8_
 // and aligned waves load every stage at once; otherwise kQuadWaveLds per wave.
 //
 // `out` takes the block digests: every lane of the wave calls it, with `valid` in the lanes
-// that hold a digest, and the payload that the block lies in. The one-launch detect path also probes the resident table there (its
+// that hold a digest, the payload that the block lies in, and what out.before(valid,
+// g) returned before the leaves were hashed (a read that would otherwise keep the wave
+// waiting at its end). The one-launch detect path also probes the resident table there (its
 // latency overlapping other waves' streaming): a held digest gets status HIT_CACHE and its
 // value as ref; any other gets kProbePending.
 constexpr uint8_t kProbePending = 0xFF;
 
-struct StoreBlocks {
-  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t v, uint64_t) const {
+struct NothingBefore {
+  static constexpr bool kFinishes = false;
+  struct Before {};
+  __device__ __forceinline__ Before before(bool, uint64_t) const { return {}; }
+};
+
+struct StoreBlocks : NothingBefore {
+  __device__ __forceinline__ void operator()(const FpArgs& a, bool valid, uint64_t g, uint64_t v, uint64_t, Before,
+                                             bool = false) const {
     if (valid) a.block_out[g] = v;
   }
 };
@@ -558,12 +567,19 @@ __device__ __forceinline__ void quad_pass(const FpArgs& a, uint64_t group, uint8
   const uint64_t g = slot >> L2;
   const uint32_t k = (uint32_t)(slot & (lpb - 1));
   const Leaf lf = locate_wave(a, wave_slot0 >> L2, g, k, lane);
+  const bool head = (lane & 3) == 0, valid = head && k == 0 && g < a.n_blocks;
+  const typename Out::Before before = out.before(valid, g);
   const uint64_t d = kDirect ? hash_slot_quad_direct(lf, lds, lane) : hash_slot_quad(lf, lds + wave * kQuadWaveLds, lane);
-  const bool head = (lane & 3) == 0;
   if (a.leaf_out && head && g < a.n_blocks) a.leaf_out[slot] = lf.len ? d : 0;
   if (kLen && head && g < a.n_blocks && lf.len && k + 1 == lf.blk_leaves) blen[g] = (k << 12) + lf.len;
   const uint64_t v = tree_reduce_lanes(d, k, lf.blk_leaves, lpb, 4);
-  out(a, head && k == 0 && g < a.n_blocks, g, v, lf.seg);
+  if constexpr (Out::kFinishes && W > 1) {
+    __shared__ typename Out::template Late<W> late;
+    out(a, valid, g, v, lf.seg, before, false, &late.wave[wave]);
+    out.finish(late);
+  } else {
+    out(a, valid, g, v, lf.seg, before);
+  }
 }
 
 }  // namespace
