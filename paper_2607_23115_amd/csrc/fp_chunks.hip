@@ -47,6 +47,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kSoloPad = 24 << 10;  // takes the workgroup's LDS past 80 KiB: one per CU
 constexpr uint64_t kQuadTailSlots = 16384;
+constexpr uint64_t kSparseUnits = 2048;
 
 template <bool kSolo, typename Out>
 __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
@@ -246,6 +247,32 @@ struct CompareLeaves : Compare {
     if (valid && match) match[slot] = same ? 1 : 0;
     lower_first_diff(first_diff, s, !same, same ? 0 : slot - (a.blk_first[s] << a.lpb_log2), rare, late);
   }
+  // Slots [slot0, end) of payload s, which hold no leaf: 0 on this side. Every thread of the
+  // workgroup calls it; end - slot0 is a multiple of 128.
+  __device__ __forceinline__ void absent(const FpArgs& a, uint64_t slot0, uint64_t end, uint64_t s) const {
+    constexpr int kEach = 4;
+    for (uint64_t at = slot0; at < end; at += kEach * kThreads) {
+      uint64_t r[kEach], any = 0;
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) {  // unconditional (clamped) loads, issued together
+        const uint64_t slot = at + (uint64_t)j * kThreads + threadIdx.x;
+        r[j] = recorded[slot < end ? slot : end - 1];
+      }
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) {
+        const uint64_t slot = at + (uint64_t)j * kThreads + threadIdx.x;
+        if (slot >= end) r[j] = 0;
+        else if (match) match[slot] = r[j] == 0 ? 1 : 0;
+        any |= r[j];
+      }
+      if (!__any(any != 0)) continue;  // as it is unless the recorded digests are of other payloads
+#pragma unroll
+      for (int j = 0; j < kEach; ++j) {
+        const uint64_t slot = at + (uint64_t)j * kThreads + threadIdx.x;
+        lower_first_diff(first_diff, s, r[j] != 0, slot - (a.blk_first[s] << a.lpb_log2), false, nullptr);
+      }
+    }
+  }
 };
 
 // The leaf digests of one wave's consecutive slots alone: no tree, so a workgroup takes the
@@ -293,6 +320,39 @@ __global__ __launch_bounds__(kThreads) void fp_leaf_kernel(FpArgs a, uint64_t fi
     leaf_pass_quad<false>(a, uniform64(slot0), tile, lane, out, &late.wave[wave]);
   }
   out.finish(late);
+}
+
+// Blocks of which most are short: a workgroup takes 1 << unit_log2 consecutive slots of one
+// block (128 to lpb), finds the block's payload once, hashes its leaves 128 slots at a time and
+// reads past the slots that hold none. The blocks' first units come first, then their second
+// ones: those with leaves are then spread over the XCDs, to which workgroups go in turn (of
+// four units a block, the first with all its leaves, they would go to two of the eight).
+// 20,000 payloads of 12 KB in 1 MiB blocks 0.86 ms, in 16 MiB blocks 1.17 (with a workgroup, and
+// a search for the payload in each of its waves, for every 64 slots 2.3 and 21; with the slots
+// written by the fingerprint kernel and compared in a pass of their own 1.75 and 4.2).
+template <typename Out>
+__global__ __launch_bounds__(kThreads) void fp_leaf_sparse_kernel(FpArgs a, uint64_t first, uint32_t unit_log2,
+                                                                  Out out) {
+  constexpr int W = kThreads / 64;
+  constexpr uint32_t GROUP = W * kLeavesPerWave;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[W * kWaveLds];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint8_t* tile = lds + wave * kWaveLds;
+  const uint64_t unit = first + blockIdx.x, part = unit / a.n_blocks, g = unit - part * a.n_blocks;
+  const uint64_t base = g << a.lpb_log2;
+  const uint64_t s = uniform64(wave_find_segment(a.blk_first, a.n_seg, g, lane));
+  const uint32_t leaves = locate_at(a, g, 0, s).blk_leaves;
+  uint32_t k = (uint32_t)part << unit_log2;
+  const uint32_t end = k + (1u << unit_log2);
+  for (; k < end && k < leaves; k += GROUP) {
+    const uint32_t mine = k + (uint32_t)wave * kLeavesPerWave + (lane >> 1);
+    const Leaf lf = locate_at(a, g, mine, s);
+    const bool valid = (lane & 1) == 0;
+    const typename Out::Before before = out.before(valid, base + mine);
+    const uint64_t d = hash_slot(lf, tile, lane);
+    out(a, valid, base + mine, lf.len ? d : 0, s, before);
+  }
+  out.absent(a, base + k, base + end, s);
 }
 
 // One-wave workgroups, every stage at once into LDS.
@@ -417,7 +477,24 @@ gleam_status launch_leaf_compare(const gleam_batch* b, const uint64_t* recorded,
     }
   }
   constexpr uint64_t group = (kThreads / 64) * kLeavesPerWave, quad_group = (kThreads / 64) * kQuadLeaves;
-  if (slots > kQuadMaxSlots && (slots / kQuadLargePayloadSlots < b->n_seg || slots / quad_group >= 0x7fffffffull))
+  // Fewer than four blocks per payload: a quarter of the blocks or more may be short. The units
+  // are 128 to 1,024 slots, as large as leaves kSparseUnits of them, four for every workgroup
+  // that the GPU holds (2,000 payloads of 300 KB in 4 MiB blocks: 117 us, 850 with 64 slots);
+  // smaller batches have idle CUs to spare.
+  if (slots > kQuadMaxSlots && b->n_blocks / 4 < b->n_seg && slots / group >= kSparseUnits && lpb_log2 >= 7) {
+    uint32_t unit_log2 = 7;
+    while (unit_log2 < 10 && unit_log2 < (uint32_t)lpb_log2 && slots >> (unit_log2 + 1) >= kSparseUnits) ++unit_log2;
+    return launch_in_parts(slots >> unit_log2, max_workgroups(kThreads), [&](uint64_t first, uint32_t groups) {
+      hipLaunchKernelGGL(fp_leaf_sparse_kernel<CompareLeaves>, dim3(groups), dim3(kThreads), 0, stream, a, first,
+                         unit_log2, out);
+      return launch_status("fp_leaf_sparse_kernel");
+    });
+  }
+  // Two lanes per leaf where payloads average fewer than kQuadLargePayloadSlots slots, or 1.5
+  // blocks, which may be nearly empty (100,000 payloads of 300 bytes in 256 KiB blocks: 537 us,
+  // 1,111 with four lanes).
+  if (slots > kQuadMaxSlots && (slots / kQuadLargePayloadSlots < b->n_seg ||
+                                b->n_blocks - b->n_blocks / 3 < b->n_seg || slots / quad_group >= 0x7fffffffull))
     a.items = (slots - kQuadTailSlots) / group;
   const uint64_t grid = a.items + (slots - a.items * group + quad_group - 1) / quad_group;
   if (grid > 0x7fffffffull) {

@@ -184,6 +184,67 @@ def test_identify_matches_the_digests_of_both_states(shape, block):
     assert np.array_equal(np.flatnonzero(want != oracle.NO_DIFF), change)
 
 
+@pytest.mark.parametrize("block,n", [(256 << 10, 3000), (512 << 10, 2100), (1 << 20, 1100), (4 << 20, 300),
+                                     (16 << 20, 150), (16 << 20, 700)])
+def test_identify_leaves_of_short_blocks(block, n):
+    """Payloads far shorter than their blocks between some of several blocks, in every unit
+    size of the launch for such batches: the matches (also of slots that hold no leaf, where
+    the recorded digests name one), first differences and verdicts are those of the digests."""
+    rng = np.random.default_rng([9300, block, n])
+    lens = rng.choice([0, 1, 4095, 4097, 20_000, 127 * 4096, 128 * 4096, 128 * 4096 + 1, block - 1, block, block + 1,
+                       2 * block + 5000], n, p=[.1, .1, .2, .2, .3] + [.1 / 7] * 7).astype(np.uint64)
+    offs = np.concatenate([[0], np.cumsum((lens + np.uint64(15)) // np.uint64(16) * np.uint64(16))[:-1]]).astype(np.uint64)
+    arena = torch.randint(0, 256, (int(offs[-1] + lens[-1]) + 16,), dtype=torch.uint8, device="cuda")
+    batch = g.Batch.from_arena(arena, offs, lens, block)
+    per, first = batch.leaves_per_block, batch.host_first.astype(np.int64)
+    say("identify leaves of short blocks", block, n, "slots", batch.n_blocks * per)
+    _, recorded = g.fp_chunks(batch, with_leaves=True)
+    change = np.flatnonzero((rng.random(n) < 0.3) & (lens > 0))
+    at = (offs[change] + (rng.random(change.size) * lens[change]).astype(np.uint64)).astype(np.int64)
+    arena[torch.from_numpy(at).cuda()] ^= 1
+    _, current = g.fp_chunks(batch, with_leaves=True)
+    stray = torch.from_numpy(rng.integers(0, batch.n_blocks * per, 25)).cuda()  # mostly slots without a leaf
+    recorded[stray] ^= 77
+    regions = np.append(np.arange(0, n, 7), n).astype(np.uint64)
+    match, first_diff, weight = g.identify_leaves(batch, recorded, regions)
+    same = recorded == current
+    assert torch.equal(match.reshape(-1) != 0, same.reshape(-1))
+    bad = torch.nonzero(~same.reshape(-1)).reshape(-1).cpu().numpy()
+    seg = np.searchsorted(first, bad // per, side="right") - 1
+    want = np.full(n, oracle.NO_DIFF, np.uint64)
+    np.minimum.at(want, seg, (bad - first[seg] * per).astype(np.uint64))
+    assert np.array_equal(u64(first_diff), want)
+    assert weight.cpu().numpy().tolist() == [int(np.all(want[a:b] == oracle.NO_DIFF))
+                                             for a, b in zip(regions[:-1].astype(int), regions[1:].astype(int))]
+
+
+def test_identify_leaves_cost_follows_the_leaves():
+    """5,000 payloads of 12 KB in 16 MiB blocks, 15,000 leaves in 20 M slots: locating changes
+    to the leaf costs less than comparing whole blocks (0.7 times); with a workgroup for every
+    64 slots it cost 13 times as much. The bound lies between."""
+    n, block = 5000, 16 << 20
+    arena = torch.randint(0, 256, (n * 12_288,), dtype=torch.uint8, device="cuda")
+    batch = g.Batch.from_arena(arena, np.arange(n, dtype=np.uint64) * np.uint64(12_288), np.full(n, 12_000, np.uint64), block)
+    blocks, leaves = g.fp_chunks(batch, with_leaves=True)
+    regions = np.array([0, n], np.uint64)
+    ws = g.workspace(leaves.numel() + n)
+    say("identify leaves cost")
+
+    def cost(call, recorded):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        best = float("inf")
+        for _ in range(4):
+            a.record()
+            call(batch, recorded, regions, ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    whole, located = cost(g.identify_weights, blocks), cost(g.identify_leaves, leaves)
+    assert located < 3 * whole, (whole, located)
+
+
 def test_identify_leaves_beyond_one_launch():
     """262,145 payloads of a few bytes in 16 MiB blocks, 2^30 leaf slots and 4,096 more: one
     workgroup for every 64 of them is more than one launch holds. The largest and the last
