@@ -154,7 +154,7 @@ gleam_status gleam_batch_geometry(const uint64_t* host_seg_len, uint64_t n_seg, 
  *                   block-major; slots past a short block's last leaf get 0
  * Errors: GLEAM_E_INVALID (null b, null descriptor or output with n_blocks > 0,
  * leaf_bytes != 4096, bad block_bytes, n_blocks > 0 with n_seg == 0),
- * GLEAM_E_UNSUPPORTED (a grid beyond 2^31 workgroups), GLEAM_E_HIP.
+ * GLEAM_E_UNSUPPORTED (a grid of 2^24 workgroups or more), GLEAM_E_HIP.
  * n_blocks == 0 is a no-op.
  */
 gleam_status gleam_fp_chunks(const gleam_batch* b, uint64_t* d_block_digest, uint64_t* d_leaf_digest,
@@ -199,7 +199,7 @@ size_t gleam_workspace_bytes(uint64_t n);
  * Capacity is enforced on the host without a device sync: if key_bound + n could
  * exceed the maximum load, GLEAM_E_CAPACITY is returned and nothing is inserted.
  * Errors: GLEAM_E_INVALID, GLEAM_E_CAPACITY, GLEAM_E_WORKSPACE, GLEAM_E_UNSUPPORTED (n
- * above 2^31 workgroups of 256 keys, or 2^40), GLEAM_E_HIP.
+ * above 2^24 - 1 workgroups of 256 keys), GLEAM_E_HIP.
  */
 gleam_status gleam_cache_insert(gleam_cache* c, const uint64_t* d_keys, const uint64_t* d_vals, uint64_t n,
                                 uint64_t* d_n_new, void* d_ws, size_t ws_bytes, void* stream);
@@ -211,8 +211,8 @@ gleam_status gleam_cache_insert(gleam_cache* c, const uint64_t* d_keys, const ui
  *   d_ref     nullable device u64[n] output (see the status enum)
  *   d_ws      device workspace, 256-byte aligned, >= gleam_workspace_bytes(n)
  * The table is only read.
- * Errors: GLEAM_E_INVALID, GLEAM_E_WORKSPACE, GLEAM_E_UNSUPPORTED (n above 2^31
- * workgroups of 256 keys, or 2^40), GLEAM_E_HIP. n == 0 is a no-op.
+ * Errors: GLEAM_E_INVALID, GLEAM_E_WORKSPACE, GLEAM_E_UNSUPPORTED (n above 2^24 - 1
+ * workgroups of 256 keys), GLEAM_E_HIP. n == 0 is a no-op.
  */
 gleam_status gleam_cache_lookup(const gleam_cache* c, const uint64_t* d_keys, uint64_t n, uint8_t* d_status,
                                 uint64_t* d_ref, void* d_ws, size_t ws_bytes, void* stream);
@@ -246,8 +246,8 @@ gleam_status gleam_cache_lookup_noalloc(const gleam_cache* c, const uint64_t* d_
  *   d_miss_count  device u64[1] output
  *   d_miss_bytes  nullable device u64[1] output: total bytes of those blocks
  *   d_ws          device workspace, 256-byte aligned, >= gleam_workspace_bytes(n)
- * Errors: GLEAM_E_INVALID, GLEAM_E_WORKSPACE, GLEAM_E_UNSUPPORTED (n above 2^40),
- * GLEAM_E_HIP. With n == 0 the counters are still set to 0.
+ * Errors: GLEAM_E_INVALID, GLEAM_E_WORKSPACE, GLEAM_E_UNSUPPORTED (n above 2^24 - 1 tiles
+ * of 2048), GLEAM_E_HIP. With n == 0 the counters are still set to 0.
  */
 gleam_status gleam_miss_compact(const uint8_t* d_status, uint64_t n, const gleam_batch* b, uint64_t* d_miss_idx,
                                 uint64_t* d_miss_count, uint64_t* d_miss_bytes, void* d_ws, size_t ws_bytes,

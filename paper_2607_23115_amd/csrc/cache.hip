@@ -21,6 +21,7 @@
 #include "gleam_device.h"
 #include "gleam_internal.h"
 #include "gleam_table.h"
+#include "launch_shape.h"
 
 namespace gleam {
 namespace {
@@ -572,8 +573,8 @@ extern "C" gleam_status gleam_cache_insert(gleam_cache* c, const uint64_t* d_key
   const WsLayout L = ws_layout(n);
   gleam_status st = check_workspace(L, d_ws, ws_bytes, "gleam_cache_insert");
   if (st != GLEAM_OK) return st;
-  if (n > 0x7fffffffull * kThreads) {
-    set_error("gleam_cache_insert: more than 2^31 workgroups of keys");
+  if (n > max_workgroups(kThreads) * kThreads) {
+    set_error("gleam_cache_insert: more keys than one launch has threads (2^32)");
     return GLEAM_E_UNSUPPORTED;
   }
   if (n > c->max_keys || c->key_bound > c->max_keys - n) {
@@ -621,8 +622,8 @@ extern "C" gleam_status gleam_cache_lookup(const gleam_cache* c, const uint64_t*
   const WsLayout L = ws_layout(n);
   gleam_status st = check_workspace(L, d_ws, ws_bytes, "gleam_cache_lookup");
   if (st != GLEAM_OK) return st;
-  if (n > 0x7fffffffull * kThreads) {
-    set_error("gleam_cache_lookup: more than 2^31 workgroups of keys");
+  if (n > max_workgroups(kThreads) * kThreads) {
+    set_error("gleam_cache_lookup: more keys than one launch has threads (2^32)");
     return GLEAM_E_UNSUPPORTED;
   }
   hipStream_t s = (hipStream_t)stream;

@@ -17,6 +17,7 @@
 
 #include "gleam_device.h"
 #include "gleam_internal.h"
+#include "launch_shape.h"
 
 namespace gleam {
 namespace {
@@ -304,8 +305,8 @@ extern "C" gleam_status gleam_miss_compact(const uint8_t* d_status, uint64_t n, 
   const WsLayout L = ws_layout(n);
   gleam_status st = check_workspace(L, d_ws, ws_bytes, "gleam_miss_compact");
   if (st != GLEAM_OK) return st;
-  if (L.tiles > 0x7fffffffull) {
-    set_error("gleam_miss_compact: more than 2^31 tiles");
+  if (L.tiles > max_workgroups(kThreads)) {
+    set_error("gleam_miss_compact: more tiles than one launch has workgroups (2^24)");
     return GLEAM_E_UNSUPPORTED;
   }
   hipStream_t s = (hipStream_t)stream;

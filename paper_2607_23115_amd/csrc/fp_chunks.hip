@@ -393,11 +393,11 @@ gleam_status launch_fp_out(const gleam_batch* b, uint64_t* d_block_digest, uint6
   const int lpb_log2 = log2_exact(b->block_bytes) - 12;
   const uint64_t lpb = 1ull << lpb_log2;
   const uint64_t slots = b->n_blocks * lpb;  // n_blocks < 2^51: no overflow
-  // (a large batch takes the four-lanes kernel only while its grid of one 4-wave
-  // workgroup per 64 slots stays below 2^31)
+  // (a large batch takes the four-lanes kernel only while one launch holds its grid of one
+  // 4-wave workgroup per 64 slots)
   if (lpb <= (uint64_t)kQuadLeaves &&
       (slots <= kQuadMaxSlots ||
-       (slots / kQuadLargePayloadSlots >= b->n_seg && slots / (4 * kQuadLeaves) < 0x7fffffffull))) {
+       (slots / kQuadLargePayloadSlots >= b->n_seg && slots / (4 * kQuadLeaves) < max_workgroups(kThreads)))) {
     int cus = 0;
     gleam_status st = device_cu_count(&cus);
     if (st != GLEAM_OK) return st;
@@ -434,8 +434,8 @@ gleam_status launch_fp_out(const gleam_batch* b, uint64_t* d_block_digest, uint6
     if (st != GLEAM_OK) return st;
     grid = items < 4ull * (uint64_t)cus ? items : 4ull * (uint64_t)cus;
   }
-  if (grid > 0x7fffffffull) {
-    set_error("fingerprint: batch needs more than 2^31 workgroups");
+  if (grid > max_workgroups(kThreads)) {
+    set_error("fingerprint: batch needs more workgroups than one launch has (2^24)");
     return GLEAM_E_UNSUPPORTED;
   }
   FpArgs a{b->seg_addr, b->seg_len, b->blk_first, b->n_seg, b->n_blocks, d_block_digest, d_leaf_digest,

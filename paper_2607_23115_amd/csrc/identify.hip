@@ -9,6 +9,7 @@
 
 #include "gleam_device.h"
 #include "gleam_internal.h"
+#include "launch_shape.h"
 
 namespace gleam {
 namespace {
@@ -33,7 +34,9 @@ __global__ void identify_region_kernel(const uint64_t* first_diff, uint64_t n_se
   region_weight[r] = 0;
 }
 
-uint32_t grid_for(uint64_t n, uint64_t cap = 0x7fffffffull) {
+constexpr uint64_t kMaxIdentify = 1ull << 39;
+
+uint32_t grid_for(uint64_t n, uint64_t cap = max_workgroups(kThreads)) {
   const uint64_t g = (n + kThreads - 1) / kThreads;
   return (uint32_t)(g < cap ? (g ? g : 1) : cap);
 }
@@ -59,9 +62,8 @@ extern "C" gleam_status gleam_identify_weights(const gleam_batch* b, const uint6
     set_error("gleam_identify_weights: null recorded digests, region list or output");
     return GLEAM_E_INVALID;
   }
-  if (b->n_seg > 0x7fffffffull * kThreads || n_regions > 0x7fffffffull * kThreads ||
-      b->n_blocks > 0x7fffffffull * kThreads) {
-    set_error("gleam_identify_weights: more than 2^31 workgroups of blocks, payloads or regions");
+  if (b->n_seg > max_workgroups(kThreads) * kThreads || n_regions > kMaxIdentify || b->n_blocks > kMaxIdentify) {
+    set_error("gleam_identify_weights: more than 2^32 payloads, or 2^39 regions or blocks");
     return GLEAM_E_UNSUPPORTED;
   }
   const WsLayout L = ws_layout(b->n_blocks + b->n_seg);
@@ -97,9 +99,8 @@ extern "C" gleam_status gleam_identify_leaves(const gleam_batch* b, const uint64
   }
   const uint32_t lpb_log2 = (uint32_t)(log2_exact(b->block_bytes) - 12);
   const uint64_t n_slots = b->n_blocks << lpb_log2;  // n_blocks < 2^51 (validate_batch)
-  if (b->n_seg > 0x7fffffffull * kThreads || n_regions > 0x7fffffffull * kThreads ||
-      n_slots > 0x7fffffffull * kThreads) {
-    set_error("gleam_identify_leaves: more than 2^31 workgroups of leaf slots, payloads or regions");
+  if (b->n_seg > max_workgroups(kThreads) * kThreads || n_regions > kMaxIdentify || n_slots > kMaxIdentify) {
+    set_error("gleam_identify_leaves: more than 2^32 payloads, or 2^39 regions or leaf slots");
     return GLEAM_E_UNSUPPORTED;
   }
   const WsLayout L = ws_layout(n_slots + b->n_seg);

@@ -6,8 +6,9 @@
 
 namespace gleam {
 
-// HIP's documented limit for one launch is fewer than 2^32 threads: 2^24 - 1 workgroups of
-// 256. (Larger ones ran with ROCm 7.2, but nothing says that they have to.)
+// One launch has fewer than 2^32 threads: 2^24 - 1 workgroups of 256. HIP starts a larger one
+// with its count of threads modulo 2^32, so workgroups are missing, and reports an error only
+// where nothing is left of it.
 constexpr uint64_t max_workgroups(uint32_t threads) { return UINT32_MAX / threads; }
 
 // Calls launch(first, count) for workgroups [first, first + count) of `groups`, at most `most`

@@ -31,6 +31,7 @@
 #include "gleam_device.h"
 #include "gleam_internal.h"
 #include "gleam_table.h"
+#include "launch_shape.h"
 #include "radix_sort.h"
 
 namespace gleam {
@@ -1737,8 +1738,8 @@ extern "C" gleam_status gleam_cache_touch(gleam_cache* c, const uint64_t* d_keys
     set_error("gleam_cache_touch: null keys");
     return GLEAM_E_INVALID;
   }
-  if (n > 0x7fffffffull * kThreads) {
-    set_error("gleam_cache_touch: more than 2^31 workgroups of keys");
+  if (n > max_workgroups(kThreads) * kThreads) {
+    set_error("gleam_cache_touch: more keys than one launch has threads (2^32)");
     return GLEAM_E_UNSUPPORTED;
   }
   hipStream_t s = (hipStream_t)stream;
@@ -1815,7 +1816,7 @@ extern "C" gleam_status gleam_cache_erase(gleam_cache* c, const uint64_t* d_keys
     set_error("gleam_cache_erase: null table, keys or counts");
     return GLEAM_E_INVALID;
   }
-  if (n > (1ull << 36) || n > 0x7fffffffull * kThreads) {
+  if (n > (1ull << 36)) {
     set_error("gleam_cache_erase: more than 2^36 keys");
     return GLEAM_E_UNSUPPORTED;
   }

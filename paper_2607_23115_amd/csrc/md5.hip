@@ -10,6 +10,7 @@
 
 #include "gleam_device.h"
 #include "gleam_internal.h"
+#include "launch_shape.h"
 
 namespace gleam {
 namespace {
@@ -134,8 +135,8 @@ extern "C" gleam_status gleam_md5_prefix(const gleam_batch* b, uint32_t prefix_b
     return GLEAM_E_INVALID;
   }
   const uint64_t grid = (b->n_seg + kThreads - 1) / kThreads;
-  if (grid > 0x7fffffffull) {
-    set_error("gleam_md5_prefix: more than 2^31 workgroups of payloads");
+  if (grid > max_workgroups(kThreads)) {
+    set_error("gleam_md5_prefix: more payloads than one launch has threads (2^32)");
     return GLEAM_E_UNSUPPORTED;
   }
   hipLaunchKernelGGL(md5_prefix_kernel, dim3((uint32_t)grid), dim3(kThreads), 0, (hipStream_t)stream, b->seg_addr,

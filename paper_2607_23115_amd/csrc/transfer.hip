@@ -354,8 +354,8 @@ extern "C" gleam_status gleam_send_plan(const gleam_batch* b, const uint64_t* d_
   const WsLayout L = ws_layout(b->n_blocks);
   st = check_workspace(L, d_ws, ws_bytes, "gleam_send_plan");
   if (st != GLEAM_OK) return st;
-  if (L.tiles > 0x7fffffffull) {
-    set_error("gleam_send_plan: more than 2^31 tiles");
+  if (L.tiles > max_workgroups(kThreads)) {
+    set_error("gleam_send_plan: more tiles than one launch has workgroups (2^24)");
     return GLEAM_E_UNSUPPORTED;
   }
   hipStream_t s = (hipStream_t)stream;

@@ -193,6 +193,23 @@ def test_counts_beyond_any_workspace_are_refused():
         assert g.lib.gleam_workspace_bytes(n) == 0
 
 
+def test_batches_beyond_one_launch_are_refused():
+    """One launch has fewer than 2^32 threads, and HIP starts a larger one without the excess
+    and mostly without an error: calls whose launches would be that large return
+    GLEAM_E_UNSUPPORTED before anything is enqueued."""
+    huge = 1 << 62
+    assert _call_fp(_batch(n_seg=1 << 24, n_blocks=1 << 24, block=512 << 10)) == g.E_UNSUPPORTED
+    assert b"2^24" in g.lib.gleam_last_error()
+    assert _call_fp(_batch(n_seg=1 << 20, n_blocks=1 << 35, block=4096)) == g.E_UNSUPPORTED
+    many = _batch(n_seg=1 << 32, n_blocks=1 << 32, block=1 << 20)
+    assert g.lib.gleam_md5_prefix(ctypes.byref(many), 128, 1024, 256, None, None, None) == g.E_UNSUPPORTED
+    for f in (g.lib.gleam_identify_weights, g.lib.gleam_identify_leaves):
+        assert f(ctypes.byref(many), 256, 256, 1, None, None, 256, 256, huge, None) == g.E_UNSUPPORTED
+    assert g.lib.gleam_miss_compact(256, 1 << 35, None, 256, 256, None, 256, huge, None) == g.E_UNSUPPORTED
+    wide = _batch(n_seg=1 << 20, n_blocks=1 << 35, block=4096)
+    assert g.lib.gleam_send_plan(ctypes.byref(wide), 256, 256, 256, 256, 256, 256, huge, None) == g.E_UNSUPPORTED
+
+
 def test_binding_refuses_batches_the_kernels_would_misread():
     """A Batch's descriptors and payloads must be GPU memory, and an arena's payloads must
     lie inside it; the binding refuses the rest before any GPU work (runs without a GPU)."""
