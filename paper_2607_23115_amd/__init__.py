@@ -179,6 +179,11 @@ def _torch_stream(stream, device) -> torch.cuda.Stream:
     return torch.cuda.ExternalStream(h, device=device)
 
 
+# The current stream's handle without a stream object. Not part of torch's public interface:
+# without it every call takes the general way below.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 class _on_stream:
     """Run a call's own allocations and fills on the stream its kernels run on; `with` gives
     that stream's handle. Tensors a call creates (outputs, workspaces, zeroed counters)
@@ -198,10 +203,10 @@ class _on_stream:
 
     def __enter__(self):
         stream, device = self.stream, self.device
-        if stream is None and isinstance(device, torch.device) and device.type == "cuda":
+        if stream is None and _raw_stream and isinstance(device, torch.device) and device.type == "cuda":
             current = torch.cuda.current_device()
             if device.index is None or device.index == current:
-                return torch._C._cuda_getCurrentRawStream(current)
+                return _raw_stream(current)
         s = _torch_stream(stream, device)
         self.inner = torch.cuda.stream(s)
         self.inner.__enter__()

@@ -83,6 +83,27 @@ def test_side_stream_matches_current_stream(kind):
     assert want[7].all() and want[8].tolist() == [1]
 
 
+def test_without_the_raw_stream_handle(monkeypatch):
+    """torch's function for the current stream's handle is not public: where it is missing,
+    calls take torch's stream objects and give the same results, on the current stream and
+    with a side stream current."""
+    p = payloads(2300)
+    arena, offs, lens = W.pack(p)
+    batch = g.Batch.from_arena(to_device(arena), offs, lens, BLOCK)
+    table, remap = g.Cache(1 << 12), g.Remap(64)
+    probe = keys_to_device(np.array([5], np.uint64))
+    say("no raw stream handle")
+    want = host(run_on(None, batch, table, remap, probe))
+    monkeypatch.setattr(g, "_raw_stream", None)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for stream in (torch.cuda.current_stream(), side):
+        with torch.cuda.stream(stream):
+            got = host(run_on(None, batch, table, remap, probe))
+        for a, b in zip(got, want):
+            assert np.array_equal(a, b)
+
+
 def test_binding_zeroed_counters_precede_the_kernel():
     """Torch's current stream is kept busy with a long read while compaction and the
     calibration read run on a side stream with counters the binding creates: the zeroing
