@@ -80,8 +80,9 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       const uint64_t g = slot >> L2;
       const uint32_t k = (uint32_t)(slot & (lpb - 1));
       const Leaf lf = locate_wave(a, wave_slot0 >> L2, g, k, lane);
-      const bool valid = lpb <= kLeavesPerWave && even && k == 0 && g < a.n_blocks;
-      const typename Out::Before before_hash = out.before(valid, g);
+      typename Out::Before before_hash{};
+      if constexpr (Out::kReadsBefore)
+        before_hash = out.before(lpb <= kLeavesPerWave && even && k == 0 && g < a.n_blocks, g);
       const uint64_t d = hash_slot(lf, tile, lane);
       if (a.leaf_out && even && g < a.n_blocks) a.leaf_out[slot] = lf.len ? d : 0;
       const uint32_t G = lpb <= kLeavesPerWave ? lpb : (uint32_t)kLeavesPerWave;
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       }
       const uint64_t v = tree_reduce_lanes(d, p, n, G, 2);
       if (lpb <= kLeavesPerWave) {
-        out(a, valid, g, v, lf.seg, before_hash);
+        out(a, even && p == 0 && g < a.n_blocks, g, v, lf.seg, before_hash);
       } else {
         if (lane == 0) roots[0][wave] = v;
         __syncthreads();
@@ -104,14 +105,15 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
           uint32_t n2 = 0;
           uint64_t v2 = 0;
           const Leaf head = locate_wave(a, (item * GROUP) >> L2, g2, 0, lane);
-          const bool valid2 = lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks;
-          const typename Out::Before before2 = out.before(valid2, g2);
+          typename Out::Before before2{};
+          if constexpr (Out::kReadsBefore)
+            before2 = out.before(lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks, g2);
           if (lane < W && g2 < a.n_blocks) {
             n2 = (head.blk_leaves + kLeavesPerWave - 1) / kLeavesPerWave;
             v2 = roots[0][lane];
           }
           v2 = tree_reduce_lanes(v2, lane & (G2 - 1), n2, G2);
-          out(a, valid2, g2, v2, head.seg, before2);
+          out(a, lane < W && (lane & (G2 - 1)) == 0 && g2 < a.n_blocks, g2, v2, head.seg, before2);
         }
       }
     } else {
@@ -120,7 +122,8 @@ __global__ __launch_bounds__(kThreads) void fp_kernel(FpArgs a, Out out) {
       const uint64_t s0 = uniform64(find_segment(a.blk_first, a.n_seg, g));
       const Leaf head = locate(a, g, 0, s0);
       const uint32_t nleaf = head.blk_leaves;
-      const typename Out::Before before_hash = out.before(threadIdx.x == 0, g);
+      typename Out::Before before_hash{};
+      if constexpr (Out::kReadsBefore) before_hash = out.before(threadIdx.x == 0, g);
       const uint32_t groups = a.leaf_out ? lpb / GROUP : (nleaf + GROUP - 1) / GROUP;
       for (uint32_t grp = 0; grp < groups; ++grp) {
         const uint32_t k = grp * GROUP + (uint32_t)wave * kLeavesPerWave + (lane >> 1);
@@ -208,7 +211,7 @@ struct Compare {
   uint64_t* first_diff;
   typedef uint64_t Before;  // the recorded digest
   // The waves' differences, for one read of the payload's word instead of one per wave.
-  static constexpr bool kFinishes = true;
+  static constexpr bool kReadsBefore = true, kFinishes = true;
   template <int W>
   struct Late {
     FirstDiff wave[W];

@@ -541,7 +541,7 @@ __device__ __forceinline__ uint64_t hash_slot_quad_direct(const Leaf& lf, uint8_
 constexpr uint8_t kProbePending = 0xFF;
 
 struct NothingBefore {
-  static constexpr bool kFinishes = false;
+  static constexpr bool kReadsBefore = false, kFinishes = false;
   struct Before {};
   __device__ __forceinline__ Before before(bool, uint64_t) const { return {}; }
 };
@@ -567,18 +567,19 @@ __device__ __forceinline__ void quad_pass(const FpArgs& a, uint64_t group, uint8
   const uint64_t g = slot >> L2;
   const uint32_t k = (uint32_t)(slot & (lpb - 1));
   const Leaf lf = locate_wave(a, wave_slot0 >> L2, g, k, lane);
-  const bool head = (lane & 3) == 0, valid = head && k == 0 && g < a.n_blocks;
-  const typename Out::Before before = out.before(valid, g);
+  typename Out::Before before{};
+  if constexpr (Out::kReadsBefore) before = out.before((lane & 3) == 0 && k == 0 && g < a.n_blocks, g);
   const uint64_t d = kDirect ? hash_slot_quad_direct(lf, lds, lane) : hash_slot_quad(lf, lds + wave * kQuadWaveLds, lane);
+  const bool head = (lane & 3) == 0;
   if (a.leaf_out && head && g < a.n_blocks) a.leaf_out[slot] = lf.len ? d : 0;
   if (kLen && head && g < a.n_blocks && lf.len && k + 1 == lf.blk_leaves) blen[g] = (k << 12) + lf.len;
   const uint64_t v = tree_reduce_lanes(d, k, lf.blk_leaves, lpb, 4);
   if constexpr (Out::kFinishes && W > 1) {
     __shared__ typename Out::template Late<W> late;
-    out(a, valid, g, v, lf.seg, before, false, &late.wave[wave]);
+    out(a, head && k == 0 && g < a.n_blocks, g, v, lf.seg, before, false, &late.wave[wave]);
     out.finish(late);
   } else {
-    out(a, valid, g, v, lf.seg, before);
+    out(a, head && k == 0 && g < a.n_blocks, g, v, lf.seg, before);
   }
 }
 
