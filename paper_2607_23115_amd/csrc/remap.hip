@@ -97,6 +97,7 @@ struct UpdLayout {
   size_t keep, wpre, tcount, tbase;      // cap: keep bits, survivors of the tile before each word; tile counts, their scan
   size_t s_start, s_et;                  // cap: the intervals as they were
   size_t kb, vb, aend, amax, acc, apos, srank;  // A: sorted keys/indices, ends, running max, kept flag, number, survivors before
+  size_t below;                          // A: places among the other chunks
   size_t rkb, rmax;                      // R: sorted starts, running max of last addresses
   size_t partial;                        // the scans' tile totals
   size_t ka, aidx, rka, ridx, last, sort;  // past kMaxChunked: the radix sorts' buffers
@@ -126,6 +127,8 @@ UpdLayout upd_layout(uint64_t cap, uint64_t n_add, uint64_t n_del) {
   L.acc = take(8 * n_add);
   L.apos = take(8 * n_add);
   L.srank = take(8 * n_add);
+  L.below = off;
+  if (n_add > kSmall) take(2 * (kMaxChunked / kSmall) * (n_add < kMaxChunked ? n_add : kMaxChunked));
   L.rkb = take(8 * n_del);
   L.rmax = take(8 * n_del);
   const uint64_t ra = n_add > kMaxChunked ? n_add : 0, rd = n_del > kMaxChunked ? n_del : 0;
@@ -392,7 +395,11 @@ struct Removals {  // sorted, in chunks of `chunk`
   uint64_t n, chunk;
 };
 struct Additions {  // sorted, in chunks of `chunk`
-  uint64_t *key, *idx, *end, *max, *acc, *pos, *srank;
+  uint64_t *key, *idx, *end, *max;
+  uint64_t* acc;    // kept: a bit per entry; in one chunk of more than kMaxChunked a word per entry
+  uint64_t* pos;    // of such a chunk: the kept ones before each entry
+  uint64_t* srank;  // survivors before each
+  uint16_t* below;  // [chunk][entry]: entries of that chunk that start before this one (kept entries)
   uint64_t n, chunk;
 };
 
@@ -461,25 +468,69 @@ struct Kept {            // the intervals as they were, and which of them stay
   ulonglong2* et;
 };
 
+// The tile's intervals span part of each chunk only (of unsorted batches a few entries of
+// every chunk): the tile's waves narrow a chunk each for all of them, so that 16 chunks are
+// not searched throughout by each of 16 waves (bound by scattered requests: 32,000 in no order
+// and 2 M intervals, removals 147 to 72 us, the merge of the kept additions below 325 to 86).
+// Up to six chunks of removals the barrier costs sorted ones what it gives the others (12,000
+// and 2 M intervals, the whole call: sorted 71 without and 76 us with it, unsorted 120 and 103).
+constexpr uint64_t kNarrowFrom = 6;
+constexpr int kMostChunks = (int)(kMaxChunked / kSmall);
+static_assert(kMostChunks <= kTileThreads / 64, "one chunk per wave");
+struct Narrowed {
+  uint64_t lo[kMostChunks], hi[kMostChunks];
+};
+
 __global__ __launch_bounds__(kTileThreads) void survive_kernel(MapRef map, Removals R, Kept K) {
   __shared__ uint32_t wcount[kTileWords];
+  __shared__ Narrowed near;  // hi 0: the chunk meets nothing here
   const uint64_t count = map.hdr[0];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t p0 = (uint64_t)blockIdx.x * kTile + 64 * wave, p = p0 + lane;
+  const uint64_t tile0 = (uint64_t)blockIdx.x * kTile, p0 = tile0 + 64 * wave, p = p0 + lane;
   if (blockIdx.x == 0 && threadIdx.x == 0) K.count[0] = count;
   bool stay = p < count;
+  const uint64_t at = stay ? p : count - 1;
+  uint64_t s = 0;
+  ulonglong2 et = make_ulonglong2(0, 0);
+  if (p0 < count) {
+    s = map.start[at];
+    et = map.et[at];
+  }
+  const bool narrow = R.n > kNarrowFrom * R.chunk;
+  if (narrow && tile0 < count && (uint64_t)wave * R.chunk < R.n) {
+    const uint64_t c = (uint64_t)wave * R.chunk, n = min(R.chunk, R.n - c);
+    const uint64_t *key = R.key + c, *max = R.max + c;
+    const uint64_t first = map.start[tile0], last = map.et[min(tile0 + kTile, count) - 1].x - 1;
+    uint64_t lo = 0, hi = 0;
+    if (key[0] <= last && max[n - 1] >= first) {
+      hi = wave_count_below<true>(key, n, last, lane);
+      if (max[hi - 1] >= first) lo = wave_count_below<true>(key, hi, first, lane);  // (hi >= 1: key[0] <= last)
+      else hi = 0;
+    }
+    if (lane == 0) {
+      near.lo[wave] = lo;
+      near.hi[wave] = hi;
+    }
+  }
+  if (narrow) __syncthreads();
   if (p0 < count) {  // the wave's intervals lie between `first` and `last`
-    const uint64_t at = stay ? p : count - 1;
-    const uint64_t s = map.start[at];
-    const ulonglong2 et = map.et[at];
     const uint64_t first = uniform64(s, 0), last = uniform64(et.x, 63) - 1;
-    for (uint64_t c = 0; c < R.n; c += R.chunk) {
-      const uint64_t n = min(R.chunk, R.n - c);
+    uint32_t x = 0;
+    for (uint64_t c = 0; c < R.n; c += R.chunk, ++x) {
       const uint64_t *key = R.key + c, *max = R.max + c;
-      if (key[0] > last || max[n - 1] < first) continue;
-      const uint64_t hi = wave_count_below<true>(key, n, last, lane);
-      if (hi == 0 || max[hi - 1] < first) continue;
-      const uint64_t lo = wave_count_below<true>(key, hi, first, lane);
+      uint64_t lo = 0, hi = min(R.chunk, R.n - c);
+      if (narrow) {
+        lo = near.lo[x];
+        hi = near.hi[x];
+        if (hi == 0) continue;
+      } else if (key[0] > last || max[hi - 1] < first) {
+        continue;
+      }
+      if (hi - lo > 64) {
+        hi = lo + wave_count_below<true>(key + lo, hi - lo, last, lane);
+        if (hi == 0 || max[hi - 1] < first) continue;
+        lo += wave_count_below<true>(key + lo, hi - lo, first, lane);
+      }
       const uint64_t q = count_below<true>(key, lo, hi, et.x - 1);
       if (q && max[q - 1] >= s) stay = false;
     }
@@ -527,123 +578,128 @@ __device__ __forceinline__ bool meets_own_chunk(const Additions& A, uint64_t c, 
   return (k > 0 && A.max[c + k - 1] > s) || (k + 1 < n && A.key[c + k + 1] < e);
 }
 
-// One workgroup per chunk of the additions (one also when there are none): which are kept,
-// their numbers within the chunk and the survivors before each. Without `scanned` the tile
-// counts are scanned here, by every workgroup for itself; the first one stores the scan.
-__global__ __launch_bounds__(kSmallThreads) void classify_chunks_kernel(Kept K, Additions A, Batches in,
-                                                                        uint32_t tiles, uint32_t scanned) {
+// Which additions are kept, their places among the other chunks and the survivors before each:
+// 256 to a workgroup, as the searches are bound by each CU's rate of scattered requests (16,000 in
+// no order and 200,000 intervals: 88 us with a chunk of 2,048 to a workgroup, 33 so; in address
+// order 21 and 12). Without additions one workgroup of 1,024. Without `scanned` the tile counts
+// are scanned here, by every workgroup for itself; the first one stores the scan.
+constexpr int kClassThreads = 256;
+static_assert(kSmall % kClassThreads == 0, "a workgroup's additions are of one chunk");
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void classify_chunks_kernel(Kept K, Additions A, Batches in, uint32_t tiles,
+                                                                   uint32_t scanned) {
   __shared__ uint32_t base[kLdsTiles + 1];
-  __shared__ uint64_t wave[kSmallThreads / 64];
+  __shared__ uint32_t wave_sum[kThreads / 64];
   const uint32_t t = threadIdx.x;
-  const uint64_t c = (uint64_t)blockIdx.x * kSmall;
+  const int lane = t & 63, wave = t >> 6;
+  const uint64_t c = (uint64_t)blockIdx.x * kThreads / kSmall * kSmall;
   const uint32_t n = A.n ? (uint32_t)min(A.n - c, (uint64_t)kSmall) : 0;
-  uint64_t k[2], s[2], e[2], id[2];
-  bool valid[2], clash[2] = {false, false};
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    k[h] = 2 * t + h;
-    const uint64_t at = c + (k[h] < n ? k[h] : 0);
-    s[h] = n ? A.key[at] : kNone;
-    e[h] = n ? A.end[at] : 0;
-    id[h] = n ? A.idx[at] : 0;
-    valid[h] = k[h] < n && s[h] != kNone;
-    if (valid[h]) clash[h] = meets_own_chunk(A, c, n, k[h], s[h], e[h]);
-  }
+  const uint32_t k = (uint32_t)((uint64_t)blockIdx.x * kThreads - c) + t;
+  const uint64_t at = c + (k < n ? k : 0);
+  const uint64_t s = n ? A.key[at] : kNone, e = n ? A.end[at] : 0, id = n ? A.idx[at] : 0;
+  const bool valid = k < n && s != kNone;
+  bool clash = valid && meets_own_chunk(A, c, n, k, s, e);
   if (!scanned) {
-    static_assert(kLdsTiles == 4 * kSmallThreads, "four tiles per thread");
-    uint64_t v[4], pair[2];
+    constexpr uint32_t kMost = kLdsTiles / kThreads;
+    const uint32_t each = (tiles + kThreads - 1) / kThreads;  // at most kMost
+    uint32_t v[kMost], sum = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = 4 * t + j < tiles ? K.tcount[4 * t + j] : 0;
-    pair[0] = v[0] + v[1];
-    pair[1] = v[2] + v[3];
-    scan_pairs(pair, ScanSum(), wave);
-    const uint64_t x[4] = {pair[0] - v[0] - v[1], pair[0] - v[1], pair[0], pair[1] - v[3]};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      base[4 * t + j] = (uint32_t)x[j];
-      if (blockIdx.x == 0 && 4 * t + j <= tiles) K.tbase[4 * t + j] = x[j];
+    for (uint32_t j = 0; j < kMost; ++j) {
+      v[j] = j < each && t * each + j < tiles ? (uint32_t)K.tcount[t * each + j] : 0;
+      sum += v[j];
     }
-    if (t == kSmallThreads - 1) {  // the end of the last tile, where there are kLdsTiles of them
-      base[kLdsTiles] = (uint32_t)pair[1];
-      if (blockIdx.x == 0 && tiles == kLdsTiles) K.tbase[kLdsTiles] = pair[1];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += y;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+    for (int w = 0; w < wave; ++w) run += wave_sum[w];
+#pragma unroll
+    for (uint32_t j = 0; j < kMost; ++j) {
+      if (j < each && t * each + j < tiles) {
+        base[t * each + j] = run;
+        if (blockIdx.x == 0) K.tbase[t * each + j] = run;
+      }
+      run += v[j];
+    }
+    if (t == kThreads - 1) {
+      base[tiles] = run;
+      if (blockIdx.x == 0) K.tbase[tiles] = run;
     }
   }
   if (n == 0) return;
+  // the wave's additions lie between its first start and the furthest end up to its last
+  const uint32_t w0 = k - (uint32_t)lane;
+  const uint64_t first = w0 < n ? A.key[c + w0] : kNone, furthest = w0 < n ? A.max[c + min(w0 + 63, n - 1)] : 0;
+  const bool some = first != kNone;  // the wave
   // other chunks, four at a time so that their searches wait together
-  for (uint64_t c0 = 0; c0 < A.n; c0 += 4 * kSmall) {
+  for (uint64_t c0 = 0; some && c0 < A.n; c0 += 4 * kSmall) {
     const uint64_t* key[4];
-    uint32_t len[4], q[2][4];
+    uint32_t len[4], q[4];
     bool any = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const uint64_t cj = c0 + j * kSmall;
       len[j] = cj < A.n && cj != c ? (uint32_t)min(A.n - cj, (uint64_t)kSmall) : 0;
       key[j] = A.key + (len[j] ? cj : 0);
-      q[0][j] = q[1][j] = 0;
-      // (sorted chunks: this one's entries lie between its first start and its furthest end)
-      if (len[j] && (key[j][0] >= A.max[c + n - 1] || A.max[cj + len[j] - 1] <= A.key[c])) len[j] = 0;
+      q[j] = 0;
+      if (len[j] && key[j][0] >= furthest) {
+        len[j] = 0;
+      } else if (len[j] && A.max[cj + len[j] - 1] <= first) {  // they all start (and end) before
+        q[j] = len[j];
+        len[j] = 0;
+      }
       any |= len[j] != 0;
     }
-    if (!any) continue;
-    for (uint32_t step = kSmall; step; step >>= 1) {
+    if (any) {
+      for (uint32_t step = kSmall; step; step >>= 1) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (q[j] + step <= len[j] && key[j][q[j] + step - 1] < e) q[j] += step;
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-          if (q[h][j] + step <= len[j] && key[j][q[h][j] + step - 1] < e[h]) q[h][j] += step;
+        if (valid && len[j] && q[j] && A.max[c0 + j * kSmall + q[j] - 1] > s) clash = true;
     }
+    if (valid) {  // (of an addition that is kept, those that start before its end start before it)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-        if (valid[h] && q[h][j] && A.max[c0 + j * kSmall + q[h][j] - 1] > s[h]) clash[h] = true;
+      for (int j = 0; j < 4; ++j) {
+        const uint64_t cj = c0 + j * kSmall;
+        if (cj < A.n && cj != c) A.below[cj / kSmall * A.n + at] = (uint16_t)q[j];
+      }
+    }
   }
   // The intervals that start before the end (i1) and those that start at or before the
-  // start (i0). The wave's 128 additions lie between its first start and the furthest end,
-  // and usually few intervals do: the wave finds those, each lane its own among them.
-  const uint32_t w0 = t / 64 * 128;
-  uint64_t i0[2] = {0, 0}, i1[2] = {0, 0};
-  if (w0 < n) {
-    const uint64_t count = K.count[0], first = A.key[c + w0], furthest = A.max[c + min(w0 + 127, n - 1)];
-    if (first != kNone) {
-      const int lane = t & 63;
-      const uint64_t lo = wave_count_below<true>(K.start, count, first, lane);
-      const uint64_t len = wave_count_below<true>(K.start, count, furthest - 1, lane) - lo;
-      for (uint64_t step = len ? top_bit((uint32_t)len) : 0; step; step >>= 1) {  // len <= 2^31
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (i1[h] + step <= len && K.start[lo + i1[h] + step - 1] < e[h]) i1[h] += step;
-          if (i0[h] + step <= len && K.start[lo + i0[h] + step - 1] <= s[h]) i0[h] += step;
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        i1[h] += lo;
-        i0[h] += lo;
-        if (valid[h] && i0[h] && K.et[i0[h] - 1].x > s[h]) --i0[h];  // those that end at or before the start
-      }
+  // start (i0). Usually few lie between the wave's first start and its furthest end: the wave
+  // finds those, each lane its own among them.
+  uint64_t i0 = 0, i1 = 0;
+  if (some) {
+    const uint64_t count = K.count[0];
+    const uint64_t lo = wave_count_below<true>(K.start, count, first, lane);
+    const uint64_t len = wave_count_below<true>(K.start, count, furthest - 1, lane) - lo;
+    for (uint64_t step = len ? top_bit((uint32_t)len) : 0; step; step >>= 1) {  // len <= 2^31
+      if (i1 + step <= len && K.start[lo + i1 + step - 1] < e) i1 += step;
+      if (i0 + step <= len && K.start[lo + i0 + step - 1] <= s) i0 += step;
     }
+    i1 += lo;
+    i0 += lo;
+    if (valid && i0 && K.et[i0 - 1].x > s) --i0;  // those that end at or before the start
   }
   __syncthreads();  // the tile bases
-  uint64_t a[2] = {0, 0};
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (!valid[h]) continue;
-    const uint64_t before = scanned ? survivors_before(K, K.tbase, i0[h]) : survivors_before(K, base, i0[h]);
-    const uint64_t up_to = scanned ? survivors_before(K, K.tbase, i1[h]) : survivors_before(K, base, i1[h]);
-    if (up_to > before) clash[h] = true;
-    a[h] = clash[h] ? 0 : 1;
-    A.srank[c + k[h]] = before;
-    if (in.status) in.status[id[h]] = clash[h] ? GLEAM_REMAP_OVERLAP : GLEAM_REMAP_ADDED;
+  bool keep = false;
+  if (valid) {
+    const uint64_t before = scanned ? survivors_before(K, K.tbase, i0) : survivors_before(K, base, i0);
+    const uint64_t up_to = scanned ? survivors_before(K, K.tbase, i1) : survivors_before(K, base, i1);
+    keep = !clash && up_to == before;
+    A.srank[at] = before;
+    if (in.status) in.status[id] = keep ? GLEAM_REMAP_ADDED : GLEAM_REMAP_OVERLAP;
   }
-  uint64_t sum[2] = {a[0], a[1]};
-  scan_pairs(sum, ScanSum(), wave);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (k[h] >= n) continue;
-    A.acc[c + k[h]] = a[h];
-    A.pos[c + k[h]] = sum[h] - a[h];
-  }
+  const uint64_t word = __ballot(keep);
+  if (lane == 0 && w0 < n) A.acc[(c + w0) / 64] = word;
 }
 
 // The same over the whole device, for one chunk of every addition; the numbers come from a
@@ -670,23 +726,96 @@ __global__ __launch_bounds__(kThreads) void classify_all_kernel(Kept K, Addition
 }
 
 // ---- merge ------------------------------------------------------------------------------
-// Kept additions among the first k of the chunk at c (of n).
-__device__ __forceinline__ uint64_t kept_before(const Additions& A, uint64_t c, uint64_t n, uint64_t k) {
-  return k < n ? A.pos[c + k] : A.pos[c + n - 1] + A.acc[c + n - 1];
-}
+// The kept additions: how many, and how many among the first k of the chunk at c (of n). In
+// chunks they are counted from their bits, which every workgroup scans for itself.
+template <bool kChunked>
+struct KeptAdditions;
+
+template <>
+struct KeptAdditions<true> {
+  static constexpr uint32_t kWords = (uint32_t)(kMaxChunked / 64), kOwn = (uint32_t)(kSmall / 64) + 1;
+  static_assert(kWords <= (uint32_t)kTileThreads && kOwn <= 64, "one word per thread");
+  static constexpr uint32_t kLds = kWords + 1 > kOwn * kTileWords ? kWords + 1 : (uint32_t)(kOwn * kTileWords);
+  struct Lds {
+    uint64_t word[kLds];
+    uint32_t before[kLds], wave[kWords / 64];
+  };
+  const Lds& lds;
+  uint32_t own;  // where the counts of this wave begin
+  uint64_t total;
+  // Every thread of the workgroup calls it. The words of one chunk are scanned by each wave for
+  // itself: the barriers cost 3 of 16 us in a map of 2 M intervals.
+  __device__ KeptAdditions(const Additions& A, Lds& l) : lds(l), own(0), total(0) {
+    if (A.n == 0) return;
+    const uint32_t t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const bool one = A.n <= kSmall;
+    const uint32_t at = one ? lane : t;
+    const uint64_t word = at < kWords && 64 * (uint64_t)at < A.n ? A.acc[at] : 0;
+    const uint32_t c = (uint32_t)__popcll(word);
+    uint32_t incl = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(incl, d, 64);
+      if (lane >= (uint32_t)d) incl += y;
+    }
+    if (one) {
+      own = kOwn * wave;
+      total = __shfl(incl, 63, 64);
+      if (lane < kOwn) {
+        l.word[own + lane] = word;
+        l.before[own + lane] = incl - c;
+      }
+      wave_lds_sync();
+      return;
+    }
+    if (t < kWords) {
+      l.word[t] = word;
+      if (lane == 63) l.wave[wave] = incl;
+    }
+    __syncthreads();
+    if (t < kWords) {
+      for (uint32_t w = 0; w < wave; ++w) incl += l.wave[w];
+      l.before[t] = incl - c;
+      if (t == kWords - 1) l.before[kWords] = incl;
+    }
+    __syncthreads();
+    total = l.before[kWords];
+  }
+  __device__ __forceinline__ uint32_t up_to(uint64_t i) const {
+    const uint32_t at = own + (uint32_t)(i / 64);
+    return lds.before[at] + (i % 64 ? (uint32_t)__popcll(lds.word[at] & ((1ull << (i % 64)) - 1)) : 0);
+  }
+  __device__ __forceinline__ uint64_t before(const Additions&, uint64_t c, uint64_t, uint64_t k) const {
+    return up_to(c + k) - up_to(c);
+  }
+  __device__ __forceinline__ bool kept(const Additions&, uint64_t k) const {
+    return (lds.word[own + k / 64] >> (k % 64)) & 1;
+  }
+};
+
+template <>
+struct KeptAdditions<false> {  // one chunk
+  struct Lds {};
+  uint64_t total;
+  __device__ KeptAdditions(const Additions& A, Lds&) { total = before(A, 0, A.n, A.n); }
+  __device__ __forceinline__ uint64_t before(const Additions& A, uint64_t, uint64_t n, uint64_t k) const {
+    return k < n ? A.pos[k] : A.pos[n - 1] + A.acc[n - 1];
+  }
+  __device__ __forceinline__ bool kept(const Additions& A, uint64_t k) const { return A.acc[k] != 0; }
+};
 
 // Workgroups [0, tiles): the survivors of a tile each; the others the additions. When
 // the result would not fit, the kept additions are FULL instead. The first one also writes
 // the header and the counts.
+template <bool kChunked>
 __global__ __launch_bounds__(kTileThreads) void place_kernel(MapRef map, Kept K, Additions A, Batches in,
                                                              uint32_t tiles, uint64_t* counts) {
+  __shared__ typename KeptAdditions<kChunked>::Lds lds;
+  __shared__ Narrowed near;  // entries of each chunk that start before the tile's first survivor, and its last
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t before = K.count[0], n_surv = K.tbase[tiles];
-  uint64_t n_acc = 0;
-  for (uint64_t c = 0; c < A.n; c += A.chunk) {
-    const uint64_t n = min(A.chunk, A.n - c);
-    n_acc += kept_before(A, c, n, n);
-  }
+  const KeptAdditions<kChunked> kept(A, lds);
+  const uint64_t n_acc = kept.total;
   const uint64_t total = n_surv + n_acc;
   const bool fits = total <= map.cap;
   const uint64_t S = total > kFence ? (total + kFence - 1) / kFence : 1;
@@ -707,42 +836,67 @@ __global__ __launch_bounds__(kTileThreads) void place_kernel(MapRef map, Kept K,
     }
   }
   if (blockIdx.x < tiles) {
-    const uint64_t p0 = (uint64_t)blockIdx.x * kTile + 64 * wave, p = p0 + lane;
-    if (!fits || p0 >= before) return;  // the wave
+    const uint64_t tile0 = (uint64_t)blockIdx.x * kTile, p0 = tile0 + 64 * wave, p = p0 + lane;
+    if (!fits || tile0 >= before) return;  // the workgroup
+    const bool narrow = A.n > A.chunk;
+    if (narrow && (uint64_t)wave * A.chunk < A.n) {
+      const uint64_t c = (uint64_t)wave * A.chunk, n = min(A.chunk, A.n - c);
+      const uint64_t* key = A.key + c;
+      const uint64_t first = K.start[tile0], last = K.start[min(tile0 + kTile, before) - 1];
+      uint64_t lo = 0, hi = 0;
+      if (key[0] < last) {
+        lo = hi = n;
+        if (key[n - 1] >= first) {
+          lo = wave_count_below<false>(key, n, first, lane);
+          hi = lo + wave_count_below<false>(key + lo, n - lo, last, lane);
+        }
+      }
+      if (lane == 0) {
+        near.lo[wave] = lo;
+        near.hi[wave] = hi;
+      }
+    }
+    if (narrow) __syncthreads();
+    if (p0 >= before) return;  // the wave
     const uint64_t at = p < before ? p : before - 1;
     const uint64_t s = K.start[at], word = K.word[p0 / 64];
     const uint64_t first = uniform64(s, 0), last = uniform64(s, 63);
     uint64_t q = K.tbase[blockIdx.x] + K.wpre[p0 / 64] + (uint64_t)__popcll(word & ((1ull << lane) - 1));
-    for (uint64_t c = 0; c < A.n; c += A.chunk) {
+    uint32_t x = 0;
+    for (uint64_t c = 0; c < A.n; c += A.chunk, ++x) {
       const uint64_t n = min(A.chunk, A.n - c);
       const uint64_t* key = A.key + c;
-      if (key[0] >= last) continue;
-      uint64_t lo = n, hi = n;  // the entries that start before every survivor of the wave, and any
-      if (key[n - 1] >= first) {
-        lo = wave_count_below<false>(key, n, first, lane);
-        hi = wave_count_below<false>(key, n, last, lane);
+      uint64_t lo = 0, hi = n;
+      if (narrow) {
+        lo = near.lo[x];
+        hi = near.hi[x];
+      } else if (key[0] >= last) {
+        continue;
+      } else if (key[n - 1] < first) {
+        lo = n;
       }
-      q += kept_before(A, c, n, lo == hi ? lo : count_below<false>(key, lo, hi, s));
+      if (hi - lo > 64) {
+        const uint64_t from = lo;
+        lo += wave_count_below<false>(key + from, hi - from, first, lane);
+        hi = from + wave_count_below<false>(key + from, hi - from, last, lane);
+      }
+      q += kept.before(A, c, n, lo == hi ? lo : count_below<false>(key, lo, hi, s));
     }
     if ((word >> lane) & 1) place(q, s, K.et[p]);
     return;
   }
   for (uint64_t k = (uint64_t)(blockIdx.x - tiles) * kTile + threadIdx.x; k < A.n;
        k += (uint64_t)(gridDim.x - tiles) * kTile) {
-    if (!A.acc[k]) continue;
+    if (!kept.kept(A, k)) continue;
     if (!fits) {
       if (in.status) in.status[A.idx[k]] = GLEAM_REMAP_FULL;
       continue;
     }
     const uint64_t s = A.key[k], own = k / A.chunk * A.chunk;
-    uint64_t q = A.srank[k] + A.pos[k];
-    for (uint64_t c = 0; c < A.n; c += A.chunk) {
-      if (c == own) continue;
-      const uint64_t n = min(A.chunk, A.n - c);
-      const uint64_t* key = A.key + c;
-      if (key[0] >= s) continue;
-      q += kept_before(A, c, n, key[n - 1] < s ? n : count_below<false>(key, 0, n, s));
-    }
+    uint64_t q = A.srank[k] + kept.before(A, own, min(A.chunk, A.n - own), k - own);
+    uint32_t x = 0;
+    for (uint64_t c = 0; c < A.n; c += A.chunk, ++x)
+      if (c != own) q += kept.before(A, c, min(A.chunk, A.n - c), A.below[x * A.n + k]);
     place(q, s, make_ulonglong2(A.end[k], in.a_target[A.idx[k]] - s));
   }
 }
@@ -924,7 +1078,7 @@ extern "C" gleam_status gleam_remap_update(gleam_remap* m, const uint64_t* d_del
   const Batches in{d_del_start, d_del_len, d_add_start, d_add_len, d_add_target, n_del, n_add, d_add_status};
   const Removals R{at(L.rkb), at(L.rmax), n_del, chunk_of(n_del)};
   const Additions A{at(L.kb), at(L.vb), at(L.aend), at(L.amax), at(L.acc), at(L.apos), at(L.srank),
-                    n_add, chunk_of(n_add)};
+                    reinterpret_cast<uint16_t*>(b + L.below), n_add, chunk_of(n_add)};
   const Kept K{hdr + 12, at(L.keep), reinterpret_cast<uint32_t*>(b + L.wpre), at(L.tcount), at(L.tbase),
                at(L.s_start), reinterpret_cast<ulonglong2*>(b + L.s_et)};
   const bool many_del = n_del > kMaxChunked, many_add = n_add > kMaxChunked;
@@ -978,15 +1132,20 @@ extern "C" gleam_status gleam_remap_update(gleam_remap* m, const uint64_t* d_del
     if ((st = launch_status("classify_all_kernel")) != GLEAM_OK) return st;
     if ((st = device_scan<ScanSum, true>(A.acc, A.pos, n_add, partial, s)) != GLEAM_OK) return st;
   } else {
-    hipLaunchKernelGGL(classify_chunks_kernel, dim3(a_chunks ? a_chunks : 1), dim3(kSmallThreads), 0, s, K, A, in,
-                       tiles, scanned ? 1u : 0u);
+    if (n_add)
+      hipLaunchKernelGGL(classify_chunks_kernel<kClassThreads>, dim3((uint32_t)((n_add + kClassThreads - 1) / kClassThreads)),
+                         dim3(kClassThreads), 0, s, K, A, in, tiles, scanned ? 1u : 0u);
+    else
+      hipLaunchKernelGGL(classify_chunks_kernel<kTileThreads>, dim3(1), dim3(kTileThreads), 0, s, K, A, in, tiles,
+                         scanned ? 1u : 0u);
     if ((st = launch_status("classify_chunks_kernel")) != GLEAM_OK) return st;
   }
 
   // 4. merge by rank into the storage (only if everything fits), the header and the counts
   const uint64_t groups = (n_add + kTile - 1) / kTile;
   const uint32_t a_groups = (uint32_t)(groups < kMaxGrid ? groups : kMaxGrid);
-  hipLaunchKernelGGL(place_kernel, dim3(tiles + a_groups), dim3(kTileThreads), 0, s, map, K, A, in, tiles, d_counts);
+  hipLaunchKernelGGL(many_add ? place_kernel<false> : place_kernel<true>, dim3(tiles + a_groups), dim3(kTileThreads), 0, s,
+                     map, K, A, in, tiles, d_counts);
   return launch_status("place_kernel");
 }
 

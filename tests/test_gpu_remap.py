@@ -353,6 +353,59 @@ def test_chunks_of_a_batch(n_add, n_del, order):
         assert_map(m, om, f"step {step}")
 
 
+@pytest.mark.parametrize("n_add,n_del", [(255, 12_288), (256, 12_289), (257, 2048), (2048, 14_336), (2305, 0),
+                                         (30_721, 30_721)])
+@pytest.mark.parametrize("room", [1 << 16, 900])
+def test_chunks_that_span_the_map(n_add, n_del, room):
+    """Unsorted batches, whose every chunk spans the map: 256 additions to a workgroup, one
+    chunk's kept ones counted by each wave and those of several by each workgroup, the tiles'
+    ranges narrowed from two chunks of additions and from 12,289 removals on; with room for
+    all that is added and (where more than 900 beyond what is removed is added) without."""
+    rng = np.random.default_rng([n_add, n_del, room])
+    count, stride = 40_963, 4096
+    start = (np.arange(count, dtype=np.uint64) + np.uint64(1)) * np.uint64(stride)
+    m, om = g.Remap(count + room), oremap.RemapMap(count + room)
+    update_both(m, om, add=(start, np.full(count, 512, np.uint64), start))
+    gone = rng.permutation(start)[:n_del]
+    a_s = rng.permutation(start)[:n_add] + rng.integers(0, stride, n_add, dtype=np.uint64)
+    add = (a_s, rng.integers(1, 600, n_add, dtype=np.uint64), rng.integers(0, 1 << 62, n_add, dtype=np.uint64))
+    say("remap spanning chunks n_add", n_add, "n_del", n_del, "room", room)
+    st, counts, est, ecounts = update_both(m, om, (gone + np.uint64(511), np.ones(n_del, np.uint64)), add)
+    assert np.array_equal(st, est) and counts == ecounts
+    assert_map(m, om, "spanning chunks")
+    assert_translate(m, om, probes(om, rng, 5000, 1 << 28), "spanning chunks")
+
+
+def test_batches_in_chunks_cost_no_more_than_sorted_ones():
+    """32,768 unsorted removals and additions are merged in 16 chunks, 32,769 after a radix sort:
+    the chunks, each of which spans the map, must not be the dearer way."""
+    count, rng = 2_000_000, np.random.default_rng(77)
+    start = (np.arange(count, dtype=np.uint64) + np.uint64(1)) << np.uint64(22)
+    m = g.Remap(count + 40_000)
+    m.update(add_start=dev(start), add_len=dev(np.full(count, 1 << 20)), add_target=dev(start))
+    snap = m.storage.clone()
+    took = {}
+    for n in (32_768, 32_769):
+        gone = rng.permutation(start)[:n]
+        args = [dev(x) for x in (gone, np.full(n, 1 << 20), gone + np.uint64(1 << 21), np.full(n, 1 << 20), gone)]
+        ws, counts = m.update_workspace(n, n), torch.zeros(4, dtype=torch.int64, device="cuda")
+        times = []
+        for _ in range(9):
+            m.storage.copy_(snap)
+            torch.cuda.synchronize()
+            a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+            a.record()
+            m.update(*args, counts=counts, ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3)
+        assert [int(c) for c in u64(counts)] == [count, n, n, 0]
+        took[n] = sorted(times)[4]
+    say("remap batches in chunks and sorted, us:", took)
+    # measured 230 and 250 (650 where every wave searched every chunk throughout); 1.3 for noise
+    assert took[32_768] <= 1.3 * took[32_769]
+
+
 @pytest.mark.parametrize("cap", [1 << 22, (1 << 22) + 1])
 def test_small_update_of_a_large_map(cap):
     """At most 4,096 tiles of 1,024 intervals are scanned by the workgroups that number the
