@@ -300,7 +300,8 @@ size_t gleam_detect_workspace_bytes(uint64_t n_blocks);
  * calls must not overlap, on any stream, with other calls on the same table.
  *
  * gleam_cache_maint_bytes: device workspace bytes for evict and export of this
- * table, about 64 bytes per slot (0 for NULL or a table above 2^31 slots).
+ * table, about 44 bytes per slot and at most about 1 MiB more (0 for NULL or a table
+ * above 2^31 slots).
  *
  * gleam_cache_touch: for every key present, stamp = max(stamp, epoch), the epoch being
  * d_epochs[i] (device u64[n]) or, when d_epochs is NULL, the scalar `epoch`.
@@ -322,9 +323,13 @@ size_t gleam_detect_workspace_bytes(uint64_t n_blocks);
  *
  * gleam_cache_export: every entry sorted by key into device u64[capacity + 1] arrays
  * d_keys, d_vals and (nullable) d_stamps; *d_count (device u64[1]) = entries written.
- * Evict and export gather the live entries and order them with a radix sort of their
- * own (kernels only), so both may be captured in a graph; their cost follows the
- * capacity.
+ * Evict selects the entries to remove in a pass over the table, sorts those, and
+ * repairs the clusters that they leave; export partitions the entries by key range and
+ * sorts each part (keys too crowded for that are sorted as a whole instead, decided on
+ * the device). Both enqueue kernels only and may be captured in a graph; their cost
+ * follows the capacity. How finely export partitions is decided on the host, by the key
+ * bound at the call: a replay over a table that has grown past it costs more time and
+ * gives the same result.
  * Re-inserting the exported pairs (and touching them with their stamps) rebuilds the
  * table: the export is also its checkpoint.
  *
@@ -555,8 +560,10 @@ gleam_status gleam_restore_blocks(const gleam_batch* dst, const gleam_send_recor
  *                 >= gleam_remap_update_bytes(m, n_add, n_del)
  * If the survivors and the accepted additions exceed the capacity, the map is left
  * exactly as it was (the removals included) and those additions get GLEAM_REMAP_FULL.
- * Every update passes over the whole capacity (survivors are marked and compacted)
- * whatever the count, plus a sort of the additions: size the capacity to the map.
+ * Every update launches workgroups for the whole capacity and reads and rewrites every
+ * interval, whatever the number of changes, after a sort of the removals and of the
+ * additions (in chunks of 2,048, merged by search, for up to 32,768 of either): size the
+ * capacity to the map.
  * Errors: GLEAM_E_INVALID, GLEAM_E_WORKSPACE, GLEAM_E_UNSUPPORTED (n_add or n_del
  * above 2^31), GLEAM_E_HIP. gleam_remap_update_bytes returns 0 for a NULL map or counts
  * above 2^31.

@@ -344,10 +344,12 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableRef t,
 
 // Inserts of up to kSmallInsertKeys keys: one 1024-thread workgroup, the dedup table in
 // LDS as in lookup_small_kernel, so one launch and no clear pass. The lowest index of
-// each key inserts it; *n_new is written once at the end. GPU time on MI355X (this /
-// the three launches): 256 keys 6.4 us, 1,024 keys 10.2 us, 2,048 keys 15.1 us, 4,096
-// keys 38 us against about 20 us: past 2,048 keys one CU's chain of table
-// compare-and-swaps costs more than the launches it saves.
+// each key inserts it; *n_new is written once at the end. GPU time on MI355X (this / the
+// three launches) in tables of 2^16 to 2^25 slots: load 0.05, 256 keys 7-8 / 20 us, 1,000
+// 9-11 / 18-19, 2,048 16-20 / 21-22, 3,000 26-32 / 20-21; load 0.5, 256 keys 11-14 / 24-27,
+// 1,000 17-20 / 24-26, 2,048 28-34 / 26-28, 3,000 43-52 / 26-27; load 0.65, 1,000 keys 23-28 /
+// 29-31, 2,048 42-50 / 32-37. Past 2,048 keys one CU's chain of table compare-and-swaps costs
+// more than the launches it saves at any load; from half load on it does from about 1,500.
 constexpr uint64_t kSmallInsertKeys = 2048;
 __global__ __launch_bounds__(kSmallThreads) void insert_small_kernel(TableRef t, const uint64_t* keys,
                                                                      const uint64_t* vals, uint64_t n,

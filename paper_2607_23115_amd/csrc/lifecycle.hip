@@ -410,9 +410,9 @@ __device__ __forceinline__ void fold_bits(uint64_t* bits, uint64_t and_w, uint64
 // Reads the table once (the entries up to a bin that the samples say holds the last
 // victim) and writes only what it evicts. Should the samples have misled it, a histogram
 // of the whole table finds the bin and a second pass collects what is missing. 20 M entries
-// in 2^25 slots, 20,000 evicted: 0.34 ms (collecting 175 us, 4.6 TB/s; the sort's sixteen
-// passes 110), against 5.6 ms for gathering, sorting and re-inserting every entry; half of
-// them evicted 2.8 against 4.7 ms; all of them 4.3 against 4.2.
+// in 2^25 slots, 20,000 evicted: 0.38 ms (collecting 184 us, 4.4 TB/s; the sort's sixteen
+// passes 136), against 5.9 ms for gathering, sorting and re-inserting every entry; half of
+// them evicted 2.9 against 5.1 ms; all of them 4.6 against 4.5.
 constexpr uint32_t kPickThreads = 1024;
 constexpr uint32_t kPickGrid = 256;  // few enough that the final atomics on the bins stay few
 constexpr uint32_t kPickItems = 4;
@@ -1162,8 +1162,10 @@ __global__ __launch_bounds__(kThreads) void evict_put_back_kernel(TableRef t, co
 // key range, and one workgroup per part of a bin picks the part's entries out of the bin,
 // sorts them in LDS and writes them out. Keys are digests, so the parts of an ordinary
 // table are even; when one holds more than kPartMax entries or a bin more than kBinMax (a
-// skewed key set), all entries go through the radix sort instead, decided on the device.
-// 20 M entries of 2^25 slots: 1.0 ms (count 90 us, spread 394, parts 430), against 3.0 ms for
+// skewed key set, a table above 2^27 slots beyond the load that kMaxAllParts allows, a replayed
+// graph whose table has outgrown the bound it was captured with), all entries go through the
+// radix sort instead, decided on the device.
+// 20 M entries of 2^25 slots: 1.0 ms (count 86 us, spread 398, parts 430), against 3.0 ms for
 // eight digit passes and a gather of the values. Bound by the chains inside a workgroup: the
 // table is read twice and the entries are written and read once, 0.3 ms at HBM rate.
 constexpr uint32_t kSpreadThreads = 1024;

@@ -1,7 +1,11 @@
 // Device-wide LSD radix sort of (key, index) pairs for the table's maintenance calls
 // (eviction order and export order) and the address map's update (removals and
 // additions by start), written for gfx950 so those calls enqueue kernels only (no
-// library sort, no memsets): a caller may capture them in a HIP graph.
+// library sort, no memsets): a caller may capture them in a HIP graph. Published methods: one
+// histogram of every pass ahead of the passes is Onesweep's (Adinets and Merrill, "Onesweep:
+// A Faster Least Significant Digit Radix Sort for GPUs", 2022), the running sums passed from
+// workgroup to workgroup are decoupled look-back (Merrill and Garland, "Single-pass Parallel
+// Prefix Scan with Decoupled Look-back", 2016).
 //
 // Keys are 64 or 128 bits (hi:lo), indices u32. Each pass sorts by one 8-bit digit,
 // stably, over 4096-element tiles. Launches: one clear, one histogram of every digit of

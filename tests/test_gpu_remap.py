@@ -425,11 +425,12 @@ def test_small_update_of_a_large_map(cap):
         assert_map(m, om, "large")
 
 
-@pytest.mark.parametrize("count", [131_072, 131_073, 262_144, 262_145, 400_003])
-def test_runs_of_whole_lines(count):
-    """Past 8,192 intervals a fence entry covers a multiple of 16 starts, which 16 lanes read
-    as one or two lines, after narrowing longer runs to 32: counts on both sides of a run of
-    16, 32 and 48, every interval edge probed, in a map with no room to spare."""
+@pytest.mark.parametrize("count", [32_768, 32_769, 131_072, 131_073, 131_088, 262_144, 262_145, 400_003])
+def test_fence_runs(count):
+    """Past 8,192 intervals a fence entry covers a run of ceil(count / 8192) starts, which each
+    lane halves by itself: counts on both sides of runs of 4, 16 and 32 starts (the halving
+    takes another step past each), a last run of one start (131,088 in runs of 17) and longer
+    runs, every interval edge probed, in a map with no room to spare."""
     rng = np.random.default_rng(count)
     start = np.sort(rng.choice(1 << 30, count, replace=False).astype(np.uint64)) * np.uint64(4)
     length = rng.integers(1, 5, count, dtype=np.uint64)
